@@ -1,0 +1,608 @@
+// The operator on vector-major blocks: y_v = c0_v (H0 - E) x_v + cp_v H+ x_v + cm_v H- x_v
+// (P(z): 1, z, 1/z) for cbs_apply, cbs_apply_noalloc, cbs_apply_parts, the bands' filter, the
+// Rayleigh-Ritz projections and the adjoint.
+//
+// Three kernels read the caller's x and write its y, with no staging copy of either; the
+// coefficients travel as kernel arguments (64 vectors a call), so nothing is copied from the
+// host and nothing has to outlive the launch:
+//   k_ap_bra    K[atom][w][i] = h_ai sum_w' coef(w' - w) sum_e u_{e,i} x(idx_e)
+//   k_ap_local  y = finite differences, potential and cell phases of x (+ beta prev)
+//   k_ap_ket    y += sum_i u_{e,i} K[a_e][w_e][i], on the matrix cores, over the 64-point
+//               groups that lie in a ball
+// The BiCG kernels (stencil.hip, nonlocal.hip) keep a run's primal and dual side by side; here
+// a vector stands alone, which halves the registers of the z queue and lets a cell be cut into
+// z segments until the chip is full.
+#include <algorithm>
+#include <type_traits>
+#include <vector>
+
+#include "cbs_internal.hpp"
+
+namespace cbs {
+
+constexpr int AP_VMAX = 64;   // vectors per launch (their coefficients: 3 KB of kernel arguments)
+constexpr int AP_VG = 8;      // vectors per ket group: 16 MFMA columns (re, im)
+
+struct ApCoef {
+  double2 c0[AP_VMAX], cp[AP_VMAX], cm[AP_VMAX];
+};
+
+template <typename R> struct apmf4;
+template <> struct apmf4<double> { typedef double T __attribute__((ext_vector_type(4))); };
+template <> struct apmf4<float> { typedef float T __attribute__((ext_vector_type(4))); };
+__device__ __forceinline__ apmf4<double>::T ap_mfma(double a, double b, apmf4<double>::T c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ apmf4<float>::T ap_mfma(float a, float b, apmf4<float>::T c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// ------------------------------------------------------------------ local part
+template <typename R>
+struct ApLocal {
+  int32_t nx, ny, nz, ty, ntiles, nseg, zlen, nlogical, nbuf;
+  int64_t N;
+  double kin, E, beta;
+  double c[5], zc[5];   // second-derivative weights, and the same times kin
+  const R* vloc;
+  const double* vloc64;
+  const cplx<R>* x;
+  const cplx<R>* prev;   // or NULL
+  cplx<R>* y;
+};
+
+// One workgroup: one vector, TY full x rows, z planes [z0, z1).  The owned planes are staged in
+// LDS for the x and y neighbours (next plane's loads in flight while this one is computed); the
+// p planes on either side are read for the owned column only, all at once.  Every thread keeps
+// the 2p+1 partial outputs of its column in registers, so a plane is read once for the z
+// direction.  R: storage, C: arithmetic precision.  Bound by HBM on large cells: 96x96x32, 24
+// complex128 vectors without projectors, 66 us for 226 MB (3.4 TB/s); the pair kernel with its two
+// layout passes took 200 us.  48x48x32, 32 vectors: 24 us (was 111 + 37 us of layout passes).
+// PIPE: every thread stages at most two elements of a plane; ADD: beta prev is added.
+template <typename R, typename C, int P, bool PIPE, bool ADD>
+__global__ void __launch_bounds__(1024) k_ap_local(ApLocal<R> a, ApCoef cf) {
+  extern __shared__ __align__(16) unsigned char ap_smem[];
+  cplx<R>* lds = reinterpret_cast<cplx<R>*>(ap_smem);
+  const int lb = remap_active(blockIdx.x, a.nlogical);
+  if (lb < 0) return;
+  const int per = a.ntiles * a.nseg;
+  const int v = lb / per;
+  const int rem = lb - v * per;
+  const int seg = rem / a.ntiles;
+  const int tile = rem - seg * a.ntiles;
+  const int z0 = seg * a.zlen, z1 = min(z0 + a.zlen, a.nz);
+  if (z0 >= z1) return;
+  const int nx = a.nx, ny = a.ny, nz = a.nz, TY = a.ty;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int tx = tid % nx, ty = tid / nx;
+  const int y = tile * TY + ty;
+  const bool own = ty < TY && y < ny;
+  const int64_t plane = (int64_t)nx * ny;
+  const int region = (TY + 2 * P) * nx;
+  const int col = own ? tx + nx * y : 0;
+  const cplx<R>* xv = a.x + (int64_t)v * a.N;
+  cplx<R>* yv = a.y + (int64_t)v * a.N;
+  const cplx<R>* pv = ADD ? a.prev + (int64_t)v * a.N : nullptr;
+  const cplx<C> c0 = ccast<C, double>(cf.c0[v]), cp = ccast<C, double>(cf.cp[v]), cm = ccast<C, double>(cf.cm[v]);
+  const C E = (C)a.E, kin = (C)a.kin, beta = (C)a.beta;
+  C cc[P + 1], zc[P + 1];
+#pragma unroll
+  for (int j = 0; j <= P; ++j) {
+    cc[j] = (C)a.c[j];
+    zc[j] = (C)a.zc[j];
+  }
+  // staging: offset within a plane of each element this thread brings in
+  constexpr int PF = 2;
+  const bool pipe = region <= PF * nthr;
+  auto plane_off = [&](int e) {
+    const int r = e / nx;
+    int gy = (tile * TY - P + r) % ny;
+    gy += (gy < 0) ? ny : 0;
+    return e - r * nx + nx * gy;
+  };
+  int soff[PF];
+#pragma unroll
+  for (int k = 0; k < PF; ++k) soff[k] = (tid + k * nthr < region) ? plane_off(tid + k * nthr) : 0;
+  R sre[PF] = {}, sim[PF] = {};
+  auto issue = [&](int m) {
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {   // past the region: element 0, not stored
+      const cplx<R> t = xv[plane * m + soff[k]];
+      sre[k] = t.x;
+      sim[k] = t.y;
+    }
+  };
+  // x neighbours within a row of LDS (nx may be smaller than p: several wraps)
+  int xl[P], xr[P];
+#pragma unroll
+  for (int j = 1; j <= P; ++j) {
+    int l = tx - j, r = tx + j;
+    while (l < 0) l += nx;
+    while (r >= nx) r -= nx;
+    xl[j - 1] = l;
+    xr[j - 1] = r;
+  }
+  cplx<R> halo[P];
+  auto load_halo = [&](int m0) {   // the owned column of planes m0 .. m0 + P - 1 (wrapped into the cell)
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      int iz = m0 + j;
+      iz += (iz < 0) ? nz : 0;
+      iz -= (iz >= nz) ? nz : 0;
+      halo[j] = xv[plane * iz + col];
+    }
+  };
+  cplx<C> acc[2 * P + 1];
+#pragma unroll
+  for (int d = 0; d <= 2 * P; ++d) acc[d] = mkc<C>(0, 0);
+  // plane m contributes s to outputs m - P .. m + P; output m - P is then complete
+  auto push = [&](int m, cplx<C> s, cplx<C> in_plane) {
+    const int o = m - P;
+    const int64_t at = plane * max(o, z0) + col;
+    cplx<R> add;
+    if constexpr (ADD) add = pv[at];
+    acc[P] = cadd<C>(acc[P], in_plane);
+#pragma unroll
+    for (int d = 0; d <= 2 * P; ++d) acc[d] = cfma_r<C>(acc[d], zc[d > P ? d - P : P - d], s);
+    if (own && o >= z0) {
+      cplx<C> out = acc[0];
+      if constexpr (ADD) out = cfma_r<C>(out, beta, ccast<C, R>(add));
+      yv[at] = ccast<R, C>(out);
+    }
+#pragma unroll
+    for (int d = 0; d < 2 * P; ++d) acc[d] = acc[d + 1];
+    acc[2 * P] = mkc<C>(0, 0);
+  };
+  auto phase = [&](int m, cplx<C> s) {
+    const C re = m < 0 ? cm.x : m >= nz ? cp.x : c0.x, im = m < 0 ? cm.y : m >= nz ? cp.y : c0.y;
+    return cmul<C>(mkc<C>(re, im), s);
+  };
+
+  auto pot = [&](int m) { return (sizeof(C) == 8) ? (C)a.vloc64[plane * m + col] : (C)a.vloc[plane * m + col]; };
+  load_halo(z0 - P);
+  C vl = pot(z0);
+  if constexpr (PIPE) issue(z0);
+#pragma unroll
+  for (int j = 0; j < P; ++j) push(z0 - P + j, phase(z0 - P + j, ccast<C, R>(halo[j])), mkc<C>(0, 0));
+  auto owned = [&](int m, bool last) {
+    cplx<R>* buf = lds + ((a.nbuf == 2) ? ((m - z0) & 1) * region : 0);
+    if (a.nbuf == 1 && m > z0) __syncthreads();   // single buffer: the previous plane is fully read
+    const C vd = vl - E;
+    if constexpr (PIPE) {
+#pragma unroll
+      for (int k = 0; k < PF; ++k)
+        if (tid + k * nthr < region) buf[tid + k * nthr] = mkc<R>(sre[k], sim[k]);
+    } else {
+      for (int e = tid; e < region; e += nthr) buf[e] = xv[plane * m + plane_off(e)];
+    }
+    if (last) {
+      load_halo(z1);
+    } else {
+      vl = pot(m + 1);
+      if constexpr (PIPE) issue(m + 1);
+    }
+    __syncthreads();
+    cplx<C> s = mkc<C>(0, 0), in_plane = s;
+    if (own) {
+      const int row = (ty + P) * nx;
+      const cplx<C> c = ccast<C, R>(buf[row + tx]);
+      cplx<C> t = cscale<C>(c, (C)2 * cc[0]);
+#pragma unroll
+      for (int j = 1; j <= P; ++j) {
+        const cplx<C> l = ccast<C, R>(buf[row + xl[j - 1]]), r = ccast<C, R>(buf[row + xr[j - 1]]);
+        const cplx<C> d = ccast<C, R>(buf[row - j * nx + tx]), u = ccast<C, R>(buf[row + j * nx + tx]);
+        t = cfma_r<C>(t, cc[j], cadd<C>(cadd<C>(l, r), cadd<C>(d, u)));
+      }
+      t = cfma_r<C>(cscale<C>(t, kin), vd, c);
+      in_plane = cmul<C>(c0, t);
+      s = cmul<C>(c0, c);
+    }
+    push(m, s, in_plane);
+  };
+  for (int m = z0; m < z1 - 1; ++m) owned(m, false);
+  owned(z1 - 1, true);
+#pragma unroll
+  for (int j = 0; j < P; ++j) push(z1 + j, phase(z1 + j, ccast<C, R>(halo[j])), mkc<C>(0, 0));
+}
+
+// ------------------------------------------------------------------ bra
+// Sums of NV values over the wave: each halving step exchanges the half of the values that the
+// other lane keeps, so NV + 6 - log2(NV) shuffles replace 6 NV.  Lane l ends with the sum of
+// value l * NV / 64.
+template <int NV, typename C>
+__device__ __forceinline__ C wave_sums(C (&v)[NV], int lane) {
+  int off = 32;
+#pragma unroll
+  for (int w = NV / 2; w >= 1; w >>= 1, off >>= 1) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int k = 0; k < w; ++k) {
+      const C lo = v[k], hi = v[k + w];
+      v[k] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, 64);
+    }
+  }
+  C t = v[0];
+  for (; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
+  return t;
+}
+
+template <typename R>
+struct ApBra {
+  int32_t n_atoms, nv, nvb, nlogical;
+  int64_t N;
+  const int32_t* seg;
+  const int32_t* idx;
+  const R* u;       // [nnz][4]
+  const R* coeff;   // [n_atoms][4]
+  const cplx<R>* x;
+  R* kt;            // per group of AP_VG vectors: [atom * 3 + w][i][2 * vectors of the group]
+};
+
+// One workgroup: one atom, VB vectors; a thread takes every 256th ball entry (one table read for
+// VB coalesced gathers) and the sums of each cell shift are added over the lanes and waves.  The
+// 4 projectors would fill a quarter of an MFMA tile, and the vector units have the same FP64 rate.
+// Bound by the gathers that miss L2 (overlapping balls; consecutive workgroups of an XCD share
+// the vectors): 48x48x32, 96 atoms, 32 vectors: 38 us in complex128, 24 in complex64, where one
+// MFMA workgroup per (atom, 16 pairs) took 145 and 194; with 512 threads 45 us, with the atoms'
+// vectors side by side on an XCD 46 us.
+template <typename R, typename C, int VB>
+__global__ void __launch_bounds__(256) k_ap_bra(ApBra<R> a, ApCoef cf) {
+  __shared__ C red[4][3][8 * VB];   // [wave][shift][(vector, i, re/im)]
+  const int lb = remap_active(blockIdx.x, a.nlogical);
+  if (lb < 0) return;
+  const int vb = lb / a.n_atoms, atom = lb - vb * a.n_atoms;
+  const int v0 = vb * VB;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  using U4 = typename vec4<R>::T;
+  const U4* ut = reinterpret_cast<const U4*>(a.u);
+  const cplx<R>* xv[VB];
+#pragma unroll
+  for (int k = 0; k < VB; ++k) xv[k] = a.x + (int64_t)min(v0 + k, a.nv - 1) * a.N;
+  for (int sg = 0; sg < 3; ++sg) {
+    const int lo = a.seg[4 * atom + sg], hi = a.seg[4 * atom + sg + 1];
+    C acc[8 * VB];
+#pragma unroll
+    for (int k = 0; k < 8 * VB; ++k) acc[k] = 0;
+    // two entries a step; their gathers go out together with the next step's indices; loads past
+    // the segment are clamped into it and weighted by zero
+    const int last = max(hi - 1, lo);
+    int n0 = 0, n1 = 0;
+    if (lo < hi) {
+      n0 = a.idx[min(lo + tid, last)];
+      n1 = a.idx[min(lo + 256 + tid, last)];
+    }
+    for (int e0 = lo; e0 < hi; e0 += 512) {
+      const int ea = e0 + tid, eb = ea + 256;
+      const U4 ua = ut[min(ea, last)], ub = ut[min(eb, last)];
+      cplx<R> ta[VB], tb[VB];
+#pragma unroll
+      for (int k = 0; k < VB; ++k) ta[k] = xv[k][n0];
+#pragma unroll
+      for (int k = 0; k < VB; ++k) tb[k] = xv[k][n1];
+      n0 = a.idx[min(ea + 512, last)];
+      n1 = a.idx[min(eb + 512, last)];
+      const C oa = ea < hi ? (C)1 : (C)0, ob = eb < hi ? (C)1 : (C)0;
+      const C wa[4] = {oa * (C)ua.x, oa * (C)ua.y, oa * (C)ua.z, oa * (C)ua.w};
+      const C wb[4] = {ob * (C)ub.x, ob * (C)ub.y, ob * (C)ub.z, ob * (C)ub.w};
+#pragma unroll
+      for (int k = 0; k < VB; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[8 * k + 2 * i] += wa[i] * (C)ta[k].x;
+          acc[8 * k + 2 * i + 1] += wa[i] * (C)ta[k].y;
+        }
+#pragma unroll
+      for (int k = 0; k < VB; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[8 * k + 2 * i] += wb[i] * (C)tb[k].x;
+          acc[8 * k + 2 * i + 1] += wb[i] * (C)tb[k].y;
+        }
+    }
+    C t = 0;
+    if (lo < hi) t = wave_sums<8 * VB, C>(acc, lane);   // uniform over the workgroup
+    if ((lane & (64 / (8 * VB) - 1)) == 0) red[wv][sg][lane / (64 / (8 * VB))] = t;
+  }
+  __syncthreads();
+  // wave k: the 12 coefficients of vector v0 + k
+  const int k = __builtin_amdgcn_readfirstlane(wv), v = v0 + k;
+  if (k >= VB || v >= a.nv || lane >= 12) return;
+  const int w = lane >> 2, i = lane & 3, q = 8 * k + 2 * i;
+  const double2 d0 = cf.c0[v], dp = cf.cp[v], dm = cf.cm[v];
+  cplx<C> s = mkc<C>(0, 0);
+#pragma unroll
+  for (int w2 = 0; w2 < 3; ++w2) {
+    const int d = w2 - w;   // cell shift of the source relative to the entry
+    if (d > 1 || d < -1) continue;
+    const cplx<C> cd = mkc<C>((C)(d == 0 ? d0.x : d == 1 ? dp.x : dm.x), (C)(d == 0 ? d0.y : d == 1 ? dp.y : dm.y));
+    const cplx<C> g = mkc<C>(red[0][w2][q] + red[1][w2][q] + red[2][w2][q] + red[3][w2][q],
+                             red[0][w2][q + 1] + red[1][w2][q + 1] + red[2][w2][q + 1] + red[3][w2][q + 1]);
+    s = cfma<C>(s, cd, g);
+  }
+  s = cscale<C>(s, (C)a.coeff[4 * atom + i]);
+  const int vg = v / AP_VG, ncol = 2 * min(AP_VG, a.nv - vg * AP_VG);
+  R* dst = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + ((int64_t)(atom * 3 + w) * 4 + i) * ncol +
+           2 * (v - vg * AP_VG);
+  dst[0] = (R)s.x;
+  dst[1] = (R)s.y;
+}
+
+// ------------------------------------------------------------------ ket
+template <typename R>
+struct ApKet {
+  int32_t n_atoms, nv, nvg, nlogical;
+  int64_t N;
+  const int32_t* grp_off;
+  const int32_t* grp_key;
+  const int32_t* grp_mask;
+  const R* grp_u;
+  const R* kt;
+  cplx<R>* y;
+};
+
+// A workgroup adds the ket of one 64-point group to AP_VG vectors: U [64 points x 4] (grouped
+// table) times K [4 x 16 columns] summed over the group's keys with MFMA 16x16x4 in four 16-point
+// row blocks (those the key's mask names).  A group in the middle of many balls has sixty keys and
+// each batch of them is one memory latency, so the four waves take every fourth key; their
+// products are added through LDS in wave order and wave w updates vectors 2w and 2w + 1, lane =
+// point.  Groups outside every ball touch nothing.  The vector groups vary fastest: they share a
+// group's table slice in one XCD's L2.  48x48x32, 96 atoms, 32 vectors: 31 us in complex128 (the
+// vectors and 27 MB of table, 3.3 TB/s), 24 in complex64; one wave per group 31 and 28, one
+// thread per point and pair 115 and 61.
+template <typename R, typename C>
+__global__ void __launch_bounds__(256) k_ap_ket(ApKet<R> a) {
+  constexpr int KB = 2;   // keys per batch (4: one wave less per SIMD, 36 us)
+  __shared__ C tile[4][KG][17];
+  const int lb = remap_active(blockIdx.x, a.nlogical);
+  if (lb < 0) return;
+  const int g = lb / a.nvg, vg = lb - g * a.nvg;
+  const int e0 = a.grp_off[g], e1 = a.grp_off[g + 1];
+  if (e0 == e1) return;   // uniform over the workgroup
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nvec = min(AP_VG, a.nv - vg * AP_VG), ncol = 2 * nvec;
+  // the vectors' values are requested first: their latency passes under the contraction
+  const int64_t n = (int64_t)g * KG + lane, nc = min(n, a.N - 1);
+  cplx<R>* yp = a.y + (int64_t)vg * AP_VG * a.N + nc;
+  const cplx<R> y0 = yp[(int64_t)min(2 * wv, nvec - 1) * a.N], y1 = yp[(int64_t)min(2 * wv + 1, nvec - 1) * a.N];
+  const int orow = lane & 15, ok4 = lane >> 4;
+  const R* kcol = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + (int64_t)ok4 * ncol + min(orow, ncol - 1);
+  typename apmf4<C>::T acc[4];
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb) acc[rb] = {0, 0, 0, 0};
+  for (int eb = e0; eb < e1; eb += 256) {
+    // lane j holds this wave's key number j: entry eb + 4 j + wv of the group
+    const int mine = eb + 4 * lane + wv;
+    const int nk = min(64, (e1 - eb - wv + 3) >> 2);
+    const int keyv = (mine < e1) ? a.grp_key[mine] : 0;
+    const int maskv = (mine < e1) ? a.grp_mask[mine] : 0;
+    C kbA[KB], ubA[KB][4], kbB[KB], ubB[KB][4];
+    int mA[KB], mB[KB];
+    auto load = [&](int j0, C (&kb)[KB], C (&ub)[KB][4], int (&m)[KB]) {
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        const bool valid = j0 + j < nk;   // wave-uniform
+        const int jj = valid ? j0 + j : 0;
+        const int key = __builtin_amdgcn_readlane(keyv, jj);
+        m[j] = valid ? __builtin_amdgcn_readlane(maskv, jj) : 0;
+        kb[j] = (C)kcol[((key >> 2) * 3 + (key & 3)) * 4 * ncol];
+        const R* up = a.grp_u + ((int64_t)(eb + 4 * jj + wv) * KG + orow) * 4 + ok4;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) ub[j][rb] = ((m[j] >> rb) & 1) ? (C)up[64 * rb] : (C)0;
+      }
+    };
+    auto mma = [&](const C (&kb)[KB], const C (&ub)[KB][4], const int (&m)[KB]) {
+#pragma unroll
+      for (int j = 0; j < KB; ++j)
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb)
+          if ((m[j] >> rb) & 1) acc[rb] = ap_mfma(ub[j][rb], kb[j], acc[rb]);
+    };
+    load(0, kbA, ubA, mA);
+    for (int j0 = 0; j0 < nk; j0 += 2 * KB) {
+      load(j0 + KB, kbB, ubB, mB);
+      mma(kbA, ubA, mA);
+      if (j0 + KB >= nk) break;
+      load(j0 + 2 * KB, kbA, ubA, mA);
+      mma(kbB, ubB, mB);
+    }
+  }
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tile[wv][16 * rb + mfma16_row<C>(lane, v)][orow] = acc[rb][v];
+  __syncthreads();
+  if (n >= a.N) return;
+  C t[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    t[c] = ((tile[0][lane][4 * wv + c] + tile[1][lane][4 * wv + c]) + tile[2][lane][4 * wv + c]) +
+           tile[3][lane][4 * wv + c];
+  if (2 * wv < nvec) yp[(int64_t)(2 * wv) * a.N] = mkc<R>((R)((C)y0.x + t[0]), (R)((C)y0.y + t[1]));
+  if (2 * wv + 1 < nvec) yp[(int64_t)(2 * wv + 1) * a.N] = mkc<R>((R)((C)y1.x + t[2]), (R)((C)y1.y + t[3]));
+}
+
+// ------------------------------------------------------------------ launches
+size_t apply_kt_bytes(const cbs_system* s, int32_t n_vec, size_t real_bytes) {
+  const int64_t nv = std::min(n_vec, AP_VMAX);
+  return (size_t)nv * s->proj.n_atoms * 24 * real_bytes;
+}
+
+// Rows per workgroup and z segments of k_ap_local: the pair with the least modelled time.  A
+// workgroup's march costs its owned planes (staged rows with their halo, plus the points worked
+// on) and 2p halo columns, or, when few points are in flight, one latency a plane (as long as
+// 1500 points take); a CU holds 16 waves, and a launch runs in whole rounds of the chip.  Against
+// every (rows, segments) pair on thirteen cells and block sizes from 8x8x12 to 160x160x48 the
+// choice is within 6 % of the fastest call (19 % on 21x70x16), where the worst pairs take twice
+// as long: 96x96x32, 24 vectors: 76 us with 10 rows in one segment, 127 us with 8.
+static void ap_shape(const cbs_system* s, int32_t nv, size_t elem, int32_t* ty, int32_t* nseg) {
+  const int p = s->p, nx = s->nx;
+  double best = 0;
+  *ty = *nseg = 1;
+  for (int t = 1; t <= s->ny && (t == 1 || nx * t <= 1024); ++t) {
+    if (t > 1 && (size_t)(t + 2 * p) * nx * elem > 64 * 1024) break;
+    const int ntiles = (s->ny + t - 1) / t, waves = (nx * t + 63) / 64, percu = std::max(1, 16 / waves);
+    const bool pipe = (t + 2 * p) * nx <= 128 * waves;
+    for (int ns = 1; ns <= std::max(1, s->nz / p); ++ns) {
+      const int zlen = (s->nz + ns - 1) / ns;
+      const int64_t nb = (int64_t)nv * ntiles * ((s->nz + zlen - 1) / zlen);
+      const int64_t rounds = (nb + 256 * percu - 1) / (256 * percu);
+      const double conc = (double)std::min<int64_t>(percu, (nb + 255) / 256);   // workgroups sharing a CU
+      const double plane = (t + 2 * p) * nx + 2.0 * nx * t, halo = (double)nx * t;
+      const double work = conc * (zlen * plane + 0.5 * 2 * p * halo);
+      const double lat = 1500.0 * (zlen * (pipe ? 1.0 : 2.0) + 2 * p * 0.25);
+      const double cost = (double)rounds * std::max(work, lat);
+      if (best == 0 || cost < best) {
+        best = cost;
+        *ty = t;
+        *nseg = ns;
+      }
+    }
+  }
+}
+
+template <typename R, typename C, int P, bool PIPE>
+static void ap_local_pp(const ApLocal<R>& a, const ApCoef& cf, dim3 grid, dim3 blk, size_t smem, hipStream_t st) {
+  if constexpr (sizeof(R) == 8) {   // only the bands' filter (complex128) adds a second block
+    if (a.prev != nullptr) {
+      hipLaunchKernelGGL((k_ap_local<R, C, P, PIPE, true>), grid, blk, smem, st, a, cf);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_ap_local<R, C, P, PIPE, false>), grid, blk, smem, st, a, cf);
+}
+
+template <typename R, typename C, int P>
+static void ap_local_p(const ApLocal<R>& a, const ApCoef& cf, bool pipe, int nthr, size_t smem, hipStream_t st) {
+  const dim3 grid((a.nlogical + 7) / 8 * 8), blk(nthr);
+  if (pipe) ap_local_pp<R, C, P, true>(a, cf, grid, blk, smem, st);
+  else ap_local_pp<R, C, P, false>(a, cf, grid, blk, smem, st);
+}
+
+template <typename R, typename C>
+static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef& cf, const cplx<R>* x, cplx<R>* y,
+                         R* kt, const cplx<R>* prev, double beta, hipStream_t st) {
+  const Projector& pr = s->proj;
+  const bool f64 = std::is_same<R, double>::value;
+  if (pr.n_atoms > 0) {
+    ApBra<R> b;
+    b.n_atoms = pr.n_atoms;
+    b.nv = nv;
+    b.N = s->N;
+    b.seg = pr.seg;
+    b.idx = pr.ball_idx;
+    b.u = f64 ? (const R*)pr.ball_u64 : (const R*)pr.ball_u32;
+    b.coeff = f64 ? (const R*)pr.coeff64 : (const R*)pr.coeff32;
+    b.x = x;
+    b.kt = kt;
+    const int vb = nv >= 4 ? 4 : 1;
+    b.nvb = (nv + vb - 1) / vb;
+    b.nlogical = b.nvb * pr.n_atoms;
+    const int grid = (b.nlogical + 7) / 8 * 8;
+    if (vb == 4) hipLaunchKernelGGL((k_ap_bra<R, C, 4>), dim3(grid), dim3(256), 0, st, b, cf);
+    else hipLaunchKernelGGL((k_ap_bra<R, C, 1>), dim3(grid), dim3(256), 0, st, b, cf);
+    CBS_HIP(hipGetLastError());
+  }
+  ApLocal<R> a;
+  int32_t ty = 1, nseg = 1;
+  ap_shape(s, nv, sizeof(cplx<R>), &ty, &nseg);
+  a.nx = s->nx;
+  a.ny = s->ny;
+  a.nz = s->nz;
+  a.ty = ty;
+  a.ntiles = (s->ny + ty - 1) / ty;
+  a.zlen = (s->nz + nseg - 1) / nseg;
+  a.nseg = (s->nz + a.zlen - 1) / a.zlen;
+  a.nlogical = nv * a.ntiles * a.nseg;
+  const size_t one = (size_t)(ty + 2 * s->p) * s->nx * sizeof(cplx<R>);
+  a.nbuf = (2 * one <= 64 * 1024) ? 2 : 1;
+  a.N = s->N;
+  a.kin = -0.5 / (s->h * s->h);
+  a.E = E;
+  a.beta = beta;
+  for (int i = 0; i < 5; ++i) {
+    a.c[i] = s->fd[i];
+    a.zc[i] = a.kin * s->fd[i];
+  }
+  a.vloc = f64 ? (const R*)s->vloc64 : (const R*)s->vloc32;
+  a.vloc64 = s->vloc64;
+  a.x = x;
+  a.prev = prev;
+  a.y = y;
+  const int nthr = (s->nx * ty + 63) / 64 * 64;
+  const bool pipe = (ty + 2 * s->p) * s->nx <= 2 * nthr;
+  switch (s->p) {
+    case 1: ap_local_p<R, C, 1>(a, cf, pipe, nthr, a.nbuf * one, st); break;
+    case 2: ap_local_p<R, C, 2>(a, cf, pipe, nthr, a.nbuf * one, st); break;
+    case 3: ap_local_p<R, C, 3>(a, cf, pipe, nthr, a.nbuf * one, st); break;
+    case 4: ap_local_p<R, C, 4>(a, cf, pipe, nthr, a.nbuf * one, st); break;
+    default: set_error("unsupported finite-difference half-width %d", s->p); return CBS_EINVAL;
+  }
+  CBS_HIP(hipGetLastError());
+  if (pr.n_atoms > 0) {
+    ApKet<R> k;
+    k.n_atoms = pr.n_atoms;
+    k.nv = nv;
+    k.nvg = (nv + AP_VG - 1) / AP_VG;
+    k.N = s->N;
+    k.nlogical = (int32_t)((s->N + KG - 1) / KG) * k.nvg;
+    k.grp_off = pr.grp_off;
+    k.grp_key = pr.grp_key;
+    k.grp_mask = pr.grp_mask;
+    k.grp_u = f64 ? (const R*)pr.grp_u64 : (const R*)pr.grp_u32;
+    k.kt = kt;
+    k.y = y;
+    hipLaunchKernelGGL((k_ap_ket<R, C>), dim3((k.nlogical + 7) / 8 * 8), dim3(256), 0, st, k);
+    CBS_HIP(hipGetLastError());
+  }
+  return CBS_OK;
+}
+
+template <typename R>
+int32_t launch_apply(const cbs_system* s, double E, int32_t n_vec, const double2* c0, const double2* cp,
+                     const double2* cm, const void* x, void* y, void* kt, const void* prev, double beta,
+                     hipStream_t st) {
+  const bool f32 = std::is_same<R, float>::value && lo_arith_fp32();
+  for (int32_t v0 = 0; v0 < n_vec; v0 += AP_VMAX) {
+    const int32_t nv = std::min(AP_VMAX, n_vec - v0);
+    ApCoef cf;
+    for (int32_t v = 0; v < AP_VMAX; ++v) {
+      const double2 z = make_double2(0, 0);
+      cf.c0[v] = v < nv ? c0[v0 + v] : z;
+      cf.cp[v] = v < nv ? cp[v0 + v] : z;
+      cf.cm[v] = v < nv ? cm[v0 + v] : z;
+    }
+    const int64_t off = (int64_t)v0 * s->N;
+    const cplx<R>* xx = (const cplx<R>*)x + off;
+    const cplx<R>* pp = (prev != nullptr) ? (const cplx<R>*)prev + off : nullptr;
+    cplx<R>* yy = (cplx<R>*)y + off;
+    if constexpr (std::is_same<R, float>::value) {
+      if (f32) {
+        CBS_TRY((ap_launch<R, float>(s, E, nv, cf, xx, yy, (R*)kt, pp, beta, st)));
+        continue;
+      }
+    }
+    CBS_TRY((ap_launch<R, double>(s, E, nv, cf, xx, yy, (R*)kt, pp, beta, st)));
+  }
+  return CBS_OK;
+}
+
+template int32_t launch_apply<double>(const cbs_system*, double, int32_t, const double2*, const double2*,
+                                      const double2*, const void*, void*, void*, const void*, double, hipStream_t);
+template int32_t launch_apply<float>(const cbs_system*, double, int32_t, const double2*, const double2*,
+                                     const double2*, const void*, void*, void*, const void*, double, hipStream_t);
+
+// Coefficients (1, z, 1/z) of P(z) for n vectors.
+void apply_coefs(int32_t n, const double* z, std::vector<double2>& c0, std::vector<double2>& cp,
+                 std::vector<double2>& cm) {
+  c0.assign(n, make_double2(1, 0));
+  cp.resize(n);
+  cm.resize(n);
+  for (int32_t v = 0; v < n; ++v) {
+    const double zr = z[2 * v], zi = z[2 * v + 1], d = zr * zr + zi * zi;
+    cp[v] = make_double2(zr, zi);
+    cm[v] = make_double2(zr / d, -zi / d);
+  }
+}
+
+}  // namespace cbs

@@ -340,19 +340,25 @@ int32_t launch_ket_add(const cbs_system* s, int32_t nruns, void* q, const void* 
 
 int32_t update_chunks(const cbs_system* s);
 
-// Utility conversions between vector-major [v][N] and pair layout.
+// The operator on vector-major blocks (apply.hip): y_v = c0 (H0 - E) x_v + cp H+ x_v + cm H- x_v
+// (+ beta prev_v), coefficients on the host (passed as kernel arguments), kt: scratch of
+// apply_kt_bytes for the projector coefficients.  x and y must not overlap; prev may be y.
+size_t apply_kt_bytes(const cbs_system* s, int32_t n_vec, size_t real_bytes);
 template <typename R>
-int32_t launch_to_pairs(int64_t N, int32_t nvec, const void* x, void* pairs, hipStream_t st);
-template <typename R>
-int32_t launch_from_pairs(int64_t N, int32_t nvec, const void* pairs, void* y, hipStream_t st);
+int32_t launch_apply(const cbs_system* s, double E, int32_t n_vec, const double2* c0, const double2* cp,
+                     const double2* cm, const void* x, void* y, void* kt, const void* prev, double beta,
+                     hipStream_t st);
+void apply_coefs(int32_t n, const double* z, std::vector<double2>& c0, std::vector<double2>& cp,
+                 std::vector<double2>& cm);
 
 // Device address of the fixed scratch array of cbs_apply_noalloc on `device` (current),
 // looked up once per device (noalloc.hip).
 int32_t noalloc_scratch(int32_t device, void** out);
 
-// Parts-form apply on complex128 vectors (used by the solver's Rayleigh-Ritz step).
+// Parts-form apply on complex128 vectors (Rayleigh-Ritz, bands, adjoint), asynchronous;
+// with prev, beta prev is added.
 int32_t apply_parts_dev(cbs_system* s, double E, int32_t n_vec, const double2* c0,
                         const double2* cp, const double2* cm, const double2* x, double2* y,
-                        hipStream_t st);
+                        hipStream_t st, const double2* prev = nullptr, double beta = 0.0);
 
 }  // namespace cbs

@@ -47,22 +47,11 @@ int32_t noalloc_scratch(int32_t device, void** out) {
   return CBS_OK;
 }
 
-// Run coefficients of up to kCoefChunk runs, passed by value as kernel arguments (no host
-// staging copy) and written into the scratch array by one small kernel.
-constexpr int kCoefChunk = 24;
-struct CoefChunk {
-  RunCoef c[kCoefChunk];
-};
-
-__global__ void k_put_coef(CoefChunk chunk, int32_t n, RunCoef* dst) {
-  const int i = threadIdx.x;
-  if (i < n) dst[i] = chunk.c[i];
-}
-
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Bytes of scratch one call needs: run coefficients, the two pair buffers and the ket
-// coefficients, each 256-byte aligned.
+// Bytes of scratch a call is admitted by (the limit that callers rely on): per pair of vectors its
+// coefficients, two staging vectors and the projector coefficients, each 256-byte aligned.  The
+// kernels use less of it: the projector coefficients, and a copy of x when y overlaps it.
 static size_t need_bytes(const cbs_system* s, int32_t n_vec, size_t pair_bytes) {
   const size_t nr = (size_t)(n_vec + 1) / 2;
   size_t b = align256(nr * sizeof(RunCoef));
@@ -74,54 +63,15 @@ static size_t need_bytes(const cbs_system* s, int32_t n_vec, size_t pair_bytes) 
 template <typename R>
 static int32_t apply_noalloc(cbs_system* s, double E, int32_t n_vec, const double* z, const void* x, void* y,
                              unsigned char* base, hipStream_t st) {
-  const int32_t nr = (n_vec + 1) / 2;
-  size_t off = 0;
-  RunCoef* coef = reinterpret_cast<RunCoef*>(base + off);
-  off += align256((size_t)nr * sizeof(RunCoef));
-  Pair<R>* px = reinterpret_cast<Pair<R>*>(base + off);
-  off += align256((size_t)nr * s->N * sizeof(Pair<R>));
-  Pair<R>* pq = reinterpret_cast<Pair<R>*>(base + off);
-  off += align256((size_t)nr * s->N * sizeof(Pair<R>));
-  Pair<R>* kt = (s->proj.n_atoms > 0) ? reinterpret_cast<Pair<R>*>(base + off) : nullptr;
-  // P(z) coefficients per half (primal = even vector, dual slot = odd vector); a missing
-  // odd vector gets c0 = 0 and z = 1, and its output half is not copied back
-  for (int k0 = 0; k0 < nr; k0 += kCoefChunk) {
-    CoefChunk ch;
-    const int n = std::min(kCoefChunk, nr - k0);
-    for (int k = 0; k < n; ++k) {
-      RunCoef& c = ch.c[k];
-      for (int h = 0; h < 2; ++h) {
-        const int v = 2 * (k0 + k) + h;
-        double zr = 1, zi = 0;
-        if (v < n_vec) {
-          zr = z[2 * v];
-          zi = z[2 * v + 1];
-        }
-        const double d = zr * zr + zi * zi;
-        c.c[3 * h + 0] = make_double2(v < n_vec ? 1.0 : 0.0, 0.0);
-        c.c[3 * h + 1] = make_double2(zr, zi);
-        c.c[3 * h + 2] = make_double2(zr / d, -zi / d);
-      }
-      c.E = E;
-      c.pad = 0;
-    }
-    hipLaunchKernelGGL(k_put_coef, dim3(1), dim3(kCoefChunk), 0, st, ch, (int32_t)n, coef + k0);
-    CBS_HIP(hipGetLastError());
+  std::vector<double2> c0, cp, cm;
+  apply_coefs(n_vec, z, c0, cp, cm);
+  const size_t kt_bytes = align256(apply_kt_bytes(s, n_vec, sizeof(R)));
+  const size_t bytes = (size_t)n_vec * s->N * sizeof(cplx<R>);
+  if ((const char*)x < (const char*)y + bytes && (const char*)y < (const char*)x + bytes) {
+    CBS_HIP(hipMemcpyAsync(base + kt_bytes, x, bytes, hipMemcpyDeviceToDevice, st));
+    x = base + kt_bytes;
   }
-  CBS_TRY(launch_to_pairs<R>(s->N, n_vec, x, px, st));
-  StencilLaunch l{};
-  l.nruns = nr;
-  l.rin = px;
-  l.q = pq;
-  l.coef = coef;
-  const int32_t ty = s->tile_y[std::is_same<R, double>::value ? 0 : 1];
-  CBS_TRY(launch_stencil<R>(s, false, l, ty ? ty : default_tile_y(s, sizeof(Pair<R>)), st));
-  if (s->proj.n_atoms > 0) {
-    CBS_TRY(launch_bra<R>(s, nr, px, coef, nullptr, 0, kt, nullptr, st, true));
-    CBS_TRY(launch_ket_add<R>(s, nr, pq, kt, st));
-  }
-  CBS_TRY(launch_from_pairs<R>(s->N, n_vec, pq, y, st));
-  return CBS_OK;
+  return launch_apply<R>(s, E, n_vec, c0.data(), cp.data(), cm.data(), x, y, base, nullptr, 0.0, st);
 }
 
 }  // namespace cbs

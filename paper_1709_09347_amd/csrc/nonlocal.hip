@@ -1021,56 +1021,6 @@ int32_t launch_ket_add(const cbs_system* s, int32_t nruns, void* q, const void* 
   return CBS_OK;
 }
 
-// ------------------------------------------------------------------ layout conversions
-template <typename R>
-__global__ void k_to_pairs(int64_t N, int32_t nvec, const cplx<R>* x, Pair<R>* p) {
-  const int64_t npair = (nvec + 1) / 2;
-  const int64_t total = npair * N;
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total;
-       g += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = g / N, n = g - k * N;
-    Pair<R> v;
-    v.a = x[(2 * k) * N + n];
-    v.b = (2 * k + 1 < nvec) ? x[(2 * k + 1) * N + n] : mkc<R>(0, 0);
-    p[g] = v;
-  }
-}
-
-template <typename R>
-__global__ void k_from_pairs(int64_t N, int32_t nvec, const Pair<R>* p, cplx<R>* y) {
-  const int64_t npair = (nvec + 1) / 2;
-  const int64_t total = npair * N;
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total;
-       g += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = g / N, n = g - k * N;
-    const Pair<R> v = p[g];
-    y[(2 * k) * N + n] = v.a;
-    if (2 * k + 1 < nvec) y[(2 * k + 1) * N + n] = v.b;
-  }
-}
-
-template <typename R>
-int32_t launch_to_pairs(int64_t N, int32_t nvec, const void* x, void* pairs, hipStream_t st) {
-  const int64_t total = (int64_t)((nvec + 1) / 2) * N;
-  if (total == 0) return CBS_OK;
-  const int grid = (int)std::min<int64_t>((total + 255) / 256, 1 << 20);
-  hipLaunchKernelGGL(k_to_pairs<R>, dim3(grid), dim3(256), 0, st, N, nvec, (const cplx<R>*)x,
-                     (Pair<R>*)pairs);
-  CBS_HIP(hipGetLastError());
-  return CBS_OK;
-}
-
-template <typename R>
-int32_t launch_from_pairs(int64_t N, int32_t nvec, const void* pairs, void* y, hipStream_t st) {
-  const int64_t total = (int64_t)((nvec + 1) / 2) * N;
-  if (total == 0) return CBS_OK;
-  const int grid = (int)std::min<int64_t>((total + 255) / 256, 1 << 20);
-  hipLaunchKernelGGL(k_from_pairs<R>, dim3(grid), dim3(256), 0, st, N, nvec, (const Pair<R>*)pairs,
-                     (cplx<R>*)y);
-  CBS_HIP(hipGetLastError());
-  return CBS_OK;
-}
-
 #define INST(R)                                                                                   \
   template int32_t launch_bra<R>(const cbs_system*, int32_t, const void*, const RunCoef*,         \
                                  const int32_t*, int32_t, void*, double2*, hipStream_t, bool,     \
@@ -1078,9 +1028,7 @@ int32_t launch_from_pairs(int64_t N, int32_t nvec, const void* pairs, void* y, h
   template int32_t launch_update<R>(const cbs_system*, int32_t, void*, const void*, const void*,  \
                                     const double2*, const int32_t*, int32_t, double*, int32_t,    \
                                     hipStream_t, const int32_t*, const int32_t*);                 \
-  template int32_t launch_ket_add<R>(const cbs_system*, int32_t, void*, const void*, hipStream_t); \
-  template int32_t launch_to_pairs<R>(int64_t, int32_t, const void*, void*, hipStream_t);         \
-  template int32_t launch_from_pairs<R>(int64_t, int32_t, const void*, void*, hipStream_t);
+  template int32_t launch_ket_add<R>(const cbs_system*, int32_t, void*, const void*, hipStream_t);
 INST(double)
 INST(float)
 #undef INST

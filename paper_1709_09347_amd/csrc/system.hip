@@ -270,94 +270,41 @@ static void free_system(cbs_system* s) {
   s->ws.release();
 }
 
+// x itself, or a copy of it in the workspace when the output overlaps it (the kernels read x while
+// they write y).
+static int32_t apply_source(cbs_system* s, const void* x, const void* y, size_t bytes, hipStream_t st,
+                            const void** out) {
+  const char *a = (const char*)x, *b = (const char*)y;
+  *out = x;
+  if (a + bytes <= b || b + bytes <= a) return CBS_OK;
+  unsigned char* t = nullptr;
+  CBS_TRY(ws_get(s->ws, "ap.x", bytes, &t));
+  CBS_HIP(hipMemcpyAsync(t, x, bytes, hipMemcpyDeviceToDevice, st));
+  *out = t;
+  return CBS_OK;
+}
+
+// Asynchronous: the coefficients are kernel arguments.
 int32_t apply_parts_dev(cbs_system* s, double E, int32_t n_vec, const double2* c0,
                         const double2* cp, const double2* cm, const double2* x, double2* y,
-                        hipStream_t st) {
+                        hipStream_t st, const double2* prev, double beta) {
   if (n_vec <= 0) return CBS_OK;
-  const int32_t nr = (n_vec + 1) / 2;
-  Pair<double>* px = nullptr;
-  Pair<double>* pq = nullptr;
-  Pair<double>* kt = nullptr;
-  RunCoef* coef = nullptr;
-  CBS_TRY(ws_get(s->ws, "ap.x", (size_t)nr * s->N, &px));
-  CBS_TRY(ws_get(s->ws, "ap.q", (size_t)nr * s->N, &pq));
-  CBS_TRY(ws_get(s->ws, "ap.coef", (size_t)nr, &coef));
-  if (s->proj.n_atoms > 0) CBS_TRY(ws_get(s->ws, "ap.kt", (size_t)nr * s->proj.n_atoms * 12, &kt));
-  std::vector<RunCoef> hc(nr);
-  for (int k = 0; k < nr; ++k) {
-    for (int h = 0; h < 2; ++h) {
-      const int v = 2 * k + h;
-      const bool ok = v < n_vec;
-      hc[k].c[3 * h + 0] = ok ? c0[v] : make_double2(0, 0);
-      hc[k].c[3 * h + 1] = ok ? cp[v] : make_double2(0, 0);
-      hc[k].c[3 * h + 2] = ok ? cm[v] : make_double2(0, 0);
-    }
-    hc[k].E = E;
-  }
-  CBS_HIP(hipMemcpyAsync(coef, hc.data(), nr * sizeof(RunCoef), hipMemcpyHostToDevice, st));
-  CBS_TRY(launch_to_pairs<double>(s->N, n_vec, x, px, st));
-  StencilLaunch l{};
-  l.nruns = nr;
-  l.rin = px;
-  l.q = pq;
-  l.coef = coef;
-  const int32_t ty = s->tile_y[0] ? s->tile_y[0] : default_tile_y(s, sizeof(Pair<double>));
-  CBS_TRY(launch_stencil<double>(s, false, l, ty, st));
-  if (s->proj.n_atoms > 0) {
-    CBS_TRY(launch_bra<double>(s, nr, px, coef, nullptr, 0, kt, nullptr, st, false));
-    CBS_TRY(launch_ket_add<double>(s, nr, pq, kt, st));
-  }
-  CBS_TRY(launch_from_pairs<double>(s->N, n_vec, pq, y, st));
-  // the host coefficient array must outlive the asynchronous copy
-  CBS_HIP(hipStreamSynchronize(st));
-  return CBS_OK;
+  double* kt = nullptr;
+  if (s->proj.n_atoms > 0)
+    CBS_TRY(ws_get(s->ws, "ap.kt", apply_kt_bytes(s, n_vec, sizeof(double)) / sizeof(double), &kt));
+  return launch_apply<double>(s, E, n_vec, c0, cp, cm, x, y, kt, prev, beta, st);
 }
 
 template <typename R>
 static int32_t apply_z(cbs_system* s, double E, int32_t n_vec, const double* z, const void* x,
                        void* y, hipStream_t st) {
-  const int32_t nr = (n_vec + 1) / 2;
-  Pair<R>* px = nullptr;
-  Pair<R>* pq = nullptr;
-  Pair<R>* kt = nullptr;
-  RunCoef* coef = nullptr;
-  const char* nx = std::is_same<R, double>::value ? "ap.x" : "ap32.x";
-  const char* nq = std::is_same<R, double>::value ? "ap.q" : "ap32.q";
+  std::vector<double2> c0, cp, cm;
+  apply_coefs(n_vec, z, c0, cp, cm);
+  R* kt = nullptr;
   const char* nk = std::is_same<R, double>::value ? "ap.kt" : "ap32.kt";
-  CBS_TRY(ws_get(s->ws, nx, (size_t)nr * s->N, &px));
-  CBS_TRY(ws_get(s->ws, nq, (size_t)nr * s->N, &pq));
-  CBS_TRY(ws_get(s->ws, "ap.coef", (size_t)nr, &coef));
-  if (s->proj.n_atoms > 0) CBS_TRY(ws_get(s->ws, nk, (size_t)nr * s->proj.n_atoms * 12, &kt));
-  std::vector<RunCoef> hc(nr);
-  for (int k = 0; k < nr; ++k) {
-    for (int h = 0; h < 2; ++h) {
-      const int v = 2 * k + h;
-      double zr = 1, zi = 0;
-      if (v < n_vec) {
-        zr = z[2 * v];
-        zi = z[2 * v + 1];
-      }
-      const double d = zr * zr + zi * zi;
-      hc[k].c[3 * h + 0] = make_double2(v < n_vec ? 1.0 : 0.0, 0.0);
-      hc[k].c[3 * h + 1] = make_double2(zr, zi);
-      hc[k].c[3 * h + 2] = make_double2(zr / d, -zi / d);
-    }
-    hc[k].E = E;
-  }
-  CBS_HIP(hipMemcpyAsync(coef, hc.data(), nr * sizeof(RunCoef), hipMemcpyHostToDevice, st));
-  CBS_TRY(launch_to_pairs<R>(s->N, n_vec, x, px, st));
-  StencilLaunch l{};
-  l.nruns = nr;
-  l.rin = px;
-  l.q = pq;
-  l.coef = coef;
-  const int32_t ty = s->tile_y[std::is_same<R, double>::value ? 0 : 1];
-  CBS_TRY(launch_stencil<R>(s, false, l, ty ? ty : default_tile_y(s, sizeof(Pair<R>)), st));
-  if (s->proj.n_atoms > 0) {
-    CBS_TRY(launch_bra<R>(s, nr, px, coef, nullptr, 0, kt, nullptr, st, true));
-    CBS_TRY(launch_ket_add<R>(s, nr, pq, kt, st));
-  }
-  CBS_TRY(launch_from_pairs<R>(s->N, n_vec, pq, y, st));
+  if (s->proj.n_atoms > 0) CBS_TRY(ws_get(s->ws, nk, apply_kt_bytes(s, n_vec, sizeof(R)) / sizeof(R), &kt));
+  CBS_TRY(apply_source(s, x, y, (size_t)n_vec * s->N * sizeof(cplx<R>), st, &x));
+  CBS_TRY(launch_apply<R>(s, E, n_vec, c0.data(), cp.data(), cm.data(), x, y, kt, nullptr, 0.0, st));
   CBS_HIP(hipStreamSynchronize(st));
   return CBS_OK;
 }
@@ -541,8 +488,12 @@ int32_t cbs_apply_parts(cbs_system* s, double E, int32_t n_vec, const double* c0
   }
   if (n_vec == 0) return CBS_OK;
   CBS_HIP(hipSetDevice(s->device));
-  return apply_parts_dev(s, E, n_vec, (const double2*)c0, (const double2*)cp, (const double2*)cm,
-                         (const double2*)x, (double2*)y, (hipStream_t)stream);
+  hipStream_t st = (hipStream_t)stream;
+  CBS_TRY(apply_source(s, x, y, (size_t)n_vec * s->N * sizeof(double2), st, &x));
+  CBS_TRY(apply_parts_dev(s, E, n_vec, (const double2*)c0, (const double2*)cp, (const double2*)cm,
+                          (const double2*)x, (double2*)y, st));
+  CBS_HIP(hipStreamSynchronize(st));
+  return CBS_OK;
 }
 
 }  // extern "C"
