@@ -25,18 +25,12 @@ namespace cbs {
 
 using c64 = double2;
 
-// out = alpha (HY - c Y) + beta X (vectors [m][N])
-__global__ void k_cheb(int64_t total, const c64* HY, const c64* Y, const c64* X, c64* out, double c, double alpha,
-                       double beta) {
+// out = alpha (HY - c Y), the first step of the filter (vectors [m][N]); the later ones run inside
+// the operator
+__global__ void k_cheb(int64_t total, const c64* HY, const c64* Y, c64* out, double c, double alpha) {
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
     const c64 hy = HY[g], y = Y[g];
-    c64 o = make_double2(alpha * (hy.x - c * y.x), alpha * (hy.y - c * y.y));
-    if (X != nullptr) {
-      const c64 x = X[g];
-      o.x += beta * x.x;
-      o.y += beta * x.y;
-    }
-    out[g] = o;
+    out[g] = make_double2(alpha * (hy.x - c * y.x), alpha * (hy.y - c * y.y));
   }
 }
 
@@ -233,7 +227,7 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
     const c64 phc = make_double2(ph.x, -ph.y);
     double upper = 0;
     CBS_TRY(spectrum_upper(s, ph, st, &upper));
-    std::vector<c64> c0(m, make_double2(1, 0)), cp(m, ph), cm(m, phc);
+    std::vector<c64> c0(m, make_double2(1, 0)), cp(m, ph), cm(m, phc), f0(m), fp(m), fm(m);
     auto applyH = [&](const c64* in, c64* out) { return apply_parts_dev(s, 0.0, m, c0.data(), cp.data(), cm.data(), in, out, st); };
     // orthonormalise the columns of Y into X (Cholesky QR: a shifted pass, then two plain ones)
     auto orthonormalise = [&](c64* src, c64* dst) -> int32_t {
@@ -310,7 +304,7 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
       const double sigma1 = sigma, gamma = 2.0 / sigma1;
       // Y = (H X - c X) sigma1 / e ; H X is HY after the last Rayleigh-Ritz step
       hipLaunchKernelGGL(k_cheb, dim3(grid_of((int64_t)blk)), dim3(256), 0, st, (int64_t)blk, (const c64*)HY,
-                         (const c64*)X, (const c64*)nullptr, Y, c, sigma1 / e, 0.0);
+                         (const c64*)X, Y, c, sigma1 / e);
       CBS_HIP(hipGetLastError());
       // three-term recurrence over the buffers (prev, cur, next), rotated each step; the
       // starting block X is only read by the first step, so all three take turns
@@ -319,11 +313,13 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
       c64* nxt = Z;
       for (int d = 2; d <= degree; ++d) {
         const double sigma2 = 1.0 / (gamma - sigma);
-        CBS_TRY(applyH(cur, HY));
-        // next = 2 (H cur - c cur) sigma2 / e - sigma sigma2 prev
-        hipLaunchKernelGGL(k_cheb, dim3(grid_of((int64_t)blk)), dim3(256), 0, st, (int64_t)blk, (const c64*)HY,
-                           (const c64*)cur, (const c64*)prev, nxt, c, 2.0 * sigma2 / e, -sigma * sigma2);
-        CBS_HIP(hipGetLastError());
+        // next = 2 (H cur - c cur) sigma2 / e - sigma sigma2 prev, in the operator's own pass: c is
+        // its energy, 2 sigma2 / e scales its coefficients
+        const double al = 2.0 * sigma2 / e;
+        std::fill(f0.begin(), f0.end(), make_double2(al, 0));
+        std::fill(fp.begin(), fp.end(), make_double2(al * ph.x, al * ph.y));
+        std::fill(fm.begin(), fm.end(), make_double2(al * phc.x, al * phc.y));
+        CBS_TRY(apply_parts_dev(s, c, m, f0.data(), fp.data(), fm.data(), cur, nxt, st, prev, -sigma * sigma2));
         c64* freed = prev;
         prev = cur;
         cur = nxt;
