@@ -206,26 +206,6 @@ __global__ void __launch_bounds__(1024) k_ap_local(ApLocal<R> a, ApCoef cf) {
 }
 
 // ------------------------------------------------------------------ bra
-// Sums of NV values over the wave: each halving step exchanges the half of the values that the
-// other lane keeps, so NV + 6 - log2(NV) shuffles replace 6 NV.  Lane l ends with the sum of
-// value l * NV / 64.
-template <int NV, typename C>
-__device__ __forceinline__ C wave_sums(C (&v)[NV], int lane) {
-  int off = 32;
-#pragma unroll
-  for (int w = NV / 2; w >= 1; w >>= 1, off >>= 1) {
-    const bool up = (lane & off) != 0;
-#pragma unroll
-    for (int k = 0; k < w; ++k) {
-      const C lo = v[k], hi = v[k + w];
-      v[k] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, 64);
-    }
-  }
-  C t = v[0];
-  for (; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
-  return t;
-}
-
 template <typename R>
 struct ApBra {
   int32_t n_atoms, nv, nvb, nlogical;

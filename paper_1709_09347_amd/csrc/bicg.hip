@@ -879,22 +879,31 @@ int32_t bicg_alloc(BicgSolve& b, const char* tag) {
   Workspace& ws = s->ws;
   const std::string t = tag;
   const size_t R = b.nruns;
-  CBS_TRY(autotune_tiles(s, nullptr));
-  if (b.mixed) CBS_TRY(alloc_vecs<float>(s, b.lo, R, t + ".lo."));
-  CBS_TRY(alloc_vecs<double>(s, b.hi, R, t + ".hi."));
-  CBS_TRY(ws_get(ws, (t + ".Y").c_str(), R * s->N, &b.Y));
-  b.nchunks = update_chunks(s);
-  const int na = s->proj.n_atoms;
-  CBS_TRY(ws_get(ws, (t + ".signl").c_str(), R * std::max(na, 1), &b.signl));
-  CBS_TRY(ws_get(ws, (t + ".upd").c_str(), R * b.nchunks * 4, &b.upd_part));
-  b.bra_part = nullptr;
-  if (s->bra_tile[0] > 0 || s->bra_tile[1] > 0) {
-    unsigned char* bp = nullptr;
-    CBS_TRY(ws_get(ws, (t + ".brapart").c_str(), bra_tile_part_bytes(s, (int32_t)R), &bp));
-    b.bra_part = bp;
+  if (b.run_wg) {
+    // a workgroup per run needs no tuning and no partial sums; r, p and x wait here between launches
+    CBS_TRY(ws_get(ws, (t + ".hi.R").c_str(), R * s->N, &b.hi.R));
+    CBS_TRY(ws_get(ws, (t + ".hi.P0").c_str(), R * s->N, &b.hi.Pb[0]));
+    CBS_TRY(ws_get(ws, (t + ".hi.X").c_str(), R * s->N, &b.hi.X));
+    CBS_TRY(ws_get(ws, (t + ".Y").c_str(), R * s->N, &b.Y));
+    b.bra_part = nullptr;
+  } else {
+    CBS_TRY(autotune_tiles(s, nullptr));
+    if (b.mixed) CBS_TRY(alloc_vecs<float>(s, b.lo, R, t + ".lo."));
+    CBS_TRY(alloc_vecs<double>(s, b.hi, R, t + ".hi."));
+    CBS_TRY(ws_get(ws, (t + ".Y").c_str(), R * s->N, &b.Y));
+    b.nchunks = update_chunks(s);
+    const int na = s->proj.n_atoms;
+    CBS_TRY(ws_get(ws, (t + ".signl").c_str(), R * std::max(na, 1), &b.signl));
+    CBS_TRY(ws_get(ws, (t + ".upd").c_str(), R * b.nchunks * 4, &b.upd_part));
+    b.bra_part = nullptr;
+    if (s->bra_tile[0] > 0 || s->bra_tile[1] > 0) {
+      unsigned char* bp = nullptr;
+      CBS_TRY(ws_get(ws, (t + ".brapart").c_str(), bra_tile_part_bytes(s, (int32_t)R), &bp));
+      b.bra_part = bp;
+    }
+    b.ru_chunks = (int32_t)(((s->N + KG - 1) / KG + 3) / 4);   // one group per wave
+    CBS_TRY(ws_get(ws, (t + ".ru").c_str(), R * b.ru_chunks * 4, &b.ru_part));
   }
-  b.ru_chunks = (int32_t)(((s->N + KG - 1) / KG + 3) / 4);   // one group per wave
-  CBS_TRY(ws_get(ws, (t + ".ru").c_str(), R * b.ru_chunks * 4, &b.ru_part));
   CBS_TRY(ws_get(ws, (t + ".alpha").c_str(), R, &b.sc.alpha));
   CBS_TRY(ws_get(ws, (t + ".xcoef").c_str(), R, &b.sc.xcoef));
   CBS_TRY(ws_get(ws, (t + ".beta").c_str(), R, &b.sc.beta));
@@ -1125,11 +1134,49 @@ static int32_t run_profiled(std::vector<BicgSolve*>& solves, hipStream_t st, int
   return rc;
 }
 
+// Runs of small cells, a workgroup each, until none is left; the next launch is queued before the
+// host waits for the count of the last one.
+constexpr int32_t WG_CAP = 1024;   // iterations per launch: 5 to 60 ms (CBS_RUN_WG=<n>: n instead, 0: this path off)
+static int32_t run_workgroups(std::vector<BicgSolve*>& solves, int32_t max_iter, int32_t* hact, hipStream_t st) {
+  const size_t ns2 = 2 * solves.size();
+  hipEvent_t evc[2] = {nullptr, nullptr};
+  struct EvGuard {
+    hipEvent_t* e;
+    ~EvGuard() {
+      for (int i = 0; i < 2; ++i)
+        if (e[i]) (void)hipEventDestroy(e[i]);
+    }
+  } evguard{evc};
+  CBS_HIP(hipEventCreateWithFlags(&evc[0], hipEventDisableTiming));
+  CBS_HIP(hipEventCreateWithFlags(&evc[1], hipEventDisableTiming));
+  const char* e = getenv("CBS_RUN_WG");
+  const int32_t cap = (e && atoi(e) > 0) ? atoi(e) : WG_CAP;
+  const int64_t most = (int64_t)max_iter / cap + 1;   // every run ends within max_iter iterations
+  auto launch = [&](int c) -> int32_t {
+    int32_t* slot = hact + (size_t)(c & 1) * ns2;
+    for (size_t i = 0; i < solves.size(); ++i) {
+      CBS_TRY(launch_run_wg(*solves[i], c == 0, cap, st));
+      CBS_HIP(hipMemcpyAsync(slot + 2 * i, solves[i]->sc.n_active, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    }
+    CBS_HIP(hipEventRecord(evc[c & 1], st));
+    return CBS_OK;
+  };
+  CBS_TRY(launch(0));
+  for (int64_t c = 0; c < most; ++c) {
+    if (c + 1 < most) CBS_TRY(launch((int)(c + 1)));
+    CBS_HIP(hipEventSynchronize(evc[c & 1]));
+    int any = 0;
+    for (size_t i = 0; i < ns2; ++i) any += hact[(size_t)(c & 1) * ns2 + i];
+    if (any == 0) break;
+  }
+  return CBS_OK;
+}
+
 // Runs all solves to completion on an internal stream ordered after `user` (and `user`
 // waits for it at the end).  Several solves (systems) advance in the same graph.
-int32_t bicg_run(std::vector<BicgSolve*>& solves, hipStream_t user, int32_t chunk, int32_t max_iter,
+int32_t bicg_run(std::vector<BicgSolve*>& all, hipStream_t user, int32_t chunk, int32_t max_iter,
                  double* elapsed_ms, bool profile) {
-  if (solves.empty()) return CBS_OK;
+  if (all.empty()) return CBS_OK;
   if (chunk < 2) chunk = 2;
   if (chunk % 2) chunk += 1;
   hipStream_t st = nullptr;
@@ -1158,9 +1205,21 @@ int32_t bicg_run(std::vector<BicgSolve*>& solves, hipStream_t user, int32_t chun
   CBS_HIP(hipEventCreate(&ev1));
   CBS_HIP(hipEventRecord(ev0, user));
   CBS_HIP(hipStreamWaitEvent(st, ev0, 0));
-  for (auto* b : solves) CBS_TRY(enqueue_init(*b, st));
   // two slots of active counts: the count of chunk c is read while chunk c + 1 runs
-  CBS_HIP(hipHostMalloc(&hact, sizeof(int32_t) * 4 * solves.size(), hipHostMallocDefault));
+  CBS_HIP(hipHostMalloc(&hact, sizeof(int32_t) * 4 * all.size(), hipHostMallocDefault));
+  const auto t_wg = std::chrono::steady_clock::now();
+  std::vector<BicgSolve*> small, solves;
+  for (auto* b : all) (b->run_wg ? small : solves).push_back(b);
+  if (!small.empty()) CBS_TRY(run_workgroups(small, max_iter, hact, st));
+  if (solves.empty()) {
+    CBS_HIP(hipStreamSynchronize(st));
+    if (elapsed_ms)
+      *elapsed_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_wg).count();
+    CBS_HIP(hipEventRecord(ev1, st));
+    CBS_HIP(hipStreamWaitEvent(user, ev1, 0));
+    return CBS_OK;
+  }
+  for (auto* b : solves) CBS_TRY(enqueue_init(*b, st));
   const bool graphs = use_graphs() && !profile;
   // CBS_VERBOSE=2: a progress line every 500 iterations (long solves); 3: one line per chunk
   // with the complex128 / complex64 active-run counts and the chunk's wall time
@@ -1179,7 +1238,7 @@ int32_t bicg_run(std::vector<BicgSolve*>& solves, hipStream_t user, int32_t chun
     CBS_HIP(e);
     CBS_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
   }
-  auto t0 = std::chrono::steady_clock::now();
+  auto t0 = small.empty() ? std::chrono::steady_clock::now() : t_wg;
   int32_t rc = CBS_OK;
   if (profile) {
     rc = run_profiled(solves, st, max_iter);
@@ -1336,6 +1395,12 @@ int32_t split_pairs(int64_t N, int32_t nruns, const Pair<double>* Y, double2* ya
   return CBS_OK;
 }
 
+// Solves that a workgroup per run can carry: complex128 throughout, no rule across runs, and no
+// timing of the launches it does without.
+bool run_wg_params(const cbs_params* prm) {
+  return prm->precision == CBS_FP64 && !prm->half_stop && !prm->profile;
+}
+
 void configure_solve(BicgSolve& b, const cbs_params* prm) {
   b.mixed = prm->precision == CBS_MIXED;
   b.tol = prm->tol;
@@ -1376,6 +1441,7 @@ int32_t solve_nodes(cbs_system* s, double E, const double2* z, int32_t n_z, int3
   b.V = V;
   b.coef = coef;
   configure_solve(b, prm);
+  b.run_wg = run_wg_fits(s) && run_wg_params(prm);
   CBS_TRY(bicg_alloc(b, "bicg"));
   const size_t hn = hist ? (size_t)hist->rows * nruns * 2 : 0;
   if (hn > 0) {

@@ -109,6 +109,7 @@ struct BicgSolve {
   double* hist = nullptr;    // [hist_rows][nruns][2] recursive relative residuals, NULL: not recorded
   int32_t hist_stride = 0, hist_rows = 0;   // row i holds iteration (i + 1) * hist_stride
   QueueState* q = nullptr;   // batched work queue, NULL: every run is its own item
+  bool run_wg = false;       // small cell: one workgroup per run (runwg.hip); set before bicg_alloc
 };
 
 // Optional residual-history request of solve_nodes (device buffer owned by the workspace).
@@ -130,11 +131,15 @@ struct NodeSolve {
 };
 
 int32_t bicg_alloc(BicgSolve& b, const char* tag);
+// Whether the runs of a cell can each be carried by one workgroup, and one launch of that kernel
+// (the first one initialises the runs; `cap` iterations at most, then n_active counts the rest).
+bool run_wg_fits(const cbs_system* s);
+int32_t launch_run_wg(BicgSolve& b, bool start, int32_t cap, hipStream_t st);
 // Work queue: allocation (item tables, moments) and the initial fill of the slots.
 int32_t queue_alloc(BicgSolve& b, QueueState& q, const std::vector<RunCoef>& item_coef,
                     const std::vector<double2>& ca, const std::vector<double2>& cb, const char* tag,
                     hipStream_t st);
-int32_t bicg_run(std::vector<BicgSolve*>& solves, hipStream_t user, int32_t chunk, int32_t max_iter,
+int32_t bicg_run(std::vector<BicgSolve*>& all, hipStream_t user, int32_t chunk, int32_t max_iter,
                  double* elapsed_ms, bool profile);
 int32_t bicg_collect(BicgSolve& b, NodeSolve& out, hipStream_t st);
 void node_coefs(const double2* z, int32_t n_z, int32_t L, double E, std::vector<RunCoef>& out);
@@ -146,5 +151,6 @@ int32_t solve_nodes_block(cbs_system* s, double E, const double2* z, int32_t n_z
 int32_t split_pairs(int64_t N, int32_t nruns, const Pair<double>* Y, double2* ya, double2* yb, hipStream_t st);
 int32_t check_params(const cbs_params* p, bool need_moments);
 void configure_solve(BicgSolve& b, const cbs_params* prm);
+bool run_wg_params(const cbs_params* prm);
 
 }  // namespace cbs

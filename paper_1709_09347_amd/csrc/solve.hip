@@ -934,8 +934,12 @@ extern "C" int32_t cbs_solve_batched(int32_t n_sys, cbs_system* const* systems, 
   }
   // the work queue (default); the energy waves below for the half-of-the-nodes stop (whose
   // groups are whole energies), profiling, or CBS_QUEUE=0
+  // (a queue slot is a run of the launch-per-step iteration), or when every cell is so small that
+  // a workgroup carries a run: it takes the next one by itself
   const char* qenv = getenv("CBS_QUEUE");
-  if (!prm->half_stop && !prm->profile && !(qenv && qenv[0] == '0'))
+  bool wg = run_wg_params(prm) && getenv("CBS_QUEUE_SLOTS") == nullptr;
+  for (int s = 0; s < n_sys; ++s) wg = wg && run_wg_fits(systems[s]);
+  if (!prm->half_stop && !prm->profile && !wg && !(qenv && qenv[0] == '0'))
     return solve_batched_queue(n_sys, systems, n_E, E, prm, V, max_eigs, lambda, n_eigs, info, st, nq, per_pt,
                                budget);
   const int wave = std::max(1, std::min(n_E, (int)(budget / per_energy)));
@@ -970,6 +974,7 @@ extern "C" int32_t cbs_solve_batched(int32_t n_sys, cbs_system* const* systems, 
       b.V = (const c64*)V[s];
       b.coef = coef;
       configure_solve(b, prm);
+      b.run_wg = wg;
       CBS_TRY(bicg_alloc(b, "bicg"));
       ptrs.push_back(&b);
     }
