@@ -484,6 +484,406 @@ __global__ void __launch_bounds__(JWG) k_svd_finish(int32_t n, c64* A, int32_t l
   }
 }
 
+// ------------------------------------------------------------------ right singular vectors
+// Where only sigma and the right singular vectors are wanted (the Rayleigh-Ritz extraction, the
+// bands), one-sided Jacobi starts from the pivoted QR A P = Q R and works on the columns of R^H:
+// R^H V = U Sigma gives A = (Q V) Sigma (P U)^H, so the right vectors are the rotated columns
+// themselves, normalised, in the rows that P names, and no second matrix is rotated.  The columns of
+// R^H are already close to orthogonal (Drmac and Veselic, SIAM J. Matrix Anal. Appl. 29, 2008):
+// 9-10 sweeps instead of 20-24 on Hankel matrices of a few eigenvalues above noise.
+//
+// A column pair belongs to a group of 8 to 64 lanes; its three inner products are summed by DPP with
+// the four values split over the lanes of each quad.  Order 64 stays in one workgroup's LDS for all
+// sweeps, larger orders take their blocks in turn as k_svd_block does.  Latency bound (one workgroup,
+// 63 rounds a sweep).  Hankel SVD of order 64: QR 0.17 + sweeps 0.64 ms, where rotating A and W from the
+// start took 4.8 ms (21 sweeps of 0.23); order 16 of the bands 0.03 ms (was 0.11).
+
+template <int CTRL>
+__device__ __forceinline__ double dppd(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double lane_of(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// the sum and the maximum over the wave, in every lane: 16 lanes by DPP, the four rows by readlane
+__device__ __forceinline__ double wave_sum_dpp(double t) {
+  t += dppd<0xB1>(t);    // lane ^ 1
+  t += dppd<0x4E>(t);    // lane ^ 2
+  t += dppd<0x141>(t);   // mirrored in 8 lanes
+  t += dppd<0x140>(t);   // mirrored in 16 lanes
+  return (lane_of(t, 0) + lane_of(t, 16)) + (lane_of(t, 32) + lane_of(t, 48));
+}
+__device__ __forceinline__ double wave_max_dpp(double t) {
+  t = fmax(t, dppd<0xB1>(t));
+  t = fmax(t, dppd<0x4E>(t));
+  t = fmax(t, dppd<0x141>(t));
+  t = fmax(t, dppd<0x140>(t));
+  return fmax(fmax(lane_of(t, 0), lane_of(t, 16)), fmax(lane_of(t, 32), lane_of(t, 48)));
+}
+
+// 1 / sqrt(x) for normal x > 0: the hardware's approximation and one step of third order (two
+// units in the last place), a fifth of the latency of a square root and a division.
+__device__ __forceinline__ double rsqrt1(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+constexpr int SV_T = 1024;
+constexpr size_t SV_LDS = 150 * 1024;   // columns of a block pair (or the whole matrix in the QR)
+
+// Pivoted Householder QR of A (n x n): X = R^H (lower triangular), piv[k]: the column of A taken
+// k-th.  One workgroup; a lane owns CPL columns, a wave 16 rows of them, all in registers, so that the
+// inner products with the reflector are sums over a lane's own rows and then over the waves; the
+// reflector's rows are read from the pivot's lane.  A wave instruction takes four cycles whatever it
+// is for, so the parts that every wave repeats (pivot, reflector) want few waves: with a column per
+// wave and 16 waves in LDS a step of order 64 took 4.8 us.
+template <int CPL>
+__global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, int32_t lda, c64* X, int32_t* piv) {
+  constexpr int NW = 4 * CPL, RW = 16;
+  __shared__ double pn[NW][64 * CPL];   // per wave: squared norms of the columns' remaining rows
+  __shared__ c64 pd[NW][64 * CPL];      // per wave: products with the reflector
+  __shared__ c64 rowk[64 * CPL];        // row k
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i0 = wv * RW;
+  c64 m[CPL][RW];
+  int pos[CPL];   // step at which the column was taken, n: not yet
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {
+    const int j = lane + 64 * c;
+    double t = 0;
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      m[c][r] = (j < n && i0 + r < n) ? A[i0 + r + (int64_t)j * lda] : make_double2(0, 0);
+      t += cabs2<double>(m[c][r]);
+    }
+    pn[wv][j] = t;
+    if (wv == 0) rowk[j] = m[c][0];
+    pos[c] = j < n ? n : -1;
+  }
+  __syncthreads();
+  for (int k = 0; k < n; ++k) {
+    // the remaining column of the largest norm (a NaN counts as the largest)
+    double nrm[CPL], best = -1;
+    int bc = 0;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      nrm[c] = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) nrm[c] += pn[w][lane + 64 * c];
+      const double v = pos[c] != n ? -1.0 : nrm[c] == nrm[c] ? nrm[c] : __builtin_inf();
+      if (v > best) {
+        best = v;
+        bc = c;
+      }
+    }
+    const int pl = __ffsll((unsigned long long)__ballot(best == wave_max_dpp(best))) - 1;
+    const int pc = CPL == 1 ? 0 : __builtin_amdgcn_readlane(bc, pl), p = pl + 64 * pc;
+    // reflector I - b v v^H, v = x - alpha e_k of the pivot's rows k..n-1: |v|^2 = 2 (|x|^2 + |x| |x_k|)
+    const double nx2 = lane_of(CPL == 1 ? nrm[0] : (pc ? nrm[CPL - 1] : nrm[0]), pl);
+    const c64 xk = rowk[p];
+    const double nx = sqrt(nx2), ak = sqrt(cabs2<double>(xk));
+    const c64 ph = ak > 0 ? make_double2(xk.x / ak, xk.y / ak) : make_double2(1, 0);
+    const c64 alpha = zscale(ph, -nx);
+    const double vv = nx2 + nx * ak, b = vv > 0 ? 1.0 / vv : 0.0;
+    c64 v[RW], d[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) d[c] = make_double2(0, 0);
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      v[r] = make_double2(0, 0);
+      if (i0 + r < k) continue;   // wave-uniform
+      const c64 src = CPL == 1 || pc == 0 ? m[0][r] : m[CPL - 1][r];
+      v[r] = make_double2(lane_of(src.x, pl), lane_of(src.y, pl));
+      if (i0 + r == k) v[r] = zsub(v[r], alpha);
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) d[c] = zadd(d[c], zmulc(v[r], m[c][r]));
+    }
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) pd[wv][lane + 64 * c] = d[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      const int j = lane + 64 * c;
+      d[c] = make_double2(0, 0);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) d[c] = zadd(d[c], pd[w][j]);
+      d[c] = zscale(d[c], b);
+      const bool on = pos[c] == n && j != p;
+      double t = 0;
+#pragma unroll
+      for (int r = 0; r < RW; ++r) {
+        if (i0 + r < k) continue;
+        const c64 u = zsub(m[c][r], zmul(v[r], d[c]));
+        if (on) m[c][r] = u;
+        if (i0 + r == k && j == p) m[c][r] = alpha;
+        if (i0 + r > k) t += cabs2<double>(u);
+        if (i0 + r == k + 1) rowk[j] = m[c][r];
+      }
+      pn[wv][j] = t;
+      if (j == p) {
+        pos[c] = k;
+        if (wv == 0) piv[k] = p;
+      }
+    }
+    __syncthreads();
+  }
+  // R[i][column] is the conjugate of X[position of the column][i]
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {
+    if (lane + 64 * c >= n) continue;
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+      if (i0 + r < n) X[pos[c] + (int64_t)(i0 + r) * n] = pos[c] >= i0 + r ? zconj(m[c][r]) : make_double2(0, 0);
+  }
+}
+
+// The same for orders beyond 128, whose columns do not fit the registers: M is a copy of A in global
+// memory, a wave owns every NW-th column, four at a time, RP rows a lane.  Every wave finds the pivot
+// and forms the reflector by itself, so a step has one barrier.
+template <int RP>
+__global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, int32_t lda, c64* M, c64* X,
+                                                     int32_t* piv) {
+  __shared__ double cnb[2][64 * RP];   // squared norms of the remaining parts, -1: taken (this step's, the next's)
+  __shared__ int32_t order[64 * RP];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int CB = 4;
+  const int NW = blockDim.x >> 6;
+  for (int j = wv; j < n; j += NW) {
+    double t = 0;
+    for (int i = lane; i < n; i += 64) {
+      const c64 v = A[i + (int64_t)j * lda];
+      M[i + j * n] = v;
+      t += cabs2<double>(v);
+    }
+    t = wave_sum_dpp(t);
+    if (lane == 0) cnb[0][j] = t;
+  }
+  __syncthreads();
+  for (int k = 0; k < n; ++k) {
+    const double* cn = cnb[k & 1];
+    double* cnext = cnb[(k + 1) & 1];
+    // the remaining column of the largest norm (a NaN counts as the largest)
+    double best = -1;
+    int p = n;
+    for (int j = lane; j < n; j += 64) {
+      double v = cn[j];
+      if (v != v) v = __builtin_inf();
+      if (v > best) {
+        best = v;
+        p = j;
+      }
+    }
+    const unsigned long long top = __ballot(best == wave_max_dpp(best));
+    p = __builtin_amdgcn_readlane(p, __ffsll(top) - 1);
+    // reflector I - b v v^H with v = x - alpha e_k of its rows k..n-1
+    c64 v[RP];
+    double nx2 = 0;
+#pragma unroll
+    for (int r = 0; r < RP; ++r) {
+      const int i = lane + 64 * r;
+      v[r] = (i >= k && i < n) ? M[i + p * n] : make_double2(0, 0);
+      nx2 += cabs2<double>(v[r]);
+    }
+    nx2 = wave_sum_dpp(nx2);
+    const c64 xk = M[k + p * n];
+    const double nx = sqrt(nx2), ak = sqrt(cabs2<double>(xk));
+    const c64 ph = ak > 0 ? make_double2(xk.x / ak, xk.y / ak) : make_double2(1, 0);
+    const c64 alpha = zscale(ph, -nx);
+    // |v|^2 = 2 (nx^2 + nx |x_k|)
+    const double vv = 2.0 * (nx2 + nx * ak), b = vv > 0 ? 2.0 / vv : 0.0;
+#pragma unroll
+    for (int r = 0; r < RP; ++r)
+      if (lane + 64 * r == k) v[r] = zsub(v[r], alpha);
+    for (int j0 = wv; j0 < n; j0 += NW * CB) {
+      c64 m[CB][RP];
+      c64 d[CB];
+#pragma unroll
+      for (int c = 0; c < CB; ++c) {
+        const int j = min(j0 + c * NW, n - 1);
+        d[c] = make_double2(0, 0);
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+          const int i = lane + 64 * r;
+          m[c][r] = (i >= k && i < n) ? M[i + j * n] : make_double2(0, 0);
+          d[c] = zadd(d[c], zmulc(v[r], m[c][r]));
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < CB; ++c) d[c] = make_double2(wave_sum_dpp(d[c].x) * b, wave_sum_dpp(d[c].y) * b);
+#pragma unroll
+      for (int c = 0; c < CB; ++c) {
+        const int j = j0 + c * NW;
+        const bool on = j < n && j != p && !(cn[min(j, n - 1)] < 0);   // wave-uniform
+        double t = 0;
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+          const int i = lane + 64 * r;
+          const c64 u = zsub(m[c][r], zmul(v[r], d[c]));
+          if (on && i >= k && i < n) M[i + j * n] = u;
+          t += i > k && i < n ? cabs2<double>(u) : 0.0;
+        }
+        t = wave_sum_dpp(t);
+        if (j < n && lane == 0) cnext[j] = on ? t : -1.0;
+      }
+    }
+    __syncthreads();
+    if (tid == 0) {   // column p is not read again before the end
+      order[k] = p;
+      piv[k] = p;
+      M[k + p * n] = alpha;
+    }
+  }
+  __syncthreads();
+  // X[j][k] = conj(R[k][j]), R[k][j] = M[k][order[j]] for j >= k
+  for (int t = tid; t < n * n; t += blockDim.x) {
+    const int j = t % n, k = t / n;
+    X[j + k * n] = j >= k ? zconj(M[k + order[j] * n]) : make_double2(0, 0);
+  }
+}
+
+// One sweep over the columns of a block pair in LDS (nb = 2: all columns, `sweeps` times or until
+// converged).  flags[s]: the largest (|a_p^H a_q| / |a_p| |a_q|)^2 of sweep s, as bits; a launch of a
+// sweep whose predecessor was converged returns at once, so the host may queue several.
+__device__ double block_max_any(double v, double* sh) {
+  v = wave_max_dpp(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double r = sh[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = fmax(r, sh[w]);
+  __syncthreads();
+  return r;
+}
+// LDS column stride: 128 bytes off a multiple of the 64 banks, so that the groups of a wave read
+// neighbouring columns from different banks.
+__host__ __device__ inline int sv_ldc(int n) { return (n + 7) / 16 * 16 + 8; }
+// RPL: rows of a column per lane, kept in registers from the inner products to the rotation.
+constexpr double SV_TOL2 = 1e-26;
+template <int RPL>
+__global__ void __launch_bounds__(1024) k_svd_cols(int32_t n, int32_t bs, int32_t nb, int32_t round, int32_t sweep,
+                                                   int32_t sweeps, int32_t gsize, c64* X, unsigned long long* flags) {
+  extern __shared__ __align__(16) unsigned char sv_smem[];
+  __shared__ double sh[16];
+  if (sweep > 0 && __longlong_as_double((long long)flags[sweep - 1]) < SV_TOL2) return;
+  c64* la = reinterpret_cast<c64*>(sv_smem);   // [2 bs][ldc]
+  const int ldc = sv_ldc(n);
+  const int bp = rr_slot(blockIdx.x, round, nb), bq = rr_slot(nb - 1 - blockIdx.x, round, nb);
+  const int tid = threadIdx.x, cols = 2 * bs;
+  auto gcol = [&](int c) { return (c < bs) ? bp * bs + c : bq * bs + (c - bs); };
+  for (int t = tid; t < cols * n; t += blockDim.x) {
+    const int c = t / n, i = t - c * n, g = gcol(c);
+    la[i + c * ldc] = (g < n) ? X[i + g * n] : make_double2(0, 0);
+  }
+  __syncthreads();
+  const int pidx = tid / gsize, sub = tid % gsize;
+  double off2 = 0;
+  for (int sw = 0; sw < sweeps; ++sw) {
+    off2 = 0;
+    for (int ir = 0; ir < cols - 1; ++ir) {
+      if (pidx < bs) {
+        int p = rr_slot(pidx, ir, cols), q = rr_slot(cols - 1 - pidx, ir, cols);
+        if (p > q) {
+          const int t = p;
+          p = q;
+          q = t;
+        }
+        c64* ap = la + p * ldc;
+        c64* aq = la + q * ldc;
+        double al = 0, be = 0, gx = 0, gy = 0;
+        c64 xs[RPL], ys[RPL];
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+          const int i = sub + r * gsize;
+          xs[r] = i < n ? ap[i] : make_double2(0, 0);
+          ys[r] = i < n ? aq[i] : make_double2(0, 0);
+          const c64 x = xs[r], y = ys[r];
+          al += cabs2<double>(x);
+          be += cabs2<double>(y);
+          gx += x.x * y.x + x.y * y.y;
+          gy += x.x * y.y - x.y * y.x;
+        }
+        // lane bits (1, 0) of a quad keep (0,0) al, (1,0) be, (0,1) gx, (1,1) gy
+        const bool odd = (sub & 1) != 0, up = (sub & 2) != 0;
+        const double k0 = (odd ? gx : al) + dppd<0xB1>(odd ? al : gx);
+        const double k1 = (odd ? gy : be) + dppd<0xB1>(odd ? be : gy);
+        double t = (up ? k1 : k0) + dppd<0x4E>(up ? k0 : k1);
+        if (gsize == 8) {
+          t += dppd<0x1B>(dppd<0x141>(t));   // lane ^ 4: mirrored in 8 lanes, then in 4
+        } else {
+          t += dppd<0x124>(t);   // rotated by 4 in 16 lanes
+          t += dppd<0x128>(t);   // rotated by 8
+        }
+        if (gsize > 16) t += __shfl_xor(t, 16, 64);
+        if (gsize > 32) t += __shfl_xor(t, 32, 64);
+        al = dppd<0x00>(t);
+        gx = dppd<0x55>(t);
+        be = dppd<0xAA>(t);
+        gy = dppd<0xFF>(t);
+        const double g2 = gx * gx + gy * gy, ab = al * be;
+        if (g2 > 1e-30 * ab && g2 > 0.0) {   // padding columns are zero
+          off2 = fmax(off2, g2 / ab);
+          // rotation by c and s e^{-i phi}: with d = be - al and h = sqrt(d^2 + 4 |g|^2),
+          // c^2 = (|d| + h) / 2h and s c = sign(d) |g| / h
+          const double d = be - al, ih = rsqrt1(d * d + 4.0 * g2);
+          const double c2 = 0.5 + 0.5 * fabs(d) * ih, ic = rsqrt1(c2), c = c2 * ic;
+          const double f = (d >= 0 ? ih : -ih) * ic;
+          const c64 se = make_double2(gx * f, -gy * f);   // s e^{-i phi}
+#pragma unroll
+          for (int r = 0; r < RPL; ++r) {
+            const int i = sub + r * gsize;
+            if (i < n) {
+              ap[i] = zsub(zscale(xs[r], c), zmul(se, ys[r]));
+              aq[i] = zadd(zscale(ys[r], c), zmul(zconj(se), xs[r]));
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (sweeps > 1) {
+      off2 = block_max_any(off2, sh);
+      if (!(off2 >= SV_TOL2)) break;
+    }
+  }
+  for (int t = tid; t < cols * n; t += blockDim.x) {
+    const int c = t / n, i = t - c * n, g = gcol(c);
+    if (g < n) X[i + g * n] = la[i + c * ldc];
+  }
+  off2 = block_max_any(off2, sh);
+  if (tid == 0 && off2 > 0) atomicMax(flags + sweep, (unsigned long long)__double_as_longlong(off2));
+}
+
+// a Hermitian positive definite A: U = W, so its own columns are rotated
+__global__ void k_svd_copy(int32_t n, const c64* A, int32_t lda, c64* X, int32_t* piv) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < n * n) X[t] = A[t % n + (int64_t)(t / n) * lda];
+  if (t < n) piv[t] = t;
+}
+
+__global__ void k_svd_clear(int32_t n, unsigned long long* flags) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) flags[i] = 0ull;
+}
+
+// sigma (descending, with its permutation) and W = P U: column j of W has the normalised column j
+// of X in the rows piv.
+__global__ void __launch_bounds__(SV_T) k_svd_right(int32_t n, const c64* X, const int32_t* piv, c64* W, int32_t ldw,
+                                                    double* sigma, int32_t* perm) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int j = wv; j < n; j += SV_T / 64) {
+    double t = 0;
+    for (int i = lane; i < n; i += 64) t += cabs2<double>(X[i + j * n]);
+    t = sqrt(wave_sum_dpp(t));
+    if (lane == 0) sigma[512 + j] = t;
+    const double inv = t > 0 ? 1.0 / t : 0.0;
+    for (int i = lane; i < n; i += 64) W[piv[i] + (int64_t)j * ldw] = zscale(X[i + j * n], inv);
+  }
+  __syncthreads();
+  for (int j = tid; j < n; j += SV_T) perm[desc_rank(n, sigma + 512, j)] = j;
+  __syncthreads();
+  for (int r = tid; r < n; r += SV_T) sigma[r] = sigma[512 + perm[r]];
+}
+
 // ------------------------------------------------------------------ small GEMM (one workgroup)
 // C = op(A) * B (+ scale of columns), op = identity or conjugate transpose.
 __global__ void __launch_bounds__(SWG) k_small_gemm(int32_t m, int32_t n, int32_t k, const c64* A, int32_t lda,
@@ -730,6 +1130,179 @@ __global__ void __launch_bounds__(SWG) k_eig(int32_t n, c64* H, int32_t ldh, c64
   }
 }
 
+// The same decomposition for n <= 64 by one wavefront, H and Z in LDS: a rotation of the QR sweep
+// needs no barrier (the next one's pair comes from two lanes' registers), and the subdiagonal is
+// scanned for small entries by all lanes at once instead of by one.  The eigenvectors of the
+// triangular factor take its free lower triangle.  Bound by the chain of a rotation.  Order 20: 0.37 ms;
+// 0.86 in the kernel above, mostly one thread's scan and two workgroup barriers per rotation.
+__global__ void __launch_bounds__(64) k_eig_wave(int32_t n, const c64* Hin, int32_t ldh, c64* w, c64* Vout,
+                                                 int32_t ldv, int32_t* info) {
+  extern __shared__ __align__(16) unsigned char ew_smem[];
+  const int ld = n | 1, lane = threadIdx.x;   // odd: rows and columns are read without bank conflicts
+  c64* H = reinterpret_cast<c64*>(ew_smem);
+  c64* Z = H + ld * n;
+  c64* sv = Z + ld * n;
+  const bool row = lane < n;
+  for (int j = 0; j < n; ++j)
+    if (row) {
+      H[lane + j * ld] = Hin[lane + (int64_t)j * ldh];
+      Z[lane + j * ld] = make_double2(lane == j ? 1.0 : 0.0, 0.0);
+    }
+  __syncthreads();   // one wave: orders the LDS accesses
+  // --- Householder reduction to upper Hessenberg form
+  for (int k = 0; k + 2 < n; ++k) {
+    const bool in = row && lane > k;
+    c64 v = in ? H[lane + k * ld] : make_double2(0, 0);
+    const double nx2 = wave_sum_dpp(cabs2<double>(v));
+    const double nx = sqrt(nx2);
+    if (nx == 0.0) continue;
+    const c64 x0 = make_double2(lane_of(v.x, k + 1), lane_of(v.y, k + 1));
+    const double a0 = sqrt(cabs2<double>(x0));
+    const c64 ph = a0 > 0 ? make_double2(x0.x / a0, x0.y / a0) : make_double2(1, 0);
+    const double inv = 1.0 / sqrt(2.0 * (nx2 + nx * a0));   // 1 / |x - alpha e1|, alpha = -ph nx
+    if (lane == k + 1) v = zadd(v, zscale(ph, nx));
+    v = zscale(v, inv);
+    sv[lane] = v;
+    __syncthreads();
+    if (row && lane >= k) {   // left, lane = column
+      c64 d = make_double2(0, 0);
+      for (int i = k + 1; i < n; ++i) d = zadd(d, zmulc(sv[i], H[i + lane * ld]));
+      d = zscale(d, 2.0);
+      for (int i = k + 1; i < n; ++i) H[i + lane * ld] = zsub(H[i + lane * ld], zmul(sv[i], d));
+    }
+    __syncthreads();
+    if (row) {   // right, lane = row of H and of Z
+      c64 d = make_double2(0, 0), e = d;
+      for (int j = k + 1; j < n; ++j) {
+        d = zadd(d, zmul(H[lane + j * ld], sv[j]));
+        e = zadd(e, zmul(Z[lane + j * ld], sv[j]));
+      }
+      d = zscale(d, 2.0);
+      e = zscale(e, 2.0);
+      for (int j = k + 1; j < n; ++j) {
+        H[lane + j * ld] = zsub(H[lane + j * ld], zmul(d, zconj(sv[j])));
+        Z[lane + j * ld] = zsub(Z[lane + j * ld], zmul(e, zconj(sv[j])));
+      }
+    }
+    __syncthreads();
+    if (row && lane > k + 1) H[lane + k * ld] = make_double2(0, 0);
+    __syncthreads();
+  }
+  // --- shifted QR (full Schur form)
+  const double eps = 2.220446049250313e-16;
+  int hi = n - 1, iter = 0, total = 0;
+  while (hi >= 0) {
+    // the last small subdiagonal entry at or above row hi opens the active window [lo, hi]
+    bool small = false;
+    if (lane >= 1 && lane <= hi) {
+      const double sd = sqrt(cabs2<double>(H[lane + (lane - 1) * ld]));
+      const double dd = sqrt(cabs2<double>(H[lane + lane * ld])) + sqrt(cabs2<double>(H[lane - 1 + (lane - 1) * ld]));
+      small = sd <= eps * dd || sd < 1e-300;
+    }
+    const unsigned long long m = __ballot(small);
+    const int lo = m ? 63 - __clzll(m) : 0;
+    if (lo > 0 && lane == 0) H[lo + (lo - 1) * ld] = make_double2(0, 0);
+    __syncthreads();
+    if (lo == hi) {
+      --hi;
+      iter = 0;
+      continue;
+    }
+    if (++total > 60 * n) {
+      if (lane == 0) info[0] = 1;   // QR failed to converge
+      break;
+    }
+    c64 mu;
+    {
+      const c64 a = H[hi - 1 + (hi - 1) * ld], b = H[hi - 1 + hi * ld], c = H[hi + (hi - 1) * ld], d = H[hi + hi * ld];
+      if (iter > 0 && iter % 11 == 0) {
+        mu = zadd(d, make_double2(0.75 * zabs(c), 0.0));   // exceptional shift
+      } else {
+        const c64 hd = zscale(zsub(a, d), 0.5);
+        const c64 disc = zsqrt(zadd(zmul(hd, hd), zmul(b, c)));
+        const c64 m1 = zadd(zscale(zadd(a, d), 0.5), disc), m2 = zsub(zscale(zadd(a, d), 0.5), disc);
+        const bool first = cabs2<double>(zsub(m1, d)) < cabs2<double>(zsub(m2, d));
+        mu = make_double2(first ? m1.x : m2.x, first ? m1.y : m2.y);
+      }
+    }
+    ++iter;
+    c64 x = zsub(H[lo + lo * ld], mu), y = H[lo + 1 + lo * ld];
+    for (int k = lo; k < hi; ++k) {
+      // G = [[c, s], [-conj(s), c]], c real, G [x; y] = [r; 0]
+      const double nx2 = cabs2<double>(x), ny2 = cabs2<double>(y);
+      double c;
+      c64 s;
+      if (ny2 == 0.0) {
+        c = 1.0;
+        s = make_double2(0, 0);
+      } else if (nx2 == 0.0) {
+        c = 0.0;
+        s = zscale(zconj(y), 1.0 / sqrt(ny2));
+      } else {
+        const double inv = rsqrt1(nx2) * rsqrt1(nx2 + ny2);
+        c = nx2 * inv;
+        s = zscale(zmul(x, zconj(y)), inv);
+      }
+      const int j0 = (k > lo) ? k - 1 : lo;
+      if (row && lane >= j0) {   // rows k, k + 1, lane = column
+        const c64 hk = H[k + lane * ld], hk1 = H[k + 1 + lane * ld];
+        H[k + lane * ld] = zadd(zscale(hk, c), zmul(s, hk1));
+        H[k + 1 + lane * ld] = zsub(zscale(hk1, c), zmul(zconj(s), hk));
+      }
+      __syncthreads();
+      const int rmax = min(k + 2, hi);
+      c64 nk = make_double2(0, 0);
+      if (lane <= rmax) {   // columns k, k + 1 of H, lane = row
+        const c64 mk = H[lane + k * ld], mk1 = H[lane + (k + 1) * ld];
+        nk = zadd(zscale(mk, c), zmul(zconj(s), mk1));
+        H[lane + k * ld] = nk;
+        H[lane + (k + 1) * ld] = zsub(zscale(mk1, c), zmul(s, mk));
+      }
+      if (row) {
+        const c64 mk = Z[lane + k * ld], mk1 = Z[lane + (k + 1) * ld];
+        Z[lane + k * ld] = zadd(zscale(mk, c), zmul(zconj(s), mk1));
+        Z[lane + (k + 1) * ld] = zsub(zscale(mk1, c), zmul(s, mk));
+      }
+      // the next rotation's pair: rows k + 1 and k + 2 of column k
+      x = make_double2(lane_of(nk.x, k + 1), lane_of(nk.y, k + 1));
+      const int l2 = min(k + 2, 63);
+      y = make_double2(lane_of(nk.x, l2), lane_of(nk.y, l2));
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  const c64 lam = row ? H[lane + lane * ld] : make_double2(0, 0);
+  if (row) w[lane] = lam;
+  // --- eigenvectors of the triangular T = H: T y = lam_k y, y_k = 1, lane = k; Y[j][k] in H[k + j ld]
+  double tnorm = 0;
+  for (int j = 0; j < n; ++j) {
+    if (row && lane <= j) tnorm = fmax(tnorm, cabs2<double>(H[lane + j * ld]));
+  }
+  tnorm = sqrt(wave_max_dpp(tnorm));
+  const double smin = fmax(eps * tnorm, 1e-300);
+  for (int i = n - 2; i >= 0; --i) {
+    if (row && lane > i) {
+      c64 acc = H[i + lane * ld];
+      for (int j = i + 1; j < lane; ++j) acc = zadd(acc, zmul(H[i + j * ld], H[lane + j * ld]));
+      c64 d = zsub(H[i + i * ld], lam);
+      if (sqrt(cabs2<double>(d)) < smin) d = make_double2(smin, 0);
+      H[lane + i * ld] = zscale(zdiv(acc, d), -1.0);
+    }
+    __syncthreads();
+  }
+  // V = Z Y, columns normalised, lane = row
+  for (int k = 0; k < n; ++k) {
+    c64 acc = make_double2(0, 0);
+    if (row) {
+      acc = Z[lane + k * ld];
+      for (int j = 0; j < k; ++j) acc = zadd(acc, zmul(Z[lane + j * ld], H[k + j * ld]));
+    }
+    const double s2 = wave_sum_dpp(cabs2<double>(acc));
+    const double inv = s2 > 0 ? 1.0 / sqrt(s2) : 0.0;
+    if (row) Vout[lane + (int64_t)k * ldv] = zscale(acc, inv);
+  }
+}
+
 int32_t eig(cbs_system* s, int32_t n, c64* H, int32_t ldh, c64* w, c64* V, int32_t ldv, int32_t* info_dev,
             hipStream_t st) {
   if (n <= 0) return CBS_OK;
@@ -737,11 +1310,99 @@ int32_t eig(cbs_system* s, int32_t n, c64* H, int32_t ldh, c64* w, c64* V, int32
     set_error("eig: order %d above 512", n);
     return CBS_EINVAL;
   }
+  if (n <= 64) {
+    CBS_HIP(hipFuncSetAttribute((const void*)k_eig_wave, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SV_LDS));
+    const size_t smem = ((size_t)2 * (n | 1) * n + 64) * sizeof(c64);
+    hipLaunchKernelGGL(k_eig_wave, dim3(1), dim3(64), smem, st, n, (const c64*)H, ldh, w, V, ldv, info_dev);
+    CBS_HIP(hipGetLastError());
+    return CBS_OK;
+  }
   c64* Z = nullptr;
   c64* Y = nullptr;
   CBS_TRY(ws_get(s->ws, "eig.Z", (size_t)n * n, &Z));
   CBS_TRY(ws_get(s->ws, "eig.Y", (size_t)n * n, &Y));
   hipLaunchKernelGGL(k_eig, dim3(1), dim3(SWG), 0, st, n, H, ldh, w, V, ldv, Z, Y, info_dev);
+  CBS_HIP(hipGetLastError());
+  return CBS_OK;
+}
+
+// sigma (descending), perm and the right singular vectors W of A (kept): column perm[r] of W
+// belongs to sigma[r].  hermitian: A is Hermitian positive definite.
+int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, int32_t ldw, double* sigma,
+                  int32_t* perm, bool hermitian, hipStream_t st) {
+  if (n <= 0) return CBS_OK;
+  if (n > 256) {
+    set_error("svd: order %d above 256", n);
+    return CBS_EINVAL;
+  }
+  constexpr int MAXS = 60, BATCH = 6;
+  c64* X = nullptr;
+  int32_t* piv = nullptr;
+  unsigned long long* flags = nullptr;
+  CBS_TRY(ws_get(s->ws, "svd.X", (size_t)n * n, &X));
+  CBS_TRY(ws_get(s->ws, "svd.piv", (size_t)n, &piv));
+  CBS_TRY(ws_get(s->ws, "svd.flag", (size_t)MAXS, &flags));
+  if (hermitian) {
+    hipLaunchKernelGGL(k_svd_copy, dim3((n * n + 255) / 256), dim3(256), 0, st, n, A, lda, X, piv);
+    CBS_HIP(hipGetLastError());
+  } else {
+    if (n <= 64)
+      hipLaunchKernelGGL(k_svd_qr<1>, dim3(1), dim3(256), 0, st, n, A, lda, X, piv);
+    else if (n <= 128)
+      hipLaunchKernelGGL(k_svd_qr<2>, dim3(1), dim3(512), 0, st, n, A, lda, X, piv);
+    else {
+      c64* M = nullptr;
+      CBS_TRY(ws_get(s->ws, "svd.M", (size_t)n * n, &M));
+      hipLaunchKernelGGL(k_svd_qr_big<4>, dim3(1), dim3(SV_T), 0, st, n, A, lda, M, X, piv);
+    }
+    CBS_HIP(hipGetLastError());
+  }
+  // column blocks of bs, a pair of them in LDS: two (all columns) up to order 64; 32 columns up to
+  // order 128, 16 beyond
+  const int bs = n <= 64 ? (n + 1) / 2 : n <= 128 ? 32 : 16;
+  int nb = (n + bs - 1) / bs;
+  nb += nb & 1;
+  // lanes of a column pair: four rows a lane; fewer lanes make long chains, more lanes repeat the
+  // rotation angles in more waves (order 64, ten sweeps: two rows 0.75 ms, four 0.64, eight 0.76)
+  int gsize = 8;
+  while (gsize * 4 < n) gsize <<= 1;
+  const int threads = (bs * gsize + 63) / 64 * 64;
+  const size_t smem = (size_t)2 * bs * sv_ldc(n) * sizeof(c64);
+  const int rpl = (n + gsize - 1) / gsize;
+  const void* cols = rpl == 1 ? (const void*)k_svd_cols<1> : rpl == 2 ? (const void*)k_svd_cols<2> : (const void*)k_svd_cols<4>;
+  CBS_HIP(hipFuncSetAttribute(cols, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SV_LDS));
+  auto sweep_launch = [&](int32_t round, int32_t sweep, int32_t sweeps) -> int32_t {
+    int32_t bs_ = bs, nb_ = nb, gs_ = gsize;
+    void* args[] = {&n, &bs_, &nb_, &round, &sweep, &sweeps, &gs_, &X, &flags};
+    CBS_HIP(hipLaunchKernel(cols, dim3(nb / 2), dim3(threads), args, smem, st));
+    return CBS_OK;
+  };
+  hipLaunchKernelGGL(k_svd_clear, dim3(1), dim3(64), 0, st, MAXS, flags);
+  CBS_HIP(hipGetLastError());
+  int sweeps = 0;
+  if (nb == 2) {
+    CBS_TRY(sweep_launch(0, 0, MAXS));
+  } else {
+    for (int s0 = 0; s0 < MAXS; s0 += BATCH) {
+      for (int sw = s0; sw < s0 + BATCH; ++sw)
+        for (int r = 0; r < nb - 1; ++r) CBS_TRY(sweep_launch(r, sw, 1));
+      unsigned long long h[BATCH];
+      CBS_HIP(hipMemcpyAsync(h, flags + s0, sizeof(h), hipMemcpyDeviceToHost, st));
+      CBS_HIP(hipStreamSynchronize(st));
+      bool done = false;
+      for (int k = 0; k < BATCH && !done; ++k) {
+        double om = 0;
+        std::memcpy(&om, &h[k], sizeof(om));
+        sweeps = s0 + k + 1;
+        done = !(om >= SV_TOL2);
+      }
+      if (done) break;
+    }
+  }
+  if (const char* v = getenv("CBS_VERBOSE"))
+    if (v[0] == '3') fprintf(stderr, "[cbs] svd: order %d, %d blocks of %d, %d sweeps\n", n, nb, bs, sweeps);
+  hipLaunchKernelGGL(k_svd_right, dim3(1), dim3(SV_T), 0, st, n, (const c64*)X, (const int32_t*)piv, W, ldw, sigma,
+                     perm);
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }

@@ -345,7 +345,11 @@ int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, 
   CBS_HIP(hipGetLastError());
   dump("T", T, (size_t)n * n * sizeof(c64), st);
   dump("Tl", Tl, (size_t)n * n * sizeof(c64), st);
-  CBS_TRY(svd(n, T, n, W, n, sig, perm, st));
+  // the Rayleigh-Ritz extraction needs the right vectors only; the Hankel extraction U too
+  if (prm->extraction == CBS_HANKEL || getenv("CBS_SVD_SINGLE"))
+    CBS_TRY(svd(n, T, n, W, n, sig, perm, st));
+  else
+    CBS_TRY(svd_right(s, n, T, n, W, n, sig, perm, false, st));
   dump("U", T, (size_t)n * n * sizeof(c64), st);
   dump("W", W, (size_t)n * n * sizeof(c64), st);
   dump("sigma", sig, (size_t)n * sizeof(double), st);
@@ -387,30 +391,31 @@ int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, 
     if (m == 0) return CBS_OK;
 
     // --- reduced Hankel problem
-    c64 *Up = nullptr, *Wp = nullptr, *TW = nullptr, *Bred = nullptr, *tau = nullptr, *phi = nullptr;
-    CBS_TRY(ws_get(ws, "hk.Up", (size_t)n * m, &Up));
+    c64 *Wp = nullptr, *tau = nullptr, *phi = nullptr;
     CBS_TRY(ws_get(ws, "hk.Wp", (size_t)n * m, &Wp));
-    CBS_TRY(ws_get(ws, "hk.TW", (size_t)n * m, &TW));
-    CBS_TRY(ws_get(ws, "hk.B", (size_t)m * m, &Bred));
     CBS_TRY(ws_get(ws, "hk.tau", (size_t)2 * n, &tau));
     CBS_TRY(ws_get(ws, "hk.phi", (size_t)m * m, &phi));
-    hipLaunchKernelGGL(k_gather_cols, dim3(launch_grid((int64_t)n * m)), dim3(256), 0, st, n, m, (const c64*)T, n,
-                       (const int32_t*)perm, Up, n);
     hipLaunchKernelGGL(k_gather_cols, dim3(launch_grid((int64_t)n * m)), dim3(256), 0, st, n, m, (const c64*)W, n,
                        (const int32_t*)perm, Wp, n);
     CBS_HIP(hipGetLastError());
-    CBS_TRY(small_gemm(n, m, n, Tl, n, false, Wp, n, TW, n, nullptr, nullptr, st));
-    // Bred = Up^H TW diag(1/sigma)
     std::vector<double> inv(m);
-    for (int i = 0; i < m; ++i) inv[i] = 1.0 / hsig[i];
-    double* dinv = nullptr;
-    CBS_TRY(ws_get(ws, "hk.inv", (size_t)m, &dinv));
-    CBS_HIP(hipMemcpyAsync(dinv, inv.data(), m * sizeof(double), hipMemcpyHostToDevice, st));
-    CBS_TRY(small_gemm(m, m, n, Up, n, true, TW, n, Bred, m, dinv, nullptr, st));
-    dump("Bred", Bred, (size_t)m * m * sizeof(c64), st);
     if (prm->extraction == CBS_HANKEL) {
       // the reduced Hankel eigenpairs are the result only for the Hankel extraction; the
-      // Rayleigh-Ritz extraction uses the SVD basis alone
+      // Rayleigh-Ritz extraction uses the SVD basis alone.  Bred = Up^H T< Wp diag(1/sigma)
+      c64 *Up = nullptr, *TW = nullptr, *Bred = nullptr;
+      double* dinv = nullptr;
+      CBS_TRY(ws_get(ws, "hk.Up", (size_t)n * m, &Up));
+      CBS_TRY(ws_get(ws, "hk.TW", (size_t)n * m, &TW));
+      CBS_TRY(ws_get(ws, "hk.B", (size_t)m * m, &Bred));
+      CBS_TRY(ws_get(ws, "hk.inv", (size_t)m, &dinv));
+      hipLaunchKernelGGL(k_gather_cols, dim3(launch_grid((int64_t)n * m)), dim3(256), 0, st, n, m, (const c64*)T, n,
+                         (const int32_t*)perm, Up, n);
+      CBS_HIP(hipGetLastError());
+      CBS_TRY(small_gemm(n, m, n, Tl, n, false, Wp, n, TW, n, nullptr, nullptr, st));
+      for (int i = 0; i < m; ++i) inv[i] = 1.0 / hsig[i];
+      CBS_HIP(hipMemcpyAsync(dinv, inv.data(), m * sizeof(double), hipMemcpyHostToDevice, st));
+      CBS_TRY(small_gemm(m, m, n, Up, n, true, TW, n, Bred, m, dinv, nullptr, st));
+      dump("Bred", Bred, (size_t)m * m * sizeof(c64), st);
       CBS_TRY(eig(s, m, Bred, m, tau, phi, m, info, st));
       dump("tau", tau, (size_t)m * sizeof(c64), st);
       dump("phi", phi, (size_t)m * m * sizeof(c64), st);
