@@ -287,15 +287,15 @@ __device__ __forceinline__ void sum_part(const double* part, int64_t off, int n,
 __device__ __forceinline__ bool is_active(int st) { return st == ST_ACT_LO || st == ST_ACT_HI; }
 
 // Compact lists of the active runs of each phase (ascending) and their counts, so the
-// iteration kernels launch over full groups of active runs.  One block of 256 threads.
-__device__ void build_lists(BicgScal& sc, int32_t nruns) {
-  __shared__ int wcnt[2][4];
+// iteration kernels launch over full groups of active runs.  One block.
+__device__ void build_lists(const BicgScal& sc, int32_t nruns) {
+  __shared__ int wcnt[2][16];
   __shared__ int base[2];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (tid == 0) base[0] = base[1] = 0;
   __syncthreads();
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int r0 = 0; r0 < nruns; r0 += 256) {
+  for (int r0 = 0; r0 < nruns; r0 += blockDim.x) {
     const int run = r0 + tid;
     const int st = (run < nruns) ? sc.status[run] : -1;
     const bool lo = st == ST_ACT_LO, hi = st == ST_ACT_HI;
@@ -313,10 +313,8 @@ __device__ void build_lists(BicgScal& sc, int32_t nruns) {
     if (lo) sc.list[olo + __popcll(mlo & below)] = run;
     if (hi) sc.list[nruns + ohi + __popcll(mhi & below)] = run;
     __syncthreads();
-    if (tid == 0) {
-      base[0] += wcnt[0][0] + wcnt[0][1] + wcnt[0][2] + wcnt[0][3];
-      base[1] += wcnt[1][0] + wcnt[1][1] + wcnt[1][2] + wcnt[1][3];
-    }
+    if (tid < 2)
+      for (int w = 0; w < (int)blockDim.x / 64; ++w) base[tid] += wcnt[tid][w];
     __syncthreads();
   }
   if (tid == 0) {
@@ -327,15 +325,15 @@ __device__ void build_lists(BicgScal& sc, int32_t nruns) {
 __device__ __forceinline__ bool is_ru(int st) { return st == ST_RU_LO || st == ST_RU_HI; }
 
 // Compact list of the runs marked for residual replacement (either phase, ascending) in
-// list[2][.], count n_active[2].  One block of 256 threads.
-__device__ void build_ru_list(BicgScal& sc, int32_t nruns) {
-  __shared__ int wcnt[4];
+// list[2][.], count n_active[2].  One block.
+__device__ void build_ru_list(const BicgScal& sc, int32_t nruns) {
+  __shared__ int wcnt[16];
   __shared__ int base;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (tid == 0) base = 0;
   __syncthreads();
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int r0 = 0; r0 < nruns; r0 += 256) {
+  for (int r0 = 0; r0 < nruns; r0 += blockDim.x) {
     const int run = r0 + tid;
     const bool ru = (run < nruns) && is_ru(sc.status[run]);
     const unsigned long long m = __ballot(ru);
@@ -345,7 +343,8 @@ __device__ void build_ru_list(BicgScal& sc, int32_t nruns) {
     for (int w = 0; w < wv; ++w) o += wcnt[w];
     if (ru) sc.list[2 * (int64_t)nruns + o + __popcll(m & below)] = run;
     __syncthreads();
-    if (tid == 0) base += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+    if (tid == 0)
+      for (int w = 0; w < (int)blockDim.x / 64; ++w) base += wcnt[w];
     __syncthreads();
   }
   if (tid == 0) sc.n_active[2] = base;
@@ -493,25 +492,22 @@ __global__ void __launch_bounds__(256) k_ru_list(BicgScal sc, int32_t nruns) {
   build_lists(sc, nruns);
 }
 
-__global__ void __launch_bounds__(256) k_s3(BicgScal sc, int32_t nruns, int32_t nchunks, double* part,
-                                            double tol, int32_t max_iter, int32_t max_ru, double ru_factor) {
-  // the partial sums of each replaced run (listed by k_ru_list): the whole block adds them up and
-  // leaves the totals in the run's first chunk slot
-  __shared__ double red[4][4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__global__ void __launch_bounds__(1024) k_s3(BicgScal sc, int32_t nruns, int32_t nchunks, double* part,
+                                             double tol, int32_t max_iter, int32_t max_ru, double ru_factor) {
+  // the partial sums of the replaced runs (listed by k_ru_list), a wave to a run: the totals go to
+  // the run's first chunk slot
+  const int lane = threadIdx.x & 63;
   const int nlist = sc.n_active[2];
-  for (int i = 0; i < nlist; ++i) {
+  for (int i = threadIdx.x >> 6; i < nlist; i += blockDim.x >> 6) {
     const int run = sc.list[2 * (int64_t)nruns + i];
     double t[4] = {0, 0, 0, 0};
-    for (int c = tid; c < nchunks; c += 256)
+    for (int c = lane; c < nchunks; c += 64)
       for (int k = 0; k < 4; ++k) t[k] += part[((int64_t)run * nchunks + c) * 4 + k];
     for (int k = 0; k < 4; ++k) t[k] = wsum<double>(t[k]);
     if (lane == 0)
-      for (int k = 0; k < 4; ++k) red[wv][k] = t[k];
-    __syncthreads();
-    if (tid < 4) part[(int64_t)run * nchunks * 4 + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
-    __syncthreads();
+      for (int k = 0; k < 4; ++k) part[(int64_t)run * nchunks * 4 + k] = t[k];
   }
+  __syncthreads();
   for (int run = threadIdx.x; run < nruns; run += blockDim.x) {
     int st = sc.status[run];
     if (is_ru(st)) {
@@ -869,7 +865,8 @@ static int32_t alloc_vecs(cbs_system* s, BicgVecs<T>& v, size_t nruns, const std
   CBS_TRY(ws_get(ws, (pre + "X").c_str(), nv, &v.X));
   if (s->proj.n_atoms > 0) CBS_TRY(ws_get(ws, (pre + "KT").c_str(), nruns * s->proj.n_atoms * 12, &v.KT));
   v.tile_y = s->tile_y[std::is_same<T, float>::value ? 1 : 0];
-  v.ntiles = stencil_tiles(s, v.tile_y);
+  v.zseg = stencil_segments(s, v.tile_y, (int32_t)nruns);
+  v.ntiles = stencil_tiles(s, v.tile_y) * v.zseg;
   CBS_TRY(ws_get(ws, (pre + "sig").c_str(), nruns * v.ntiles, &v.sig));
   return CBS_OK;
 }
@@ -891,7 +888,7 @@ int32_t bicg_alloc(BicgSolve& b, const char* tag) {
     if (b.mixed) CBS_TRY(alloc_vecs<float>(s, b.lo, R, t + ".lo."));
     CBS_TRY(alloc_vecs<double>(s, b.hi, R, t + ".hi."));
     CBS_TRY(ws_get(ws, (t + ".Y").c_str(), R * s->N, &b.Y));
-    b.nchunks = update_chunks(s);
+    b.nchunks = update_chunks(s, b.nruns);
     const int na = s->proj.n_atoms;
     CBS_TRY(ws_get(ws, (t + ".signl").c_str(), R * std::max(na, 1), &b.signl));
     CBS_TRY(ws_get(ws, (t + ".upd").c_str(), R * b.nchunks * 4, &b.upd_part));
@@ -967,6 +964,7 @@ static int32_t enqueue_stencil_bra(BicgSolve& b, BicgVecs<T>& v, int32_t need, i
   l.status = b.sc.status;
   l.need_status = need;
   l.sig_part = v.sig;
+  l.zseg = v.zseg;
   const int ph = (need == ST_ACT_LO) ? 0 : 1;
   l.list = b.sc.list + (size_t)ph * b.nruns;
   l.count = b.sc.n_active + ph;
@@ -1023,7 +1021,7 @@ static int32_t enqueue_replacement(BicgSolve& b, int parity, hipStream_t st) {
                      (const Pair<double>*)b.hi.Q, (const Pair<double>*)b.hi.KT, s->proj.grp_off, s->proj.grp_key,
                      (const double*)s->proj.grp_u64, b.hi.R, (Pair<double>*)nullptr, b.ru_part);
   CBS_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_s3, dim3(1), dim3(256), 0, st, b.sc, b.nruns, b.ru_chunks, b.ru_part, b.tol,
+  hipLaunchKernelGGL(k_s3, dim3(1), dim3(1024), 0, st, b.sc, b.nruns, b.ru_chunks, b.ru_part, b.tol,
                      b.max_iter, b.max_ru, b.ru_factor);
   CBS_HIP(hipGetLastError());
   return CBS_OK;
@@ -1280,7 +1278,8 @@ int32_t bicg_run(std::vector<BicgSolve*>& all, hipStream_t user, int32_t chunk, 
     rc = launch_chunk(0);
     int launched = 1;
     for (int c = 0; c < max_chunks && rc == CBS_OK; ++c) {
-      if (launched < max_chunks) {
+      // not past the iteration limit, though, where the runs are expected to have ended
+      if (launched < max_chunks && (launched * chunk < max_iter || launched == c)) {
         rc = launch_chunk(launched);
         ++launched;
         if (rc != CBS_OK) break;

@@ -55,8 +55,9 @@ struct BicgVecs {
   Pair<T>* Q = nullptr;
   Pair<T>* X = nullptr;
   Pair<T>* KT = nullptr;
-  double2* sig = nullptr;   // [run][tile] stencil partials of sigma
-  int32_t tile_y = 0, ntiles = 0;
+  double2* sig = nullptr;   // [run][tile][segment] stencil partials of sigma
+  int32_t tile_y = 0, zseg = 1;
+  int32_t ntiles = 0;       // partials of sigma per run: tiles times z segments
   hipEvent_t ev0 = nullptr, ev1 = nullptr;   // profiling of the stencil launches
   int64_t prof_launches = 0;
   double prof_ms = 0, prof_bytes = 0;

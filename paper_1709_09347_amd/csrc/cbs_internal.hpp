@@ -326,15 +326,16 @@ struct StencilLaunch {
   const double2* xcoef;     // BiCG [nruns]
   const int32_t* status;    // [nruns] or NULL (no filter)
   int32_t need_status;      // blocks of runs whose status differs return at once
-  double2* sig_part;        // BiCG [nruns*ntiles]
+  double2* sig_part;        // BiCG [nruns * ntiles * segments]
   const int32_t* list;      // device [nruns] active runs (ascending) or NULL: all runs
   const int32_t* count;     // device: entries of list (with list)
-  int32_t zseg;             // apply only: z segments per tile (0 or 1: one), for short run lists
+  int32_t zseg;             // z segments per tile (0 or 1: one), for few runs
 };
 template <typename R>
 int32_t launch_stencil(const cbs_system* s, bool bicg, const StencilLaunch& a, int32_t tile_y,
                        hipStream_t st);
 int32_t stencil_tiles(const cbs_system* s, int32_t tile_y);
+int32_t stencil_segments(const cbs_system* s, int32_t tile_y, int32_t nruns);   // z segments per tile
 int32_t default_tile_y(const cbs_system* s, int32_t bytes_per_pair);
 // Times every feasible tile height once per system and precision (CBS_AUTOTUNE=0: keep defaults).
 int32_t autotune_tiles(cbs_system* s, hipStream_t st);
@@ -358,7 +359,7 @@ int32_t launch_update(const cbs_system* s, int32_t nruns, void* r, const void* q
 template <typename R>
 int32_t launch_ket_add(const cbs_system* s, int32_t nruns, void* q, const void* kt, hipStream_t st);
 
-int32_t update_chunks(const cbs_system* s);
+int32_t update_chunks(const cbs_system* s, int32_t nruns);
 
 // The operator on vector-major blocks (apply.hip): y_v = c0 (H0 - E) x_v + cp H+ x_v + cm H- x_v
 // (+ beta prev_v), coefficients on the host (passed as kernel arguments), kt: scratch of
