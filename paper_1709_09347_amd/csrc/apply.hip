@@ -2,13 +2,14 @@
 // (P(z): 1, z, 1/z) for cbs_apply, cbs_apply_noalloc, cbs_apply_parts, the bands' filter, the
 // Rayleigh-Ritz projections and the adjoint.
 //
-// Three kernels read the caller's x and write its y, with no staging copy of either; the
+// Three parts read the caller's x and write its y, with no staging copy of either; the
 // coefficients travel as kernel arguments (64 vectors a call), so nothing is copied from the
 // host and nothing has to outlive the launch:
-//   k_ap_bra    K[atom][w][i] = h_ai sum_w' coef(w' - w) sum_e u_{e,i} x(idx_e)
+//   ap_bra      K[atom][w][i] = h_ai sum_w' coef(w' - w) sum_e u_{e,i} x(idx_e)
 //   k_ap_local  y = finite differences, potential and cell phases of x (+ beta prev)
 //   k_ap_ket    y += sum_i u_{e,i} K[a_e][w_e][i], on the matrix cores, over the 64-point
 //               groups that lie in a ball
+// The bra is a launch of its own or the first workgroups of the local part's (bra_shape).
 // The BiCG kernels (stencil.hip, nonlocal.hip) keep a run's primal and dual side by side; here
 // a vector stands alone, which halves the registers of the z queue and lets a cell be cut into
 // z segments until the chip is full.
@@ -37,6 +38,118 @@ __device__ __forceinline__ apmf4<float>::T ap_mfma(float a, float b, apmf4<float
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// ------------------------------------------------------------------ bra
+template <typename R>
+struct ApBra {
+  int32_t n_atoms, nv, nvb, nlogical;
+  int32_t nsub;   // items (an atom and its vectors) per workgroup, four waves each; further waves leave
+  int32_t grid;   // with the local part: the launch's first workgroups
+  int64_t N;
+  const int32_t* seg;
+  const int32_t* idx;
+  const R* u;       // [nnz][4]
+  const R* coeff;   // [n_atoms][4]
+  const cplx<R>* x;
+  R* kt;            // per group of AP_VG vectors: [atom * 3 + w][i][2 * vectors of the group]
+};
+
+// Four waves an item, an atom and VB vectors; a thread takes every 256th ball entry (one table read
+// for VB coalesced gathers) and the sums of each cell shift are added over the lanes and waves.  The
+// 4 projectors would fill a quarter of an MFMA tile, and the vector units have the same FP64 rate.
+// Bound by the gathers that miss L2 (overlapping balls; consecutive workgroups of an XCD share
+// the vectors): 48x48x32, 96 atoms, 32 vectors: 38 us in complex128, 24 in complex64, where one
+// MFMA workgroup per (atom, 16 pairs) took 145 and 194; with 512 threads 45 us, with the atoms'
+// vectors side by side on an XCD 46 us.
+template <typename R, typename C, int VB>
+__device__ __forceinline__ void ap_bra(const ApBra<R>& a, const ApCoef& cf, unsigned char* smem) {
+  const int nsub = a.nsub;
+  const int sub = threadIdx.x >> 8, tid = threadIdx.x & 255, lane = tid & 63, wv = tid >> 6;
+  const int lb = remap_active(blockIdx.x, a.nlogical);
+  if (lb < 0 || sub >= nsub) return;
+  C(*red)[3][8 * VB] = reinterpret_cast<C(*)[3][8 * VB]>(smem) + 4 * sub;   // [wave][shift][(vector, i, re/im)]
+  const int item = min(lb * nsub + sub, a.n_atoms * a.nvb - 1);   // the last workgroup may repeat the last one
+  const int vb = item / a.n_atoms, atom = item - vb * a.n_atoms;
+  const int v0 = vb * VB;
+  using U4 = typename vec4<R>::T;
+  const U4* ut = reinterpret_cast<const U4*>(a.u);
+  const cplx<R>* xv[VB];
+#pragma unroll
+  for (int k = 0; k < VB; ++k) xv[k] = a.x + (int64_t)min(v0 + k, a.nv - 1) * a.N;
+  for (int sg = 0; sg < 3; ++sg) {
+    const int lo = a.seg[4 * atom + sg], hi = a.seg[4 * atom + sg + 1];
+    C acc[8 * VB];
+#pragma unroll
+    for (int k = 0; k < 8 * VB; ++k) acc[k] = 0;
+    // two entries a step; their gathers go out together with the next step's indices; loads past
+    // the segment are clamped into it and weighted by zero
+    const int last = max(hi - 1, lo);
+    int n0 = 0, n1 = 0;
+    if (lo < hi) {
+      n0 = a.idx[min(lo + tid, last)];
+      n1 = a.idx[min(lo + 256 + tid, last)];
+    }
+    for (int e0 = lo; e0 < hi; e0 += 512) {
+      const int ea = e0 + tid, eb = ea + 256;
+      const U4 ua = ut[min(ea, last)], ub = ut[min(eb, last)];
+      cplx<R> ta[VB], tb[VB];
+#pragma unroll
+      for (int k = 0; k < VB; ++k) ta[k] = xv[k][n0];
+#pragma unroll
+      for (int k = 0; k < VB; ++k) tb[k] = xv[k][n1];
+      n0 = a.idx[min(ea + 512, last)];
+      n1 = a.idx[min(eb + 512, last)];
+      const C oa = ea < hi ? (C)1 : (C)0, ob = eb < hi ? (C)1 : (C)0;
+      const C wa[4] = {oa * (C)ua.x, oa * (C)ua.y, oa * (C)ua.z, oa * (C)ua.w};
+      const C wb[4] = {ob * (C)ub.x, ob * (C)ub.y, ob * (C)ub.z, ob * (C)ub.w};
+#pragma unroll
+      for (int k = 0; k < VB; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[8 * k + 2 * i] += wa[i] * (C)ta[k].x;
+          acc[8 * k + 2 * i + 1] += wa[i] * (C)ta[k].y;
+        }
+#pragma unroll
+      for (int k = 0; k < VB; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[8 * k + 2 * i] += wb[i] * (C)tb[k].x;
+          acc[8 * k + 2 * i + 1] += wb[i] * (C)tb[k].y;
+        }
+    }
+    C t = 0;
+    if (lo < hi) t = wave_sums<8 * VB, C>(acc, lane);   // uniform over the workgroup
+    if ((lane & (64 / (8 * VB) - 1)) == 0) red[wv][sg][lane / (64 / (8 * VB))] = t;
+  }
+  __syncthreads();
+  // wave k: the 12 coefficients of vector v0 + k
+  const int k = __builtin_amdgcn_readfirstlane(wv), v = v0 + k;
+  if (k >= VB || v >= a.nv || lane >= 12) return;
+  const int w = lane >> 2, i = lane & 3, q = 8 * k + 2 * i;
+  const double2 d0 = cf.c0[v], dp = cf.cp[v], dm = cf.cm[v];
+  cplx<C> s = mkc<C>(0, 0);
+#pragma unroll
+  for (int w2 = 0; w2 < 3; ++w2) {
+    const int d = w2 - w;   // cell shift of the source relative to the entry
+    if (d > 1 || d < -1) continue;
+    const cplx<C> cd = mkc<C>((C)(d == 0 ? d0.x : d == 1 ? dp.x : dm.x), (C)(d == 0 ? d0.y : d == 1 ? dp.y : dm.y));
+    const cplx<C> g = mkc<C>(red[0][w2][q] + red[1][w2][q] + red[2][w2][q] + red[3][w2][q],
+                             red[0][w2][q + 1] + red[1][w2][q + 1] + red[2][w2][q + 1] + red[3][w2][q + 1]);
+    s = cfma<C>(s, cd, g);
+  }
+  s = cscale<C>(s, (C)a.coeff[4 * atom + i]);
+  const int vg = v / AP_VG, ncol = 2 * min(AP_VG, a.nv - vg * AP_VG);
+  R* dst = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + ((int64_t)(atom * 3 + w) * 4 + i) * ncol +
+           2 * (v - vg * AP_VG);
+  dst[0] = (R)s.x;
+  dst[1] = (R)s.y;
+}
+
+template <typename R, typename C, int VB>
+__global__ void __launch_bounds__(256) k_ap_bra(ApBra<R> a, ApCoef cf) {
+  __shared__ __align__(16) unsigned char smem[4 * 3 * 8 * VB * sizeof(C)];
+  ap_bra<R, C, VB>(a, cf, smem);
+}
+
 // ------------------------------------------------------------------ local part
 template <typename R>
 struct ApLocal {
@@ -59,11 +172,17 @@ struct ApLocal {
 // complex128 vectors without projectors, 66 us for 226 MB (3.4 TB/s); the pair kernel with its two
 // layout passes took 200 us.  48x48x32, 32 vectors: 24 us (was 111 + 37 us of layout passes).
 // PIPE: every thread stages at most two elements of a plane; ADD: beta prev is added.
-template <typename R, typename C, int P, bool PIPE, bool ADD>
-__global__ void __launch_bounds__(1024) k_ap_local(ApLocal<R> a, ApCoef cf) {
+template <typename R, typename C, int P, bool PIPE, bool ADD, int VB>
+__global__ void __launch_bounds__(1024) k_ap_local(ApLocal<R> a, ApBra<R> b, ApCoef cf) {
   extern __shared__ __align__(16) unsigned char ap_smem[];
+  if constexpr (VB > 0) {
+    if ((int)blockIdx.x < b.grid) {
+      ap_bra<R, C, VB>(b, cf, ap_smem);
+      return;
+    }
+  }
   cplx<R>* lds = reinterpret_cast<cplx<R>*>(ap_smem);
-  const int lb = remap_active(blockIdx.x, a.nlogical);
+  const int lb = remap_active(blockIdx.x - (VB > 0 ? b.grid : 0), a.nlogical);
   if (lb < 0) return;
   const int per = a.ntiles * a.nseg;
   const int v = lb / per;
@@ -205,108 +324,6 @@ __global__ void __launch_bounds__(1024) k_ap_local(ApLocal<R> a, ApCoef cf) {
   for (int j = 0; j < P; ++j) push(z1 + j, phase(z1 + j, ccast<C, R>(halo[j])), mkc<C>(0, 0));
 }
 
-// ------------------------------------------------------------------ bra
-template <typename R>
-struct ApBra {
-  int32_t n_atoms, nv, nvb, nlogical;
-  int64_t N;
-  const int32_t* seg;
-  const int32_t* idx;
-  const R* u;       // [nnz][4]
-  const R* coeff;   // [n_atoms][4]
-  const cplx<R>* x;
-  R* kt;            // per group of AP_VG vectors: [atom * 3 + w][i][2 * vectors of the group]
-};
-
-// One workgroup: one atom, VB vectors; a thread takes every 256th ball entry (one table read for
-// VB coalesced gathers) and the sums of each cell shift are added over the lanes and waves.  The
-// 4 projectors would fill a quarter of an MFMA tile, and the vector units have the same FP64 rate.
-// Bound by the gathers that miss L2 (overlapping balls; consecutive workgroups of an XCD share
-// the vectors): 48x48x32, 96 atoms, 32 vectors: 38 us in complex128, 24 in complex64, where one
-// MFMA workgroup per (atom, 16 pairs) took 145 and 194; with 512 threads 45 us, with the atoms'
-// vectors side by side on an XCD 46 us.
-template <typename R, typename C, int VB>
-__global__ void __launch_bounds__(256) k_ap_bra(ApBra<R> a, ApCoef cf) {
-  __shared__ C red[4][3][8 * VB];   // [wave][shift][(vector, i, re/im)]
-  const int lb = remap_active(blockIdx.x, a.nlogical);
-  if (lb < 0) return;
-  const int vb = lb / a.n_atoms, atom = lb - vb * a.n_atoms;
-  const int v0 = vb * VB;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  using U4 = typename vec4<R>::T;
-  const U4* ut = reinterpret_cast<const U4*>(a.u);
-  const cplx<R>* xv[VB];
-#pragma unroll
-  for (int k = 0; k < VB; ++k) xv[k] = a.x + (int64_t)min(v0 + k, a.nv - 1) * a.N;
-  for (int sg = 0; sg < 3; ++sg) {
-    const int lo = a.seg[4 * atom + sg], hi = a.seg[4 * atom + sg + 1];
-    C acc[8 * VB];
-#pragma unroll
-    for (int k = 0; k < 8 * VB; ++k) acc[k] = 0;
-    // two entries a step; their gathers go out together with the next step's indices; loads past
-    // the segment are clamped into it and weighted by zero
-    const int last = max(hi - 1, lo);
-    int n0 = 0, n1 = 0;
-    if (lo < hi) {
-      n0 = a.idx[min(lo + tid, last)];
-      n1 = a.idx[min(lo + 256 + tid, last)];
-    }
-    for (int e0 = lo; e0 < hi; e0 += 512) {
-      const int ea = e0 + tid, eb = ea + 256;
-      const U4 ua = ut[min(ea, last)], ub = ut[min(eb, last)];
-      cplx<R> ta[VB], tb[VB];
-#pragma unroll
-      for (int k = 0; k < VB; ++k) ta[k] = xv[k][n0];
-#pragma unroll
-      for (int k = 0; k < VB; ++k) tb[k] = xv[k][n1];
-      n0 = a.idx[min(ea + 512, last)];
-      n1 = a.idx[min(eb + 512, last)];
-      const C oa = ea < hi ? (C)1 : (C)0, ob = eb < hi ? (C)1 : (C)0;
-      const C wa[4] = {oa * (C)ua.x, oa * (C)ua.y, oa * (C)ua.z, oa * (C)ua.w};
-      const C wb[4] = {ob * (C)ub.x, ob * (C)ub.y, ob * (C)ub.z, ob * (C)ub.w};
-#pragma unroll
-      for (int k = 0; k < VB; ++k)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[8 * k + 2 * i] += wa[i] * (C)ta[k].x;
-          acc[8 * k + 2 * i + 1] += wa[i] * (C)ta[k].y;
-        }
-#pragma unroll
-      for (int k = 0; k < VB; ++k)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[8 * k + 2 * i] += wb[i] * (C)tb[k].x;
-          acc[8 * k + 2 * i + 1] += wb[i] * (C)tb[k].y;
-        }
-    }
-    C t = 0;
-    if (lo < hi) t = wave_sums<8 * VB, C>(acc, lane);   // uniform over the workgroup
-    if ((lane & (64 / (8 * VB) - 1)) == 0) red[wv][sg][lane / (64 / (8 * VB))] = t;
-  }
-  __syncthreads();
-  // wave k: the 12 coefficients of vector v0 + k
-  const int k = __builtin_amdgcn_readfirstlane(wv), v = v0 + k;
-  if (k >= VB || v >= a.nv || lane >= 12) return;
-  const int w = lane >> 2, i = lane & 3, q = 8 * k + 2 * i;
-  const double2 d0 = cf.c0[v], dp = cf.cp[v], dm = cf.cm[v];
-  cplx<C> s = mkc<C>(0, 0);
-#pragma unroll
-  for (int w2 = 0; w2 < 3; ++w2) {
-    const int d = w2 - w;   // cell shift of the source relative to the entry
-    if (d > 1 || d < -1) continue;
-    const cplx<C> cd = mkc<C>((C)(d == 0 ? d0.x : d == 1 ? dp.x : dm.x), (C)(d == 0 ? d0.y : d == 1 ? dp.y : dm.y));
-    const cplx<C> g = mkc<C>(red[0][w2][q] + red[1][w2][q] + red[2][w2][q] + red[3][w2][q],
-                             red[0][w2][q + 1] + red[1][w2][q + 1] + red[2][w2][q + 1] + red[3][w2][q + 1]);
-    s = cfma<C>(s, cd, g);
-  }
-  s = cscale<C>(s, (C)a.coeff[4 * atom + i]);
-  const int vg = v / AP_VG, ncol = 2 * min(AP_VG, a.nv - vg * AP_VG);
-  R* dst = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + ((int64_t)(atom * 3 + w) * 4 + i) * ncol +
-           2 * (v - vg * AP_VG);
-  dst[0] = (R)s.x;
-  dst[1] = (R)s.y;
-}
-
 // ------------------------------------------------------------------ ket
 template <typename R>
 struct ApKet {
@@ -441,22 +458,54 @@ static void ap_shape(const cbs_system* s, int32_t nv, size_t elem, int32_t* ty, 
   }
 }
 
-template <typename R, typename C, int P, bool PIPE>
-static void ap_local_pp(const ApLocal<R>& a, const ApCoef& cf, dim3 grid, dim3 blk, size_t smem, hipStream_t st) {
+// Vectors per bra item, and whether the bra shares the local part's launch: neither reads what the
+// other writes, so up to 576 items of two vectors the chip has room for both at once and a launch is
+// saved (48x48x32, 96 atoms, 8 complex128 vectors, whole call: 57 us, apart 64; 45x37x29, 60 atoms,
+// 8: 42, apart 51; 32x32x24, 40 atoms, 24: 46, apart 57).  Past that the table reads of four
+// vectors an item count for more: in complex64 together up to 768 items (48x48x32, 32 vectors: 78,
+// apart 83; 64x64x40, 170 atoms, 24: 118, apart 115), in complex128 in a launch of its own, where
+// the bra keeps L2 for its gathers (48x48x32, 32 vectors: 113, together 125).
+static int bra_shape(int32_t n_atoms, int32_t nv, bool f32, bool* together) {
+  *together = true;
+  if ((int64_t)n_atoms * ((nv + 1) / 2) <= 576) return 2;
+  *together = f32 && (int64_t)n_atoms * ((nv + 3) / 4) <= 768;
+  return 4;
+}
+
+template <typename R>
+struct ApGrid {
+  int32_t grid, nthr, vb;   // vb: vectors per bra item, 0: no bra in this launch
+  bool pipe;
+  size_t smem;
+};
+
+template <typename R, typename C, int P, bool PIPE, int VB>
+static void ap_local_pv(const ApLocal<R>& a, const ApBra<R>& b, const ApCoef& cf, const ApGrid<R>& g, hipStream_t st) {
   if constexpr (sizeof(R) == 8) {   // only the bands' filter (complex128) adds a second block
     if (a.prev != nullptr) {
-      hipLaunchKernelGGL((k_ap_local<R, C, P, PIPE, true>), grid, blk, smem, st, a, cf);
+      hipLaunchKernelGGL((k_ap_local<R, C, P, PIPE, true, VB>), dim3(g.grid), dim3(g.nthr), g.smem, st, a, b, cf);
       return;
     }
   }
-  hipLaunchKernelGGL((k_ap_local<R, C, P, PIPE, false>), grid, blk, smem, st, a, cf);
+  hipLaunchKernelGGL((k_ap_local<R, C, P, PIPE, false, VB>), dim3(g.grid), dim3(g.nthr), g.smem, st, a, b, cf);
+}
+
+template <typename R, typename C, int P, bool PIPE>
+static void ap_local_pp(const ApLocal<R>& a, const ApBra<R>& b, const ApCoef& cf, const ApGrid<R>& g, hipStream_t st) {
+  if constexpr (sizeof(R) == 4) {
+    if (g.vb == 4) {
+      ap_local_pv<R, C, P, PIPE, 4>(a, b, cf, g, st);
+      return;
+    }
+  }
+  if (g.vb == 2) ap_local_pv<R, C, P, PIPE, 2>(a, b, cf, g, st);
+  else ap_local_pv<R, C, P, PIPE, 0>(a, b, cf, g, st);
 }
 
 template <typename R, typename C, int P>
-static void ap_local_p(const ApLocal<R>& a, const ApCoef& cf, bool pipe, int nthr, size_t smem, hipStream_t st) {
-  const dim3 grid((a.nlogical + 7) / 8 * 8), blk(nthr);
-  if (pipe) ap_local_pp<R, C, P, true>(a, cf, grid, blk, smem, st);
-  else ap_local_pp<R, C, P, false>(a, cf, grid, blk, smem, st);
+static void ap_local_p(const ApLocal<R>& a, const ApBra<R>& b, const ApCoef& cf, const ApGrid<R>& g, hipStream_t st) {
+  if (g.pipe) ap_local_pp<R, C, P, true>(a, b, cf, g, st);
+  else ap_local_pp<R, C, P, false>(a, b, cf, g, st);
 }
 
 template <typename R, typename C>
@@ -464,25 +513,6 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
                          R* kt, const cplx<R>* prev, double beta, hipStream_t st) {
   const Projector& pr = s->proj;
   const bool f64 = std::is_same<R, double>::value;
-  if (pr.n_atoms > 0) {
-    ApBra<R> b;
-    b.n_atoms = pr.n_atoms;
-    b.nv = nv;
-    b.N = s->N;
-    b.seg = pr.seg;
-    b.idx = pr.ball_idx;
-    b.u = f64 ? (const R*)pr.ball_u64 : (const R*)pr.ball_u32;
-    b.coeff = f64 ? (const R*)pr.coeff64 : (const R*)pr.coeff32;
-    b.x = x;
-    b.kt = kt;
-    const int vb = nv >= 4 ? 4 : 1;
-    b.nvb = (nv + vb - 1) / vb;
-    b.nlogical = b.nvb * pr.n_atoms;
-    const int grid = (b.nlogical + 7) / 8 * 8;
-    if (vb == 4) hipLaunchKernelGGL((k_ap_bra<R, C, 4>), dim3(grid), dim3(256), 0, st, b, cf);
-    else hipLaunchKernelGGL((k_ap_bra<R, C, 1>), dim3(grid), dim3(256), 0, st, b, cf);
-    CBS_HIP(hipGetLastError());
-  }
   ApLocal<R> a;
   int32_t ty = 1, nseg = 1;
   ap_shape(s, nv, sizeof(cplx<R>), &ty, &nseg);
@@ -509,13 +539,47 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
   a.x = x;
   a.prev = prev;
   a.y = y;
-  const int nthr = (s->nx * ty + 63) / 64 * 64;
-  const bool pipe = (ty + 2 * s->p) * s->nx <= 2 * nthr;
+  ApGrid<R> g;
+  g.nthr = (s->nx * ty + 63) / 64 * 64;
+  g.smem = a.nbuf * one;
+  g.vb = 0;
+  ApBra<R> b{};
+  if (pr.n_atoms > 0) {
+    bool together = false;
+    const int vb = bra_shape(pr.n_atoms, nv, !f64, &together);
+    b.n_atoms = pr.n_atoms;
+    b.nv = nv;
+    b.N = s->N;
+    b.seg = pr.seg;
+    b.idx = pr.ball_idx;
+    b.u = f64 ? (const R*)pr.ball_u64 : (const R*)pr.ball_u32;
+    b.coeff = f64 ? (const R*)pr.coeff64 : (const R*)pr.coeff32;
+    b.x = x;
+    b.kt = kt;
+    b.nvb = (nv + vb - 1) / vb;
+    if (together) {
+      g.vb = vb;
+      g.nthr = std::max(g.nthr, 256);
+    }
+    const int items = b.nvb * pr.n_atoms;
+    b.nsub = together ? std::max(1, std::min(g.nthr, items) / 256) : 1;   // spread over the CUs first
+    const size_t red = (size_t)b.nsub * 4 * 3 * 8 * vb * sizeof(C);
+    b.nlogical = (items + b.nsub - 1) / b.nsub;
+    b.grid = (b.nlogical + 7) / 8 * 8;
+    if (together) {
+      g.smem = std::max(g.smem, red);
+    } else {
+      hipLaunchKernelGGL((k_ap_bra<R, C, 4>), dim3(b.grid), dim3(256), 0, st, b, cf);
+      CBS_HIP(hipGetLastError());
+    }
+  }
+  g.grid = (g.vb > 0 ? b.grid : 0) + (a.nlogical + 7) / 8 * 8;
+  g.pipe = (ty + 2 * s->p) * s->nx <= 2 * g.nthr;
   switch (s->p) {
-    case 1: ap_local_p<R, C, 1>(a, cf, pipe, nthr, a.nbuf * one, st); break;
-    case 2: ap_local_p<R, C, 2>(a, cf, pipe, nthr, a.nbuf * one, st); break;
-    case 3: ap_local_p<R, C, 3>(a, cf, pipe, nthr, a.nbuf * one, st); break;
-    case 4: ap_local_p<R, C, 4>(a, cf, pipe, nthr, a.nbuf * one, st); break;
+    case 1: ap_local_p<R, C, 1>(a, b, cf, g, st); break;
+    case 2: ap_local_p<R, C, 2>(a, b, cf, g, st); break;
+    case 3: ap_local_p<R, C, 3>(a, b, cf, g, st); break;
+    case 4: ap_local_p<R, C, 4>(a, b, cf, g, st); break;
     default: set_error("unsupported finite-difference half-width %d", s->p); return CBS_EINVAL;
   }
   CBS_HIP(hipGetLastError());
