@@ -34,9 +34,20 @@ __global__ void k_cheb(int64_t total, const c64* HY, const c64* Y, c64* out, dou
   }
 }
 
-// A' = G + s I for the Hermitian G (m x m, column-major), symmetrised
-__global__ void k_shift_herm(int32_t m, const c64* G, double s, c64* A) {
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < m * m; t += gridDim.x * blockDim.x) {
+// A' = G + s I for the Hermitian G (m x m, column-major), symmetrised, with s = |G|_F + 1 above its
+// spectral radius; *s_out = s.  One workgroup.
+__global__ void __launch_bounds__(1024) k_shift_herm(int32_t m, const c64* G, double* s_out, c64* A) {
+  __shared__ double red[16];
+  double f = 0;
+  for (int t = threadIdx.x; t < m * m; t += 1024) f += G[t].x * G[t].x + G[t].y * G[t].y;
+  f = wsum<double>(f);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = f;
+  __syncthreads();
+  double fro = 0;
+  for (int w = 0; w < 16; ++w) fro += red[w];
+  const double s = sqrt(fro) + 1.0;
+  if (threadIdx.x == 0) *s_out = s;
+  for (int t = threadIdx.x; t < m * m; t += 1024) {
     const int i = t % m, j = t / m;
     const c64 a = G[i + (int64_t)j * m], b = G[j + (int64_t)i * m];
     c64 v = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
@@ -65,8 +76,9 @@ __global__ void __launch_bounds__(256) k_ritz_res(int64_t N, const c64* HX, cons
 
 // theta (ascending) and the eigenvector matrix U (columns in that order) from the SVD of
 // G + s I: sigma descending with perm, so rank r from the bottom is eigenvalue r
-__global__ void k_ritz_order(int32_t m, const double* sigma, const int32_t* perm, const c64* W, double s,
-                             double* theta, c64* U) {
+__global__ void k_ritz_order(int32_t m, const double* sigma, const int32_t* perm, const c64* W,
+                             const double* shift, double* theta, c64* U) {
+  const double s = *shift;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < m * m; t += gridDim.x * blockDim.x) {
     const int i = t % m, r = t / m;   // row, ascending rank
     const int src = perm[m - 1 - r];
@@ -118,54 +130,111 @@ static double tridiag_max(const std::vector<double>& a, const std::vector<double
   return hi;
 }
 
+// Lanczos steps on the device: a dot or a norm leaves one partial sum per workgroup, which every
+// workgroup of the next kernel adds up for itself, so that a step needs no round trip to the host.
+__device__ double lz_block_sum(double v, double* sh) {
+  v = wsum<double>(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  const double r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  __syncthreads();
+  return r;
+}
+
+// w = a fixed, non-smooth start vector, with the partial sums of its square
+__global__ void __launch_bounds__(256) k_lz_start(int64_t N, c64* w, double* part) {
+  __shared__ double sh[4];
+  double s = 0;
+  for (int64_t n = blockIdx.x * (int64_t)256 + threadIdx.x; n < N; n += (int64_t)gridDim.x * 256) {
+    const double t = sin(0.7 * (double)n + 0.3) + 0.5 * cos(1.3 * (double)n);
+    w[n] = make_double2(t, 0.25 * t);
+    s += t * t * 1.0625;
+  }
+  s = lz_block_sum(s, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// v = w / beta, beta = |w| from its partial sums
+__global__ void __launch_bounds__(256) k_lz_norm(int64_t N, const c64* w, const double* part, c64* v, double* beta) {
+  __shared__ double sh[4];
+  const double b = sqrt(lz_block_sum(threadIdx.x < gridDim.x ? part[threadIdx.x] : 0.0, sh));
+  if (blockIdx.x == 0 && threadIdx.x == 0) *beta = b;
+  for (int64_t n = blockIdx.x * (int64_t)256 + threadIdx.x; n < N; n += (int64_t)gridDim.x * 256)
+    v[n] = make_double2(w[n].x / b, w[n].y / b);
+}
+
+// partial sums of alpha = Re v^H w
+__global__ void __launch_bounds__(256) k_lz_dot(int64_t N, const c64* v, const c64* w, double* part) {
+  __shared__ double sh[4];
+  double s = 0;
+  for (int64_t n = blockIdx.x * (int64_t)256 + threadIdx.x; n < N; n += (int64_t)gridDim.x * 256)
+    s += v[n].x * w[n].x + v[n].y * w[n].y;
+  s = lz_block_sum(s, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// w -= alpha v + beta vp (vp NULL in the first step), with the partial sums of |w|^2
+__global__ void __launch_bounds__(256) k_lz_update(int64_t N, const c64* v, const c64* vp, const double* beta, c64* w,
+                                                   const double* part_a, double* part_b, double* alpha) {
+  __shared__ double sh[4];
+  const double al = lz_block_sum(threadIdx.x < gridDim.x ? part_a[threadIdx.x] : 0.0, sh);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = al;
+  const double be = (vp != nullptr) ? *beta : 0.0;
+  double s = 0;
+  for (int64_t n = blockIdx.x * (int64_t)256 + threadIdx.x; n < N; n += (int64_t)gridDim.x * 256) {
+    const c64 p = (vp != nullptr) ? vp[n] : make_double2(0, 0);
+    const c64 x = make_double2(w[n].x - (al * v[n].x + be * p.x), w[n].y - (al * v[n].y + be * p.y));
+    w[n] = x;
+    s += x.x * x.x + x.y * x.y;
+  }
+  s = lz_block_sum(s, sh);
+  if (threadIdx.x == 0) part_b[blockIdx.x] = s;
+}
+
 // Upper bound of the spectrum of the Hermitian H(k) (phase ph = e^{ika}): k steps of
 // Lanczos from a fixed start vector give the largest Ritz value theta; theta + |b_k| (the
 // last off-diagonal) bounds the spectrum from above for a Lanczos run that has captured
 // the top of it; 10% of the spread is added as margin.
 static int32_t spectrum_upper(cbs_system* s, c64 ph, hipStream_t st, double* upper) {
   const int64_t N = s->N;
-  const int steps = 16;
-  c64 *dv = nullptr, *dw = nullptr;
-  CBS_TRY(ws_get(s->ws, "bd.lz_v", (size_t)N, &dv));
-  CBS_TRY(ws_get(s->ws, "bd.lz_w", (size_t)N, &dw));
-  std::vector<c64> v(N), vp(N, make_double2(0, 0)), w(N);
-  double nrm = 0;
-  for (int64_t n = 0; n < N; ++n) {
-    // a fixed, non-smooth start vector
-    const double t = std::sin(0.7 * (double)n + 0.3) + 0.5 * std::cos(1.3 * (double)n);
-    v[n] = make_double2(t, 0.25 * t);
-    nrm += t * t * 1.0625;
-  }
-  nrm = std::sqrt(nrm);
-  for (auto& x : v) x = make_double2(x.x / nrm, x.y / nrm);
-  std::vector<double> al, be;
-  double beta = 0;
+  constexpr int steps = 16;
+  const int G = (int)std::min<int64_t>(256, (N + 1023) / 1024);   // a partial sum per thread of a workgroup
+  c64 *v = nullptr, *vp = nullptr, *w = nullptr;
+  double* sc = nullptr;
+  CBS_TRY(ws_get(s->ws, "bd.lz_v", (size_t)N, &v));
+  CBS_TRY(ws_get(s->ws, "bd.lz_p", (size_t)N, &vp));
+  CBS_TRY(ws_get(s->ws, "bd.lz_w", (size_t)N, &w));
+  CBS_TRY(ws_get(s->ws, "bd.lz_sc", (size_t)2 * G + 2 * steps + 1, &sc));
+  double *part_a = sc, *part_b = sc + G, *alpha = sc + 2 * G, *beta = alpha + steps;   // beta[0]: the start's norm
+  hipLaunchKernelGGL(k_lz_start, dim3(G), dim3(256), 0, st, N, w, part_b);
+  hipLaunchKernelGGL(k_lz_norm, dim3(G), dim3(256), 0, st, N, (const c64*)w, (const double*)part_b, v, beta);
+  CBS_HIP(hipGetLastError());
   const c64 one = make_double2(1, 0), phc = make_double2(ph.x, -ph.y);
   for (int k = 0; k < steps; ++k) {
-    CBS_HIP(hipMemcpyAsync(dv, v.data(), N * sizeof(c64), hipMemcpyHostToDevice, st));
-    CBS_TRY(apply_parts_dev(s, 0.0, 1, &one, &ph, &phc, dv, dw, st));
-    CBS_HIP(hipMemcpyAsync(w.data(), dw, N * sizeof(c64), hipMemcpyDeviceToHost, st));
-    CBS_HIP(hipStreamSynchronize(st));
-    double alpha = 0;
-    for (int64_t n = 0; n < N; ++n) alpha += v[n].x * w[n].x + v[n].y * w[n].y;   // Re v^H w
-    double bn = 0;
-    for (int64_t n = 0; n < N; ++n) {
-      w[n].x -= alpha * v[n].x + beta * vp[n].x;
-      w[n].y -= alpha * v[n].y + beta * vp[n].y;
-      bn += w[n].x * w[n].x + w[n].y * w[n].y;
-    }
-    al.push_back(alpha);
-    beta = std::sqrt(bn);
-    if (k + 1 < steps) be.push_back(beta);
-    if (!(beta > 0)) break;
-    vp = v;
-    for (int64_t n = 0; n < N; ++n) v[n] = make_double2(w[n].x / beta, w[n].y / beta);
+    CBS_TRY(apply_parts_dev(s, 0.0, 1, &one, &ph, &phc, v, w, st));
+    hipLaunchKernelGGL(k_lz_dot, dim3(G), dim3(256), 0, st, N, (const c64*)v, (const c64*)w, part_a);
+    hipLaunchKernelGGL(k_lz_update, dim3(G), dim3(256), 0, st, N, (const c64*)v, (const c64*)(k > 0 ? vp : nullptr),
+                       (const double*)(beta + k), w, (const double*)part_a, part_b, alpha + k);
+    hipLaunchKernelGGL(k_lz_norm, dim3(G), dim3(256), 0, st, N, (const c64*)w, (const double*)part_b, vp,
+                       beta + k + 1);
+    CBS_HIP(hipGetLastError());
+    std::swap(v, vp);
   }
-  be.resize(al.size() > 0 ? al.size() - 1 : 0);
+  std::vector<double> h(2 * steps + 1), al, be;
+  CBS_HIP(hipMemcpyAsync(h.data(), alpha, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+  CBS_HIP(hipStreamSynchronize(st));
+  double last = 0;
+  for (int k = 0; k < steps; ++k) {   // a beta of zero (an invariant subspace) ends the recurrence
+    al.push_back(h[k]);
+    last = h[steps + 1 + k];
+    if (!(last > 0)) break;
+    be.push_back(last);
+  }
+  be.resize(al.size() - 1);
   const double tmax = tridiag_max(al, be);
   double tmin = tmax;
   for (double a : al) tmin = std::min(tmin, a);
-  *upper = tmax + std::fabs(beta) + 0.1 * (tmax - tmin);
+  *upper = tmax + std::fabs(last) + 0.1 * (tmax - tmin);
   return CBS_OK;
 }
 
@@ -211,8 +280,9 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
   CBS_TRY(ws_get(ws, "bd.Ri", (size_t)m * m, &Ri));
   CBS_TRY(ws_get(ws, "bd.U", (size_t)m * m, &U));
   CBS_TRY(ws_get(ws, "bd.sig", 1024, &sig));
-  CBS_TRY(ws_get(ws, "bd.theta", (size_t)m, &theta));
-  CBS_TRY(ws_get(ws, "bd.res", (size_t)m, &res));
+  CBS_TRY(ws_get(ws, "bd.theta", (size_t)2 * m + 1, &theta));   // with the residuals, and s of G + s I
+  res = theta + m;
+  double* shift = theta + 2 * m;
   CBS_TRY(ws_get(ws, "bd.perm", 512, &perm));
   CBS_TRY(ws_get(ws, "bd.info", 4, &info));
   // lowest local potential (below it lies no band of the local part)
@@ -235,15 +305,9 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
       c64* b = dst;
       for (int pass = 0; pass < 3; ++pass) {
         CBS_TRY(gram(s, N, m, a, N, m, a, N, G, m, st));
-        double shift = 0;
-        if (pass == 0) {
-          std::vector<c64> hg((size_t)m * m);
-          CBS_HIP(hipMemcpyAsync(hg.data(), G, hg.size() * sizeof(c64), hipMemcpyDeviceToHost, st));
-          CBS_HIP(hipStreamSynchronize(st));
-          double tr = 0;
-          for (int i = 0; i < m; ++i) tr += hg[(size_t)i * m + i].x;
-          shift = 11.0 * ((double)N * m + (double)m * (m + 1)) * 1.1102230246251565e-16 * tr;
-        }
+        // 11 (N m + m (m + 1)) u of the trace
+        const double shift =
+            pass == 0 ? 11.0 * ((double)N * m + (double)m * (m + 1)) * 1.1102230246251565e-16 : 0.0;
         CBS_TRY(chol_inv(m, G, m, shift, Ri, info, st));
         CBS_TRY(tall_gemm(N, m, m, a, N, Ri, m, b, N, st));
         std::swap(a, b);
@@ -255,17 +319,11 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
     auto rayleigh_ritz = [&]() -> int32_t {
       CBS_TRY(applyH(X, HY));
       CBS_TRY(gram(s, N, m, X, N, m, HY, N, G, m, st));
-      std::vector<c64> hg((size_t)m * m);
-      CBS_HIP(hipMemcpyAsync(hg.data(), G, hg.size() * sizeof(c64), hipMemcpyDeviceToHost, st));
-      CBS_HIP(hipStreamSynchronize(st));
-      double fro = 0;
-      for (auto& v : hg) fro += v.x * v.x + v.y * v.y;
-      const double shift = std::sqrt(fro) + 1.0;
-      hipLaunchKernelGGL(k_shift_herm, dim3(grid_of((int64_t)m * m)), dim3(256), 0, st, m, (const c64*)G, shift, A);
+      hipLaunchKernelGGL(k_shift_herm, dim3(1), dim3(1024), 0, st, m, (const c64*)G, shift, A);
       CBS_HIP(hipGetLastError());
       CBS_TRY(svd_right(s, m, A, m, W, m, sig, perm, true, st));
       hipLaunchKernelGGL(k_ritz_order, dim3(grid_of((int64_t)m * m)), dim3(256), 0, st, m, (const double*)sig,
-                         (const int32_t*)perm, (const c64*)W, shift, theta, U);
+                         (const int32_t*)perm, (const c64*)W, (const double*)shift, theta, U);
       CBS_HIP(hipGetLastError());
       CBS_TRY(tall_gemm(N, m, m, X, N, U, m, Z, N, st));
       std::swap(X, Z);
@@ -279,15 +337,15 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
     CBS_HIP(hipGetLastError());
     CBS_TRY(orthonormalise(Y, X));
     CBS_TRY(rayleigh_ritz());
-    std::vector<double> hth(m), hres(m);
+    std::vector<double> hth(2 * (size_t)m);   // theta, then the residuals
+    const double* hres = hth.data() + m;
     int it = 0;
     bool done = false;
     for (; it < max_iter && !done; ++it) {
-      CBS_HIP(hipMemcpyAsync(hth.data(), theta, m * sizeof(double), hipMemcpyDeviceToHost, st));
       hipLaunchKernelGGL(k_ritz_res, dim3(m), dim3(256), 0, st, N, (const c64*)HY, (const c64*)X,
                          (const double*)theta, res);
       CBS_HIP(hipGetLastError());
-      CBS_HIP(hipMemcpyAsync(hres.data(), res, m * sizeof(double), hipMemcpyDeviceToHost, st));
+      CBS_HIP(hipMemcpyAsync(hth.data(), theta, 2 * m * sizeof(double), hipMemcpyDeviceToHost, st));
       CBS_HIP(hipStreamSynchronize(st));
       done = true;
       for (int b = 0; b < n_bands; ++b) done = done && hres[b] <= tol * (std::fabs(hth[b]) + 1.0);
@@ -335,10 +393,9 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
     }
     int32_t hinfo[4];
     CBS_HIP(hipMemcpyAsync(hinfo, info, sizeof(hinfo), hipMemcpyDeviceToHost, st));
-    CBS_HIP(hipMemcpyAsync(hth.data(), theta, m * sizeof(double), hipMemcpyDeviceToHost, st));
     hipLaunchKernelGGL(k_ritz_res, dim3(m), dim3(256), 0, st, N, (const c64*)HY, (const c64*)X,
                        (const double*)theta, res);
-    CBS_HIP(hipMemcpyAsync(hres.data(), res, m * sizeof(double), hipMemcpyDeviceToHost, st));
+    CBS_HIP(hipMemcpyAsync(hth.data(), theta, 2 * m * sizeof(double), hipMemcpyDeviceToHost, st));
     CBS_HIP(hipStreamSynchronize(st));
     if (hinfo[0] != 0) {
       set_error("cbs_bands: Cholesky QR of the filtered block failed at k[%d]", ik);

@@ -121,15 +121,31 @@ __global__ void __launch_bounds__(256) k_gram_plain(int64_t N, int32_t na, int32
   o[1] = acc.y;
 }
 
-__global__ void k_gram_reduce(int32_t na, int32_t nb, int32_t nsplit, const double* part, c64* C, int64_t ldc) {
+// The slices' sums in slice order; eight slices are requested at a time (36 slices, 16 x 16: 3.7 us,
+// 9.4 one after the other).
+__global__ void __launch_bounds__(64) k_gram_reduce(int32_t na, int32_t nb, int32_t nsplit, const double* part,
+                                                    c64* C, int64_t ldc) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= na * nb) return;
   const int i = t / nb, j = t - i * nb;
+  const c64* p = reinterpret_cast<const c64*>(part) + t;
+  const int64_t stride = (int64_t)na * nb;
   double re = 0, im = 0;
-  for (int s = 0; s < nsplit; ++s) {
-    const double* o = part + (((int64_t)s * na + i) * nb + j) * 2;
-    re += o[0];
-    im += o[1];
+  int s = 0;
+  for (; s + 8 <= nsplit; s += 8) {
+    c64 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = p[(s + k) * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      re += v[k].x;
+      im += v[k].y;
+    }
+  }
+  for (; s < nsplit; ++s) {
+    const c64 v = p[s * stride];
+    re += v.x;
+    im += v.y;
   }
   C[i + (int64_t)j * ldc] = make_double2(re, im);
 }
@@ -156,49 +172,73 @@ int32_t gram(cbs_system* s, int64_t N, int32_t na, const c64* A, int64_t lda, in
     hipLaunchKernelGGL(k_gram_mfma, dim3(tiles * nsplit), dim3(256), 0, st, N, na, nb, A, lda, B, ldb, tiles_b,
                        nsplit, span, part);
   CBS_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_gram_reduce, dim3((na * nb + 255) / 256), dim3(256), 0, st, na, nb, nsplit,
+  hipLaunchKernelGGL(k_gram_reduce, dim3((na * nb + 63) / 64), dim3(64), 0, st, na, nb, nsplit,
                      (const double*)part, C, ldc);
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }
 
 // ------------------------------------------------------------------ tall-skinny product
-// out[c][n] = sum_k A[k][n] W[k + c*ldw] for c < nc; W staged in LDS per column tile.
-constexpr int TG_C = 16;
-__global__ void __launch_bounds__(256) k_tall_gemm(int64_t N, int32_t K, int32_t nc, const c64* A, int64_t lda,
-                                                   const c64* W, int32_t ldw, c64* out, int64_t ldo) {
-  extern __shared__ c64 w_s[];   // [K][TG_C]
-  const int c0 = blockIdx.y * TG_C;
-  const int ncl = std::min(TG_C, nc - c0);
-  for (int t = threadIdx.x; t < K * TG_C; t += blockDim.x) {
-    const int k = t / TG_C, c = t - k * TG_C;
+// out[c][n] = sum_k A[k][n] W[k + c*ldw] for c < nc; W staged in LDS per tile of TC columns.
+// KU rows of A are requested at a time.  A product of many outputs takes 16 columns a thread, so that
+// A is read seldom; one of few, whose workgroups would not fill the chip and whose time is the chain
+// of loads over k, 4 columns a thread in workgroups of one wave.  K = 32, us with 16 and with 4:
+// N nc = 147 000 (9216 x 16) 22.1 and 7.6, 768 000 (24000 x 32) 24.9 and 20.4, 1 180 000 (73728 x 16)
+// 27.4 and 15.4, 2 360 000 (73728 x 32) 31.3 and 26.6, but 103.7 and 139.4 at K = 128, and
+// 4 700 000 (294912 x 16) 52 and 101.
+template <int TC, int KU>
+__global__ void __launch_bounds__(TC == 16 ? 256 : 64) k_tall_gemm(int64_t N, int32_t K, int32_t nc, const c64* A,
+                                                                   int64_t lda, const c64* W, int32_t ldw, c64* out,
+                                                                   int64_t ldo) {
+  extern __shared__ c64 w_s[];   // [K][TC]
+  const int c0 = blockIdx.y * TC;
+  const int ncl = std::min(TC, nc - c0);
+  for (int t = threadIdx.x; t < K * TC; t += blockDim.x) {
+    const int k = t / TC, c = t - k * TC;
     w_s[t] = (c < ncl) ? W[k + (int64_t)(c0 + c) * ldw] : make_double2(0, 0);
   }
   __syncthreads();
   for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < N; n += (int64_t)gridDim.x * blockDim.x) {
-    c64 acc[TG_C];
+    c64 acc[TC];
 #pragma unroll
-    for (int c = 0; c < TG_C; ++c) acc[c] = make_double2(0, 0);
-    for (int k = 0; k < K; ++k) {
+    for (int c = 0; c < TC; ++c) acc[c] = make_double2(0, 0);
+    int k = 0;
+    for (; k + KU <= K; k += KU) {
+      c64 a[KU];
+#pragma unroll
+      for (int u = 0; u < KU; ++u) a[u] = A[(int64_t)(k + u) * lda + n];
+#pragma unroll
+      for (int u = 0; u < KU; ++u)
+#pragma unroll
+        for (int c = 0; c < TC; ++c) acc[c] = zadd(acc[c], zmul(a[u], w_s[(k + u) * TC + c]));
+    }
+    for (; k < K; ++k) {
       const c64 a = A[(int64_t)k * lda + n];
 #pragma unroll
-      for (int c = 0; c < TG_C; ++c) acc[c] = zadd(acc[c], zmul(a, w_s[k * TG_C + c]));
+      for (int c = 0; c < TC; ++c) acc[c] = zadd(acc[c], zmul(a, w_s[k * TC + c]));
     }
-    for (int c = 0; c < ncl; ++c) out[(int64_t)(c0 + c) * ldo + n] = acc[c];
+#pragma unroll
+    for (int c = 0; c < TC; ++c)
+      if (c < ncl) out[(int64_t)(c0 + c) * ldo + n] = acc[c];
   }
 }
 
 int32_t tall_gemm(int64_t N, int32_t K, int32_t nc, const c64* A, int64_t lda, const c64* W, int32_t ldw, c64* out,
                   int64_t ldo, hipStream_t st) {
   if (nc <= 0 || N <= 0) return CBS_OK;
-  const size_t smem = (size_t)K * TG_C * sizeof(c64);
-  if (smem > 64 * 1024) {
+  if ((size_t)K * 16 * sizeof(c64) > 64 * 1024) {
     set_error("tall_gemm: inner dimension %d too large", K);
     return CBS_EINVAL;
   }
-  const int gx = (int)std::min<int64_t>((N + 255) / 256, 2048);
-  hipLaunchKernelGGL(k_tall_gemm, dim3(gx, (nc + TG_C - 1) / TG_C), dim3(256), smem, st, N, K, nc, A, lda, W, ldw,
-                     out, ldo);
+  if (N * nc <= 1250000) {
+    const int gx = (int)((N + 63) / 64);
+    hipLaunchKernelGGL((k_tall_gemm<4, 8>), dim3(gx, (nc + 3) / 4), dim3(64), (size_t)K * 4 * sizeof(c64), st, N, K,
+                       nc, A, lda, W, ldw, out, ldo);
+  } else {
+    const int gx = (int)std::min<int64_t>((N + 255) / 256, 2048);
+    hipLaunchKernelGGL((k_tall_gemm<16, 2>), dim3(gx, (nc + 15) / 16), dim3(256), (size_t)K * 16 * sizeof(c64), st,
+                       N, K, nc, A, lda, W, ldw, out, ldo);
+  }
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }
@@ -1556,11 +1596,15 @@ int32_t lu_solve(int32_t n, c64* A, int32_t lda, c64* B, int32_t ldb, int32_t nr
 }
 
 // ------------------------------------------------------------------ Cholesky + inverse
-// G = R^H R (upper R), Rinv = R^{-1} (upper); G destroyed.  A shift is added to the
-// diagonal first (shifted Cholesky QR).
+// G = R^H R (upper R), Rinv = R^{-1} (upper); G destroyed.  shift times the trace is added to
+// the diagonal first (shifted Cholesky QR).
 __global__ void __launch_bounds__(SWG) k_chol_inv(int32_t n, c64* G, int32_t ldg, double shift, c64* Rinv,
                                                    int32_t* info) {
   const int tid = threadIdx.x;
+  double tr = 0;
+  for (int i = 0; i < n && shift != 0; ++i) tr += G[i + (int64_t)i * ldg].x;
+  shift *= tr;
+  __syncthreads();
   for (int i = tid; i < n; i += SWG) G[i + (int64_t)i * ldg].x += shift;
   __syncthreads();
   // right-looking: for k, R[k][k] = sqrt(G[k][k]); R[k][j] = G[k][j]/R[k][k]; G[i][j] -= conj(R[k][i]) R[k][j]
@@ -1592,9 +1636,71 @@ __global__ void __launch_bounds__(SWG) k_chol_inv(int32_t n, c64* G, int32_t ldg
   }
 }
 
+// The same for n up to CI_NMAX by one elimination in LDS, one barrier a row: G = L D L^H with unit
+// lower L; the row operations that clear G below the diagonal turn the identity into L^-1, and
+// R^-1 = (D^{-1/2} L^-1)^H.  The upper triangle of M holds what is left of G, the strict lower one
+// L^-1.  A row's chain (pivot, reciprocal, one update, a barrier) bounds it: 9.7 us for n = 16 (the
+// kernel above takes 29), 24 for 32, 57 for 64, 157 for 96 (97 above: 936).
+constexpr int CI_NMAX = 96;
+template <int TX>
+__global__ void __launch_bounds__(TX == 32 ? 256 : 1024) k_chol_inv_lds(int32_t n, const c64* G, int32_t ldg,
+                                                                        double shift, c64* Rinv, int32_t* info) {
+  extern __shared__ __align__(16) unsigned char ci_smem[];
+  c64* M = reinterpret_cast<c64*>(ci_smem);   // [n][n]
+  const int tx = threadIdx.x % TX, ty = threadIdx.x / TX, TY = blockDim.x / TX;
+  for (int t = threadIdx.x; t < n * n; t += blockDim.x) {
+    const int j = t / n, i = t - j * n;
+    const c64 v = G[i + (int64_t)j * ldg];
+    M[i * n + j] = (i <= j) ? v : make_double2(0, 0);
+  }
+  __syncthreads();
+  if (shift != 0) {
+    double tr = 0;
+    for (int i = 0; i < n; ++i) tr += M[i * n + i].x;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) M[i * n + i].x += shift * tr;
+    __syncthreads();
+  }
+  for (int k = 0; k < n; ++k) {
+    const c64* row = M + k * n;
+    const double d = row[k].x;
+    const double inv = (d > 0) ? 1.0 / d : 0.0;
+    if (threadIdx.x == 0 && !(d > 0)) info[0] = 3;
+    for (int i = k + 1 + ty; i < n; i += TY) {
+      const c64 l = make_double2(row[i].x * inv, -row[i].y * inv);
+      for (int j = tx; j < n; j += TX) {
+        if (j > k && j < i) continue;
+        c64* m = M + i * n + j;
+        *m = (j == k) ? make_double2(-l.x, -l.y) : zsub(*m, zmul(l, row[j]));
+      }
+    }
+    __syncthreads();
+  }
+  for (int t = threadIdx.x; t < n * n; t += blockDim.x) {
+    const int c = t / n, i = t - c * n;   // R^-1[i][c], i <= c
+    const double d = M[c * n + c].x;
+    const double f = (d > 0) ? 1.0 / sqrt(d) : 0.0;
+    c64 v = make_double2(0, 0);
+    if (i < c) v = make_double2(M[c * n + i].x * f, -M[c * n + i].y * f);
+    if (i == c) v = make_double2(f, 0);
+    Rinv[t] = v;
+  }
+}
+
 int32_t chol_inv(int32_t n, c64* G, int32_t ldg, double shift, c64* Rinv, int32_t* info_dev, hipStream_t st) {
   if (n <= 0) return CBS_OK;
-  hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(SWG), 0, st, n, G, ldg, shift, Rinv, info_dev);
+  const size_t smem = (size_t)n * n * sizeof(c64);
+  if (n <= 32) {
+    hipLaunchKernelGGL((k_chol_inv_lds<32>), dim3(1), dim3(256), smem, st, n, (const c64*)G, ldg, shift, Rinv,
+                       info_dev);
+  } else if (n <= CI_NMAX) {
+    CBS_HIP(hipFuncSetAttribute((const void*)k_chol_inv_lds<64>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                CI_NMAX * CI_NMAX * (int)sizeof(c64)));
+    hipLaunchKernelGGL((k_chol_inv_lds<64>), dim3(1), dim3(1024), smem, st, n, (const c64*)G, ldg, shift, Rinv,
+                       info_dev);
+  } else {
+    hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(SWG), 0, st, n, G, ldg, shift, Rinv, info_dev);
+  }
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }

@@ -27,6 +27,7 @@ int32_t eig(cbs_system* s, int32_t n, double2* H, int32_t ldh, double2* w, doubl
             int32_t* info_dev, hipStream_t st);
 int32_t lu_solve(int32_t n, double2* A, int32_t lda, double2* B, int32_t ldb, int32_t nrhs, int32_t* info_dev,
                  hipStream_t st);
+// Rinv = R^-1 of R^H R = G + shift tr(G) I; G destroyed.
 int32_t chol_inv(int32_t n, double2* G, int32_t ldg, double shift, double2* Rinv, int32_t* info_dev,
                  hipStream_t st);
 

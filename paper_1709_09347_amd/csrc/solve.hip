@@ -446,15 +446,9 @@ int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, 
       CBS_TRY(tall_gemm(N, n, m, S, N, Wp, n, Qa, N, st));
       for (int pass = 0; pass < 3; ++pass) {
         CBS_TRY(gram(s, N, m, Qa, N, m, Qa, N, G, m, st));
-        double shift = 0;
-        if (pass == 0) {
-          std::vector<c64> hg((size_t)m * m);
-          CBS_HIP(hipMemcpyAsync(hg.data(), G, hg.size() * sizeof(c64), hipMemcpyDeviceToHost, st));
-          CBS_HIP(hipStreamSynchronize(st));
-          double tr = 0;
-          for (int i = 0; i < m; ++i) tr += hg[(size_t)i * m + i].x;
-          shift = 11.0 * ((double)N * m + (double)m * (m + 1)) * 1.1102230246251565e-16 * tr;
-        }
+        // 11 (N m + m (m + 1)) u of the trace
+        const double shift =
+            pass == 0 ? 11.0 * ((double)N * m + (double)m * (m + 1)) * 1.1102230246251565e-16 : 0.0;
         CBS_TRY(chol_inv(m, G, m, shift, Ri, info, st));
         CBS_TRY(tall_gemm(N, m, m, Qa, N, Ri, m, Qb, N, st));
         std::swap(Qa, Qb);
