@@ -18,7 +18,7 @@
 namespace cbs {
 
 struct WgArgs {
-  int32_t nx, ny, nz, N, nruns, L, n_atoms, start, cap, max_iter, max_ru, hstride, hrows;
+  int32_t nx, ny, nz, N, nruns, L, n_atoms, nnz, start, cap, max_iter, max_ru, hstride, hrows;
   double kin, tol, div_factor;
   double c[5];
   const double* vloc;
@@ -46,6 +46,11 @@ struct WgArgs {
 constexpr int WG_RED = 2 * 16 * 4;   // [buffer][wave][value]
 static size_t wg_lds_bytes(int64_t N, int32_t n_atoms) {
   return (size_t)N * 32 + (size_t)n_atoms * (48 + 48) * sizeof(double) + WG_RED * sizeof(double);
+}
+// and, where they fit as well, the potential and the projectors' tables, which every iteration reads
+// again: from LDS a bra or ket step is not a trip to L2
+static size_t wg_table_bytes(int64_t N, int64_t nnz) {
+  return (size_t)N * 8 + (size_t)nnz * 2 * (32 + 4) + (size_t)(N + 1) * 4;
 }
 
 // A value that is the same in every lane, in scalar registers (lane 0's).
@@ -94,7 +99,7 @@ __device__ __forceinline__ void wg_sum(double (&v)[NV], double* red, int lane, i
 // places in LDS, its addresses) is worked out anew each time: kept, it would take 30 registers a
 // point and spill.  r, q (and x of a single point) fit 128 registers at 1024 threads for one or two
 // points, 256 at 512 threads for eight.
-template <int P, int NPT, bool HP>
+template <int P, int NPT, bool HP, bool TAB>
 __global__ void __launch_bounds__(NPT <= 2 ? 1024 : 512) k_run_wg(WgArgs a) {
   extern __shared__ __align__(16) unsigned char wg_smem[];
   constexpr bool XREG = NPT == 1;   // x in registers, else in global memory
@@ -106,6 +111,13 @@ __global__ void __launch_bounds__(NPT <= 2 ? 1024 : 512) k_run_wg(WgArgs a) {
   double* G = reinterpret_cast<double*>(pb + N);                            // [atom][shift][16]
   Pair<double>* kt = reinterpret_cast<Pair<double>*>(G + 48 * a.n_atoms);   // [atom][shift][4]
   double* red = reinterpret_cast<double*>(kt + 12 * a.n_atoms);
+  // TAB: the tables in LDS (ball_u, pt_u, vloc, ball_idx, pt_key, pt_off)
+  double4* t_u = reinterpret_cast<double4*>(red + WG_RED);
+  double4* t_pu = t_u + a.nnz;
+  double* t_v = reinterpret_cast<double*>(t_pu + a.nnz);
+  int32_t* t_idx = reinterpret_cast<int32_t*>(t_v + N);
+  int32_t* t_key = t_idx + a.nnz;
+  int32_t* t_off = t_key + a.nnz;
   int tid = threadIdx.x;
   const int T = blockDim.x, lane = tid & 63, nw = T >> 6;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -188,6 +200,16 @@ __global__ void __launch_bounds__(NPT <= 2 ? 1024 : 512) k_run_wg(WgArgs a) {
       }
     }
   }
+  if (TAB && status == ST_ACT_HI) {   // the first barrier of an iteration comes before their use
+    for (int e = tid; e < a.nnz; e += T) {
+      t_u[e] = reinterpret_cast<const double4*>(a.u)[e];
+      t_pu[e] = reinterpret_cast<const double4*>(a.pt_u)[e];
+      t_idx[e] = a.idx[e];
+      t_key[e] = a.pt_key[e];
+    }
+    for (int n = tid; n < N; n += T) t_v[n] = a.vloc[n];
+    for (int n = tid; n <= N; n += T) t_off[n] = a.pt_off[n];
+  }
   // --- iterations (repl = false) and residual replacements (repl = true)
   bool repl = false;
   int steps = 0;
@@ -244,8 +266,8 @@ __global__ void __launch_bounds__(NPT <= 2 ? 1024 : 512) k_run_wg(WgArgs a) {
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
             const int e = min(e0 + 64 * q, hi - 1);
-            uu[q] = reinterpret_cast<const double4*>(a.u)[e];
-            n[q] = a.idx[e];
+            uu[q] = TAB ? t_u[e] : reinterpret_cast<const double4*>(a.u)[e];
+            n[q] = TAB ? t_idx[e] : a.idx[e];
           }
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
@@ -286,7 +308,7 @@ __global__ void __launch_bounds__(NPT <= 2 ? 1024 : 512) k_run_wg(WgArgs a) {
     for (int k = 0; k < NPT; ++k) {
       const int n = min(tid + k * T, N - 1);
       const int ix = pos[k] & 255, iy = (pos[k] >> 8) & 4095, iz = pos[k] >> 20;
-      const double vd = a.vloc[n] - cf.E;
+      const double vd = (TAB ? t_v[n] : a.vloc[n]) - cf.E;
       const double2 va = pa[n], vb = pb[n];
       double2 sa = cscale<double>(va, 3.0 * a.c[0]), sb = cscale<double>(vb, 3.0 * a.c[0]);
       double2 ua = make_double2(0, 0), ub = ua, da = ua, db = ua;   // from the cells above and below
@@ -319,12 +341,14 @@ __global__ void __launch_bounds__(NPT <= 2 ? 1024 : 512) k_run_wg(WgArgs a) {
       sa = cfma_r<double>(cscale<double>(sa, a.kin), vd, va);
       sb = cfma_r<double>(cscale<double>(sb, a.kin), vd, vb);
       if (HP && a.n_atoms > 0) {
-        const int e1 = a.pt_off[n + 1];
-        for (int e = a.pt_off[n]; e < e1; e += 2) {
+        const int e1 = TAB ? t_off[n + 1] : a.pt_off[n + 1];
+        for (int e = TAB ? t_off[n] : a.pt_off[n]; e < e1; e += 2) {
           // two entries a step, their table reads in flight together
           const int f = min(e + 1, e1 - 1);
-          const int key[2] = {a.pt_key[e], a.pt_key[f]};
-          const double4 uu[2] = {reinterpret_cast<const double4*>(a.pt_u)[e], reinterpret_cast<const double4*>(a.pt_u)[f]};
+          const int32_t* keys = TAB ? t_key : a.pt_key;
+          const double4* ptu = TAB ? t_pu : reinterpret_cast<const double4*>(a.pt_u);
+          const int key[2] = {keys[e], keys[f]};
+          const double4 uu[2] = {ptu[e], ptu[f]};
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
             if (e + q >= e1) break;
@@ -486,8 +510,22 @@ __global__ void __launch_bounds__(256) k_wg_count(BicgScal sc, int32_t nruns) {
   }
 }
 
-static int wg_points(const cbs_system* s) {
-  return s->N <= 1024 ? 1 : s->N <= 2048 ? 2 : 8;
+// Points a thread, and whether the tables go to LDS (*tab).  A run at a time is quickest with a point
+// a thread; past a run per CU two points a thread let a second run share the CU (8x8x12, 672 ball
+// entries, microseconds per iteration of 512 runs: 15.8, one point 17.9; 256 runs 11.3 and 9.8), if
+// need be with the tables left in L2 (8x8x16, 512 runs: 16.1, one point 20.3, two with the tables in
+// LDS and so one run per CU 20.0).  One run or 256: 9.4 and 9.8 with the tables in LDS, 10.4 and 10.8
+// from L2.
+static int wg_points(const cbs_system* s, int32_t nruns, bool* tab) {
+  const size_t own = wg_lds_bytes(s->N, s->proj.n_atoms), tables = wg_table_bytes(s->N, s->proj.nnz);
+  *tab = s->proj.n_atoms > 0 && own + tables <= 160 * 1024;
+  if (s->N > 1024) return s->N <= 2048 ? 2 : 8;
+  const int64_t waves1 = (s->N + 63) / 64, waves2 = (s->N + 127) / 128;
+  if (nruns > 256 && 2 * waves1 > 16 && 2 * waves2 <= 16 && 2 * own <= 160 * 1024) {
+    *tab = *tab && 2 * (own + tables) <= 160 * 1024;
+    return 2;
+  }
+  return 1;
 }
 
 // The cells of this path: p must fit the LDS beside the projectors' sums (4096 points at most), a
@@ -505,14 +543,16 @@ bool run_wg_fits(const cbs_system* s) {
          s->proj.nnz <= 8 * s->N && wg_lds_bytes(s->N, s->proj.n_atoms) <= 160 * 1024;
 }
 
-template <int P, bool HP>
+template <int P, bool HP, bool TAB>
 static const void* wg_kernel(int npt) {
-  return npt == 1 ? (const void*)k_run_wg<P, 1, HP> : npt == 2 ? (const void*)k_run_wg<P, 2, HP> : (const void*)k_run_wg<P, 8, true>;
+  return npt == 1 ? (const void*)k_run_wg<P, 1, HP, TAB> : npt == 2 ? (const void*)k_run_wg<P, 2, HP, TAB> : (const void*)k_run_wg<P, 8, true, TAB>;
 }
 // (Eight points always take the kernel with projectors: without the ket's loop between them the
 // scheduler interleaves the points' LDS reads, and 290 registers spill: 45 us an iteration for 24.)
 template <int P>
-static const void* wg_kernel(int npt, bool hp) { return hp ? wg_kernel<P, true>(npt) : wg_kernel<P, false>(npt); }
+static const void* wg_kernel(int npt, bool hp, bool tab) {
+  return !hp ? wg_kernel<P, false, false>(npt) : tab ? wg_kernel<P, true, true>(npt) : wg_kernel<P, true, false>(npt);
+}
 
 int32_t launch_run_wg(BicgSolve& b, bool start, int32_t cap, hipStream_t st) {
   const cbs_system* s = b.sys;
@@ -524,6 +564,7 @@ int32_t launch_run_wg(BicgSolve& b, bool start, int32_t cap, hipStream_t st) {
   a.nruns = b.nruns;
   a.L = b.L;
   a.n_atoms = s->proj.n_atoms;
+  a.nnz = (int32_t)s->proj.nnz;
   a.start = start;
   a.cap = cap;
   a.max_iter = b.max_iter;
@@ -552,11 +593,13 @@ int32_t launch_run_wg(BicgSolve& b, bool start, int32_t cap, hipStream_t st) {
   a.pt_off = s->proj.pt_off;
   a.pt_key = s->proj.pt_key;
   a.pt_u = s->proj.pt_u64;
-  const int npt = wg_points(s);
+  bool tab = false;
+  const int npt = wg_points(s, b.nruns, &tab);
   const int nthr = (int)(((s->N + npt - 1) / npt + 63) / 64 * 64);
-  const size_t smem = wg_lds_bytes(s->N, s->proj.n_atoms);
+  size_t smem = wg_lds_bytes(s->N, s->proj.n_atoms);
   const bool hp = a.n_atoms > 0;
-  const void* f = s->p == 1 ? wg_kernel<1>(npt, hp) : s->p == 2 ? wg_kernel<2>(npt, hp) : s->p == 3 ? wg_kernel<3>(npt, hp) : wg_kernel<4>(npt, hp);
+  if (tab) smem += wg_table_bytes(s->N, s->proj.nnz);
+  const void* f = s->p == 1 ? wg_kernel<1>(npt, hp, tab) : s->p == 2 ? wg_kernel<2>(npt, hp, tab) : s->p == 3 ? wg_kernel<3>(npt, hp, tab) : wg_kernel<4>(npt, hp, tab);
   // always the most a cell can ask for: the attribute is the kernel's, not the launch's, and another
   // thread may be launching it for another cell
   CBS_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
