@@ -321,7 +321,7 @@ extern "C" int32_t cbs_bands(cbs_system* s, int32_t n_k, const double* k, int32_
       CBS_TRY(gram(s, N, m, X, N, m, HY, N, G, m, st));
       hipLaunchKernelGGL(k_shift_herm, dim3(1), dim3(1024), 0, st, m, (const c64*)G, shift, A);
       CBS_HIP(hipGetLastError());
-      CBS_TRY(svd_right(s, m, A, m, W, m, sig, perm, true, st));
+      CBS_TRY(svd_right(s, m, A, m, W, m, sig, perm, true, 1, st));
       hipLaunchKernelGGL(k_ritz_order, dim3(grid_of((int64_t)m * m)), dim3(256), 0, st, m, (const double*)sig,
                          (const int32_t*)perm, (const c64*)W, (const double*)shift, theta, U);
       CBS_HIP(hipGetLastError());

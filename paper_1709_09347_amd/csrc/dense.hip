@@ -582,6 +582,9 @@ constexpr size_t SV_LDS = 150 * 1024;   // columns of a block pair (or the whole
 // wave and 16 waves in LDS a step of order 64 took 4.8 us.
 template <int CPL>
 __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, int32_t lda, c64* X, int32_t* piv) {
+  A += blockIdx.y * (int64_t)lda * n;
+  X += blockIdx.y * (int64_t)n * n;
+  piv += blockIdx.y * n;
   constexpr int NW = 4 * CPL, RW = 16;
   __shared__ double pn[NW][64 * CPL];   // per wave: squared norms of the columns' remaining rows
   __shared__ c64 pd[NW][64 * CPL];      // per wave: products with the reflector
@@ -685,6 +688,10 @@ __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, i
 template <int RP>
 __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, int32_t lda, c64* M, c64* X,
                                                      int32_t* piv) {
+  A += blockIdx.y * (int64_t)lda * n;
+  M += blockIdx.y * (int64_t)n * n;
+  X += blockIdx.y * (int64_t)n * n;
+  piv += blockIdx.y * n;
   __shared__ double cnb[2][64 * RP];   // squared norms of the remaining parts, -1: taken (this step's, the next's)
   __shared__ int32_t order[64 * RP];
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -800,11 +807,14 @@ __device__ double block_max_any(double v, double* sh) {
 __host__ __device__ inline int sv_ldc(int n) { return (n + 7) / 16 * 16 + 8; }
 // RPL: rows of a column per lane, kept in registers from the inner products to the rotation.
 constexpr double SV_TOL2 = 1e-26;
+constexpr int SV_SWEEPS = 60;   // at most; also the flags of a matrix
 template <int RPL>
 __global__ void __launch_bounds__(1024) k_svd_cols(int32_t n, int32_t bs, int32_t nb, int32_t round, int32_t sweep,
                                                    int32_t sweeps, int32_t gsize, c64* X, unsigned long long* flags) {
   extern __shared__ __align__(16) unsigned char sv_smem[];
   __shared__ double sh[16];
+  X += blockIdx.y * (int64_t)n * n;
+  flags += blockIdx.y * SV_SWEEPS;
   if (sweep > 0 && __longlong_as_double((long long)flags[sweep - 1]) < SV_TOL2) return;
   c64* la = reinterpret_cast<c64*>(sv_smem);   // [2 bs][ldc]
   const int ldc = sv_ldc(n);
@@ -910,6 +920,11 @@ __global__ void k_svd_clear(int32_t n, unsigned long long* flags) {
 __global__ void __launch_bounds__(SV_T) k_svd_right(int32_t n, const c64* X, const int32_t* piv, c64* W, int32_t ldw,
                                                     double* sigma, int32_t* perm) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  X += blockIdx.y * (int64_t)n * n;
+  piv += blockIdx.y * n;
+  W += blockIdx.y * (int64_t)ldw * n;
+  sigma += blockIdx.y * 1024;
+  perm += blockIdx.y * 512;
   for (int j = wv; j < n; j += SV_T / 64) {
     double t = 0;
     for (int i = lane; i < n; i += 64) t += cabs2<double>(X[i + j * n]);
@@ -1367,33 +1382,39 @@ int32_t eig(cbs_system* s, int32_t n, c64* H, int32_t ldh, c64* w, c64* V, int32
 }
 
 // sigma (descending), perm and the right singular vectors W of A (kept): column perm[r] of W
-// belongs to sigma[r].  hermitian: A is Hermitian positive definite.
+// belongs to sigma[r].  hermitian: A is Hermitian positive definite.  nbatch matrices lda n apart (W:
+// ldw n, sigma: 1024, perm: 512) take the time of one: a matrix is a workgroup or a few (order 64,
+// six matrices: 0.85 ms, one after the other 5.0).
 int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, int32_t ldw, double* sigma,
-                  int32_t* perm, bool hermitian, hipStream_t st) {
-  if (n <= 0) return CBS_OK;
+                  int32_t* perm, bool hermitian, int32_t nbatch, hipStream_t st) {
+  if (n <= 0 || nbatch <= 0) return CBS_OK;
   if (n > 256) {
     set_error("svd: order %d above 256", n);
     return CBS_EINVAL;
   }
-  constexpr int MAXS = 60, BATCH = 6;
+  constexpr int MAXS = SV_SWEEPS, BATCH = 6;
   c64* X = nullptr;
   int32_t* piv = nullptr;
   unsigned long long* flags = nullptr;
-  CBS_TRY(ws_get(s->ws, "svd.X", (size_t)n * n, &X));
-  CBS_TRY(ws_get(s->ws, "svd.piv", (size_t)n, &piv));
-  CBS_TRY(ws_get(s->ws, "svd.flag", (size_t)MAXS, &flags));
+  CBS_TRY(ws_get(s->ws, "svd.X", (size_t)nbatch * n * n, &X));
+  CBS_TRY(ws_get(s->ws, "svd.piv", (size_t)nbatch * n, &piv));
+  CBS_TRY(ws_get(s->ws, "svd.flag", (size_t)nbatch * MAXS, &flags));
   if (hermitian) {
+    if (nbatch != 1) {
+      set_error("svd_right: Hermitian matrices come one at a time");
+      return CBS_EINVAL;
+    }
     hipLaunchKernelGGL(k_svd_copy, dim3((n * n + 255) / 256), dim3(256), 0, st, n, A, lda, X, piv);
     CBS_HIP(hipGetLastError());
   } else {
     if (n <= 64)
-      hipLaunchKernelGGL(k_svd_qr<1>, dim3(1), dim3(256), 0, st, n, A, lda, X, piv);
+      hipLaunchKernelGGL(k_svd_qr<1>, dim3(1, nbatch), dim3(256), 0, st, n, A, lda, X, piv);
     else if (n <= 128)
-      hipLaunchKernelGGL(k_svd_qr<2>, dim3(1), dim3(512), 0, st, n, A, lda, X, piv);
+      hipLaunchKernelGGL(k_svd_qr<2>, dim3(1, nbatch), dim3(512), 0, st, n, A, lda, X, piv);
     else {
       c64* M = nullptr;
-      CBS_TRY(ws_get(s->ws, "svd.M", (size_t)n * n, &M));
-      hipLaunchKernelGGL(k_svd_qr_big<4>, dim3(1), dim3(SV_T), 0, st, n, A, lda, M, X, piv);
+      CBS_TRY(ws_get(s->ws, "svd.M", (size_t)nbatch * n * n, &M));
+      hipLaunchKernelGGL(k_svd_qr_big<4>, dim3(1, nbatch), dim3(SV_T), 0, st, n, A, lda, M, X, piv);
     }
     CBS_HIP(hipGetLastError());
   }
@@ -1414,10 +1435,10 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
   auto sweep_launch = [&](int32_t round, int32_t sweep, int32_t sweeps) -> int32_t {
     int32_t bs_ = bs, nb_ = nb, gs_ = gsize;
     void* args[] = {&n, &bs_, &nb_, &round, &sweep, &sweeps, &gs_, &X, &flags};
-    CBS_HIP(hipLaunchKernel(cols, dim3(nb / 2), dim3(threads), args, smem, st));
+    CBS_HIP(hipLaunchKernel(cols, dim3(nb / 2, nbatch), dim3(threads), args, smem, st));
     return CBS_OK;
   };
-  hipLaunchKernelGGL(k_svd_clear, dim3(1), dim3(64), 0, st, MAXS, flags);
+  hipLaunchKernelGGL(k_svd_clear, dim3(1), dim3(64), 0, st, nbatch * MAXS, flags);
   CBS_HIP(hipGetLastError());
   int sweeps = 0;
   if (nb == 2) {
@@ -1426,22 +1447,26 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
     for (int s0 = 0; s0 < MAXS; s0 += BATCH) {
       for (int sw = s0; sw < s0 + BATCH; ++sw)
         for (int r = 0; r < nb - 1; ++r) CBS_TRY(sweep_launch(r, sw, 1));
-      unsigned long long h[BATCH];
-      CBS_HIP(hipMemcpyAsync(h, flags + s0, sizeof(h), hipMemcpyDeviceToHost, st));
+      std::vector<unsigned long long> h((size_t)nbatch * MAXS);
+      CBS_HIP(hipMemcpyAsync(h.data(), flags, h.size() * sizeof(h[0]), hipMemcpyDeviceToHost, st));
       CBS_HIP(hipStreamSynchronize(st));
-      bool done = false;
-      for (int k = 0; k < BATCH && !done; ++k) {
-        double om = 0;
-        std::memcpy(&om, &h[k], sizeof(om));
-        sweeps = s0 + k + 1;
-        done = !(om >= SV_TOL2);
+      bool done = true;
+      for (int b = 0; b < nbatch; ++b) {
+        bool one = false;
+        for (int k = s0; k < s0 + BATCH && !one; ++k) {
+          double om = 0;
+          std::memcpy(&om, &h[(size_t)b * MAXS + k], sizeof(om));
+          sweeps = std::max(sweeps, k + 1);
+          one = !(om >= SV_TOL2);
+        }
+        done = done && one;
       }
       if (done) break;
     }
   }
   if (const char* v = getenv("CBS_VERBOSE"))
     if (v[0] == '3') fprintf(stderr, "[cbs] svd: order %d, %d blocks of %d, %d sweeps\n", n, nb, bs, sweeps);
-  hipLaunchKernelGGL(k_svd_right, dim3(1), dim3(SV_T), 0, st, n, (const c64*)X, (const int32_t*)piv, W, ldw, sigma,
+  hipLaunchKernelGGL(k_svd_right, dim3(1, nbatch), dim3(SV_T), 0, st, n, (const c64*)X, (const int32_t*)piv, W, ldw, sigma,
                      perm);
   CBS_HIP(hipGetLastError());
   return CBS_OK;

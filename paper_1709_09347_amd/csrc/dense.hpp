@@ -19,9 +19,10 @@ int32_t small_gemm(int32_t m, int32_t n, int32_t k, const double2* A, int32_t ld
 // sorted descending with perm[r] = source column of rank r; sigma needs 1024 doubles.
 int32_t svd(int32_t n, double2* A, int32_t lda, double2* V, int32_t ldv, double* sigma, int32_t* perm,
             hipStream_t st);
-// sigma, perm and W alone (A kept): faster, for callers that need no U.
+// sigma, perm and W alone (A kept): faster, for callers that need no U; nbatch matrices lda n apart (W:
+// ldw n, sigma: 1024, perm: 512).
 int32_t svd_right(cbs_system* s, int32_t n, const double2* A, int32_t lda, double2* W, int32_t ldw, double* sigma,
-                  int32_t* perm, bool hermitian, hipStream_t st);
+                  int32_t* perm, bool hermitian, int32_t nbatch, hipStream_t st);
 // Eigenvalues w and unit eigenvectors V of a general complex matrix H (destroyed).
 int32_t eig(cbs_system* s, int32_t n, double2* H, int32_t ldh, double2* w, double2* V, int32_t ldv,
             int32_t* info_dev, hipStream_t st);

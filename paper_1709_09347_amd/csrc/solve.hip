@@ -56,6 +56,8 @@ __global__ void __launch_bounds__(256) k_moments(int64_t N, int32_t L, int32_t n
                                                  int32_t k0, int32_t nk, const Pair<double>* Y, const c64* ca,
                                                  const c64* cb, c64* S) {
   const int64_t total = N * L;
+  Y += blockIdx.y * (int64_t)n_q * total;   // one energy after the other
+  S += blockIdx.y * (int64_t)nk_total * total;
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
     const int64_t l = g / N, n = g - l * N;
     c64 acc[MOM_CHUNK];
@@ -123,6 +125,9 @@ static int32_t nodes_to_solve(cbs_system* s, const cbs_params* prm, const c64* c
 // Block Hankel matrices from mu (C[a + (k L + b) L] = mu_k[a][b]).
 __global__ void k_hankel(int32_t L, int32_t M, const c64* C, c64* T, c64* Tl) {
   const int n = L * M;
+  C += blockIdx.y * (int64_t)2 * M * L * L;   // one energy after the other
+  T += blockIdx.y * (int64_t)n * n;
+  Tl += blockIdx.y * (int64_t)n * n;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n * n; t += gridDim.x * blockDim.x) {
     const int r = t % n, c = t / n;
     const int i = r / L, a = r % L, j = c / L, b = c % L;
@@ -278,9 +283,6 @@ static void moment_weights(const cbs_params* prm, int nq, int nk, std::vector<c6
   }
 }
 
-int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, const c64* V, const c64* S,
-                  hipStream_t st, Extracted& out, double* t_mom_ms, std::chrono::steady_clock::time_point t0);
-
 // The largest primal relative residual of the runs [r0, r1) (relres: [run][primal, dual]),
 // finite values only: the noise level of the moments built from those solutions.
 static double solve_noise(const std::vector<double>& relres, int64_t r0, int64_t r1) {
@@ -290,73 +292,99 @@ static double solve_noise(const std::vector<double>& relres, int64_t r0, int64_t
   return m;
 }
 
-// Steps 2-5 for one system / energy; Y = node solutions (pairs, run = j*L + l); noise: the
-// largest relative residual of those solutions.
-int32_t extract(cbs_system* s, double E, const cbs_params* prm, double noise, const c64* V, const Pair<double>* Y,
-                int32_t nq_solved, hipStream_t st, Extracted& out, double* t_mom_ms) {
-  const int L = prm->n_rhs, M = prm->n_mom, nq = nq_solved, nk = 2 * M;
-  const int32_t conj = nq_solved != prm->n_q;
+// Moments S [ne][2M][L][N] of ne energies from their node solutions Y (pairs, run = j*L + l), one energy
+// after the other.
+static int32_t moments(cbs_system* s, const cbs_params* prm, const Pair<double>* Y, int32_t nq, int32_t ne,
+                       hipStream_t st, c64** S) {
+  const int L = prm->n_rhs, nk = 2 * prm->n_mom;
+  const int32_t conj = nq != prm->n_q;
   const int64_t N = s->N;
   Workspace& ws = s->ws;
-  auto t0 = std::chrono::steady_clock::now();
   std::vector<c64> ca, cb;
   moment_weights(prm, nq, nk, ca, cb);
-  c64 *dca = nullptr, *dcb = nullptr, *S = nullptr;
+  c64 *dca = nullptr, *dcb = nullptr;
   CBS_TRY(ws_get(ws, "mom.ca", ca.size(), &dca));
   CBS_TRY(ws_get(ws, "mom.cb", cb.size(), &dcb));
-  CBS_TRY(ws_get(ws, "mom.S", (size_t)nk * L * N, &S));
+  CBS_TRY(ws_get(ws, "mom.S", (size_t)ne * nk * L * N, S));
   CBS_HIP(hipMemcpyAsync(dca, ca.data(), ca.size() * sizeof(c64), hipMemcpyHostToDevice, st));
   CBS_HIP(hipMemcpyAsync(dcb, cb.data(), cb.size() * sizeof(c64), hipMemcpyHostToDevice, st));
   for (int k0 = 0; k0 < nk; k0 += MOM_CHUNK) {
-    hipLaunchKernelGGL(k_moments, dim3(launch_grid(N * L)), dim3(256), 0, st, N, L, nq, conj, nk, k0,
-                       std::min(MOM_CHUNK, nk - k0), Y, (const c64*)dca, (const c64*)dcb, S);
+    hipLaunchKernelGGL(k_moments, dim3(launch_grid(N * L), ne), dim3(256), 0, st, N, L, nq, conj, nk, k0,
+                       std::min(MOM_CHUNK, nk - k0), Y, (const c64*)dca, (const c64*)dcb, *S);
     CBS_HIP(hipGetLastError());
   }
-  return extract_S(s, E, prm, noise, V, S, st, out, t_mom_ms, t0);
+  return CBS_OK;
 }
 
-// Steps 2 (mu_k = V^H S_k) to 5 from the moments S [2M][L][N] of one system / energy.
-int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, const c64* V, const c64* S,
-                  hipStream_t st, Extracted& out, double* t_mom_ms, std::chrono::steady_clock::time_point t0) {
+// Hankel matrices of a group of energies and their SVDs (device, one energy after the other; sig:
+// 1024 apart, perm: 512 apart) with the singular values on the host.
+struct HankelSvd {
+  c64 *T = nullptr, *Tl = nullptr, *W = nullptr;
+  double* sig = nullptr;
+  int32_t* perm = nullptr;
+  std::vector<double> hsig;
+  double t_mom_ms = 0, t_svd_ms = 0;   // per energy of the group
+};
+
+// Energies per group: the SVD of a small matrix is a chain on one CU, and those of other energies
+// run beside it.  One where the general SVD is asked for or the arrays are dumped.
+static int32_t svd_group(const cbs_params* prm, int32_t ne, double bytes_per_energy) {
+  if (prm->extraction == CBS_HANKEL || getenv("CBS_SVD_SINGLE") || getenv("CBS_DUMP")) return 1;
+  return std::max(1, std::min({ne, 32, (int32_t)(64.0 * (1 << 20) / std::max(bytes_per_energy, 1.0))}));
+}
+
+// Steps 2 (mu_k = V^H S_k) and 3 (Hankel SVD) from the moments S [ne][2M][L][N]; t0: when they were begun.
+static int32_t hankel_svds(cbs_system* s, const cbs_params* prm, const c64* V, const c64* S, int32_t ne,
+                           hipStream_t st, std::chrono::steady_clock::time_point t0, HankelSvd& h) {
   const int L = prm->n_rhs, M = prm->n_mom, nk = 2 * M, n = L * M;
   const int64_t N = s->N;
   Workspace& ws = s->ws;
   c64* C = nullptr;
-  CBS_TRY(ws_get(ws, "mom.C", (size_t)L * nk * L, &C));
-  CBS_TRY(gram(s, N, L, V, N, nk * L, S, N, C, L, st));
+  CBS_TRY(ws_get(ws, "mom.C", (size_t)ne * L * nk * L, &C));
+  CBS_TRY(gram(s, N, L, V, N, ne * nk * L, S, N, C, L, st));
   CBS_HIP(hipStreamSynchronize(st));
   dump("S", S, (size_t)nk * L * N * sizeof(c64), st);
   dump("mu", C, (size_t)L * nk * L * sizeof(c64), st);
   auto t1 = std::chrono::steady_clock::now();
-  if (t_mom_ms) *t_mom_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
-
-  // --- Hankel SVD
-  c64 *T = nullptr, *Tl = nullptr, *W = nullptr;
-  double* sig = nullptr;
-  int32_t *perm = nullptr, *info = nullptr;
-  CBS_TRY(ws_get(ws, "hk.T", (size_t)n * n, &T));
-  CBS_TRY(ws_get(ws, "hk.Tl", (size_t)n * n, &Tl));
-  CBS_TRY(ws_get(ws, "hk.W", (size_t)n * n, &W));
-  CBS_TRY(ws_get(ws, "hk.sig", 1024, &sig));
-  CBS_TRY(ws_get(ws, "hk.perm", 512, &perm));
-  CBS_TRY(ws_get(ws, "hk.info", 4, &info));
-  CBS_HIP(hipMemsetAsync(info, 0, 4 * sizeof(int32_t), st));
-  hipLaunchKernelGGL(k_hankel, dim3(launch_grid((int64_t)n * n)), dim3(256), 0, st, L, M, (const c64*)C, T, Tl);
+  h.t_mom_ms = std::chrono::duration<double, std::milli>(t1 - t0).count() / ne;
+  CBS_TRY(ws_get(ws, "hk.T", (size_t)ne * n * n, &h.T));
+  CBS_TRY(ws_get(ws, "hk.Tl", (size_t)ne * n * n, &h.Tl));
+  CBS_TRY(ws_get(ws, "hk.W", (size_t)ne * n * n, &h.W));
+  CBS_TRY(ws_get(ws, "hk.sig", (size_t)ne * 1024, &h.sig));
+  CBS_TRY(ws_get(ws, "hk.perm", (size_t)ne * 512, &h.perm));
+  hipLaunchKernelGGL(k_hankel, dim3(launch_grid((int64_t)n * n), ne), dim3(256), 0, st, L, M, (const c64*)C, h.T, h.Tl);
   CBS_HIP(hipGetLastError());
-  dump("T", T, (size_t)n * n * sizeof(c64), st);
-  dump("Tl", Tl, (size_t)n * n * sizeof(c64), st);
+  dump("T", h.T, (size_t)n * n * sizeof(c64), st);
+  dump("Tl", h.Tl, (size_t)n * n * sizeof(c64), st);
   // the Rayleigh-Ritz extraction needs the right vectors only; the Hankel extraction U too
   if (prm->extraction == CBS_HANKEL || getenv("CBS_SVD_SINGLE"))
-    CBS_TRY(svd(n, T, n, W, n, sig, perm, st));
+    CBS_TRY(svd(n, h.T, n, h.W, n, h.sig, h.perm, st));
   else
-    CBS_TRY(svd_right(s, n, T, n, W, n, sig, perm, false, st));
-  dump("U", T, (size_t)n * n * sizeof(c64), st);
-  dump("W", W, (size_t)n * n * sizeof(c64), st);
-  dump("sigma", sig, (size_t)n * sizeof(double), st);
-  dump("perm", perm, (size_t)n * sizeof(int32_t), st);
-  std::vector<double> hsig(n);
-  CBS_HIP(hipMemcpyAsync(hsig.data(), sig, n * sizeof(double), hipMemcpyDeviceToHost, st));
+    CBS_TRY(svd_right(s, n, h.T, n, h.W, n, h.sig, h.perm, false, ne, st));
+  dump("U", h.T, (size_t)n * n * sizeof(c64), st);
+  dump("W", h.W, (size_t)n * n * sizeof(c64), st);
+  dump("sigma", h.sig, (size_t)n * sizeof(double), st);
+  dump("perm", h.perm, (size_t)n * sizeof(int32_t), st);
+  h.hsig.resize((size_t)ne * 1024);
+  CBS_HIP(hipMemcpyAsync(h.hsig.data(), h.sig, h.hsig.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   CBS_HIP(hipStreamSynchronize(st));
+  h.t_svd_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t1).count() / ne;
+  return CBS_OK;
+}
+
+// Steps 4 and 5 from the moments S [2M][L][N] and the SVD (number at of its group) of one system /
+// energy; noise: the largest relative residual of the node solutions.
+int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, const c64* S, const HankelSvd& h,
+                  int32_t at, hipStream_t st, Extracted& out) {
+  const int L = prm->n_rhs, M = prm->n_mom, n = L * M;
+  const int64_t N = s->N;
+  Workspace& ws = s->ws;
+  c64 *T = h.T + (size_t)at * n * n, *Tl = h.Tl + (size_t)at * n * n, *W = h.W + (size_t)at * n * n;
+  double* sig = h.sig + (size_t)at * 1024;
+  int32_t *perm = h.perm + (size_t)at * 512, *info = nullptr;
+  CBS_TRY(ws_get(ws, "hk.info", 4, &info));
+  CBS_HIP(hipMemsetAsync(info, 0, 4 * sizeof(int32_t), st));
+  const std::vector<double> hsig(h.hsig.begin() + (size_t)at * 1024, h.hsig.begin() + (size_t)at * 1024 + n);
   if (!all_finite(n, hsig.data())) {
     set_error("non-finite singular values of the Hankel matrix (a linear solve diverged)");
     return CBS_ENONFINITE;
@@ -598,6 +626,18 @@ int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, 
   return CBS_OK;
 }
 
+// Steps 2-5 for one system / energy; Y = node solutions (pairs, run = j*L + l).
+int32_t extract(cbs_system* s, double E, const cbs_params* prm, double noise, const c64* V, const Pair<double>* Y,
+                int32_t nq_solved, hipStream_t st, Extracted& out, double* t_mom_ms) {
+  const auto t0 = std::chrono::steady_clock::now();
+  c64* S = nullptr;
+  HankelSvd h;
+  CBS_TRY(moments(s, prm, Y, nq_solved, 1, st, &S));
+  CBS_TRY(hankel_svds(s, prm, V, S, 1, st, t0, h));
+  if (t_mom_ms) *t_mom_ms = h.t_mom_ms;
+  return extract_S(s, E, prm, noise, S, h, 0, st, out);
+}
+
 int32_t store_last(cbs_system* s, double E, const Extracted& ex, hipStream_t st) {
   LastSolve& L = s->last;
   const size_t cnt = ex.lam.size();
@@ -812,14 +852,19 @@ static int32_t solve_batched_queue(int32_t n_sys, cbs_system* const* systems, in
     CBS_HIP(hipMemcpyAsync(stt.data(), q.item_status, stt.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     CBS_HIP(hipMemcpyAsync(rr.data(), q.item_relres, rr.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     CBS_HIP(hipStreamSynchronize(st));
+    const int group = svd_group(prm, n_E, 0);
+    HankelSvd h;
     for (int e = 0; e < n_E; ++e) {
-      const int ie = s * n_E + e;
+      const int ie = s * n_E + e, at = e % group;
       Extracted ex;
-      double tmom = 0;
-      auto t0 = std::chrono::steady_clock::now();
       const c64* Se = q.S + (size_t)e * M2 * L * sy->N;
-      const int32_t rc = extract_S(sy, E[e], prm, solve_noise(rr, (int64_t)e * nq * L, (int64_t)(e + 1) * nq * L),
-                                   (const c64*)V[s], Se, st, ex, &tmom, t0);
+      if (at == 0)
+        CBS_TRY(hankel_svds(sy, prm, (const c64*)V[s], Se, std::min(group, n_E - e), st,
+                            std::chrono::steady_clock::now(), h));
+      const double tmom = h.t_mom_ms;
+      const auto t0 = std::chrono::steady_clock::now();
+      const int32_t rc = extract_S(sy, E[e], prm, solve_noise(rr, (int64_t)e * nq * L, (int64_t)(e + 1) * nq * L), Se,
+                                   h, at, st, ex);
       if (rc == CBS_EHIP || rc == CBS_ENOMEM || rc == CBS_EINVAL) return rc;
       bool noconv = false, brk = false;
       double mx = 0, sum = 0;
@@ -859,7 +904,7 @@ static int32_t solve_batched_queue(int32_t n_sys, cbs_system* const* systems, in
         for (double r : ex.res) in.max_eig_resid = std::max(in.max_eig_resid, r);
         in.sigma_first = ex.sig1;
         in.sigma_ratio = ex.sig_ratio;
-        in.t_extract_ms = std::chrono::duration<double, std::milli>(t1 - t0).count() - tmom;
+        in.t_extract_ms = std::chrono::duration<double, std::milli>(t1 - t0).count() + h.t_svd_ms;
       }
       int32_t prc = CBS_OK;
       if (cnt > max_eigs) {
@@ -983,15 +1028,24 @@ extern "C" int32_t cbs_solve_batched(int32_t n_sys, cbs_system* const* systems, 
       cbs_system* sy = systems[s];
       NodeSolve ns;
       CBS_TRY(bicg_collect(solves[s], ns, st));
+      const size_t s_len = (size_t)2 * prm->n_mom * L * sy->N;
+      const int group = svd_group(prm, ne, (double)s_len * sizeof(c64));
+      HankelSvd h;
+      c64* S = nullptr;
       for (int e = 0; e < ne; ++e) {
-        const int ie = s * n_E + e0 + e;
+        const int ie = s * n_E + e0 + e, at = e % group;
         Extracted ex;
-        double tmom = 0;
-        auto t0 = std::chrono::steady_clock::now();
-        const Pair<double>* Ye = ns.Y + (size_t)e * nq * L * sy->N;
-        const int32_t rc = extract(sy, E[e0 + e], prm,
-                                   solve_noise(ns.relres, (int64_t)e * nq * L, (int64_t)(e + 1) * nq * L),
-                                   (const c64*)V[s], Ye, nq, st, ex, &tmom);
+        if (at == 0) {
+          const auto tb = std::chrono::steady_clock::now();
+          const int cnt = std::min(group, ne - e);
+          CBS_TRY(moments(sy, prm, ns.Y + (size_t)e * nq * L * sy->N, nq, cnt, st, &S));
+          CBS_TRY(hankel_svds(sy, prm, (const c64*)V[s], S, cnt, st, tb, h));
+        }
+        const double tmom = h.t_mom_ms;
+        const auto t0 = std::chrono::steady_clock::now();
+        const int32_t rc = extract_S(sy, E[e0 + e], prm,
+                                     solve_noise(ns.relres, (int64_t)e * nq * L, (int64_t)(e + 1) * nq * L),
+                                     S + at * s_len, h, at, st, ex);
         if (rc == CBS_EHIP || rc == CBS_ENOMEM || rc == CBS_EINVAL) return rc;
         if (rc != CBS_OK) {
           // this pair has no eigenpairs (non-finite moments or a failed dense step); the
@@ -1032,7 +1086,7 @@ extern "C" int32_t cbs_solve_batched(int32_t n_sys, cbs_system* const* systems, 
           in.sigma_ratio = ex.sig_ratio;
           in.t_solve_ms = ms;   // shared by the whole wave
           in.t_moments_ms = tmom;
-          in.t_extract_ms = std::chrono::duration<double, std::milli>(t1 - t0).count() - tmom;
+          in.t_extract_ms = std::chrono::duration<double, std::milli>(t1 - t0).count() + h.t_svd_ms;
           in.matvecs = (int64_t)(2 * sum);
           in.refine_steps = ns.n_ru;
           in.restarts = (int32_t)std::min<int64_t>(ns.restarts, INT32_MAX);
