@@ -867,6 +867,7 @@ static int32_t alloc_vecs(cbs_system* s, BicgVecs<T>& v, size_t nruns, const std
   v.tile_y = s->tile_y[std::is_same<T, float>::value ? 1 : 0];
   v.zseg = stencil_segments(s, v.tile_y, (int32_t)nruns);
   v.ntiles = stencil_tiles(s, v.tile_y) * v.zseg;
+  v.bra_with = bra_with_stencil(s, (int32_t)nruns, v.zseg);
   CBS_TRY(ws_get(ws, (pre + "sig").c_str(), nruns * v.ntiles, &v.sig));
   return CBS_OK;
 }
@@ -968,10 +969,15 @@ static int32_t enqueue_stencil_bra(BicgSolve& b, BicgVecs<T>& v, int32_t need, i
   const int ph = (need == ST_ACT_LO) ? 0 : 1;
   l.list = b.sc.list + (size_t)ph * b.nruns;
   l.count = b.sc.n_active + ph;
+  const bool together = v.bra_with && v.ev0 == nullptr;
+  if (together) {
+    l.kt = v.KT;
+    l.signl = b.signl;
+  }
   if (v.ev0) CBS_HIP(hipEventRecord(v.ev0, st));
   CBS_TRY(launch_stencil<T>(s, true, l, v.tile_y, st));
   if (v.ev1) CBS_HIP(hipEventRecord(v.ev1, st));
-  if (s->proj.n_atoms > 0)
+  if (s->proj.n_atoms > 0 && !together)
     CBS_TRY(launch_bra<T>(s, b.nruns, v.Pb[parity & 1], b.coef, b.sc.status, need, v.KT, b.signl, st, true,
                           l.list, l.count, false, b.bra_part));
   return CBS_OK;

@@ -57,6 +57,7 @@ struct BicgVecs {
   Pair<T>* KT = nullptr;
   double2* sig = nullptr;   // [run][tile][segment] stencil partials of sigma
   int32_t tile_y = 0, zseg = 1;
+  bool bra_with = false;    // the bra in the stencil's launch
   int32_t ntiles = 0;       // partials of sigma per run: tiles times z segments
   hipEvent_t ev0 = nullptr, ev1 = nullptr;   // profiling of the stencil launches
   int64_t prof_launches = 0;

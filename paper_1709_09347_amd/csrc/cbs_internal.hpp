@@ -330,12 +330,15 @@ struct StencilLaunch {
   const int32_t* list;      // device [nruns] active runs (ascending) or NULL: all runs
   const int32_t* count;     // device: entries of list (with list)
   int32_t zseg;             // z segments per tile (0 or 1: one), for few runs
+  void* kt;                 // BiCG in z segments: K [nruns][atom][12] pairs, if this launch does the bra too
+  double2* signl;           // with kt: its part of sigma [nruns * n_atoms]
 };
 template <typename R>
 int32_t launch_stencil(const cbs_system* s, bool bicg, const StencilLaunch& a, int32_t tile_y,
                        hipStream_t st);
 int32_t stencil_tiles(const cbs_system* s, int32_t tile_y);
 int32_t stencil_segments(const cbs_system* s, int32_t tile_y, int32_t nruns);   // z segments per tile
+bool bra_with_stencil(const cbs_system* s, int32_t nruns, int32_t zseg);   // one launch for both
 int32_t default_tile_y(const cbs_system* s, int32_t bytes_per_pair);
 // Times every feasible tile height once per system and precision (CBS_AUTOTUNE=0: keep defaults).
 int32_t autotune_tiles(cbs_system* s, hipStream_t st);

@@ -47,6 +47,14 @@ struct StArgs {
   double2* sig_part;
   const int32_t* list;    // active runs (ascending) or NULL
   const int32_t* count;   // device count of list entries
+  // the bra, where the launch carries it: its workgroups come first
+  int32_t bgrid, nruns, n_atoms, nsub;   // nsub: items (an atom and a run) per workgroup, four waves each
+  const int32_t* bseg;
+  const int32_t* bidx;
+  const R* bu;
+  const R* bcoeff;
+  Pair<R>* kt;
+  double2* signl;
 };
 
 __device__ __forceinline__ double2 wave_sum2(double2 v) {
@@ -67,18 +75,116 @@ __device__ __forceinline__ cplx<C> dir_fma(cplx<C> r, cplx<C> b, cplx<C> p) {
   return mkc<C>(fma(-b.y, p.y, fma(b.x, p.x, r.x)), fma(b.y, p.x, fma(b.x, p.y, r.y)));
 }
 
+// The projections of an atom and a run, K[w][i] = h_ai z^-w c_i with c_i = sum_w z^w sum_e u_{e,i} p(idx_e)
+// (dual: 1/conj z), and the atom's part of sigma, on the direction that the same launch's stencil
+// writes: p = r + beta p_old is worked out again at the ball's points, as stored.  For few runs, where
+// the two would each leave the chip idle.
+template <typename R, typename C>
+__device__ __forceinline__ void bicg_bra(const StArgs<R>& a, unsigned char* smem) {
+  const int sub = threadIdx.x >> 8, tid = threadIdx.x & 255, lane = tid & 63, wv = tid >> 6;
+  const int nslots = (a.list != nullptr) ? *a.count : a.nruns;
+  const int item = blockIdx.x * a.nsub + sub;   // the atoms of a run side by side
+  C(*red)[3][16] = reinterpret_cast<C(*)[3][16]>(smem) + 4 * sub;   // [wave][shift][4 i + (a.x, a.y, b.x, b.y)]
+  const int slot = item / a.n_atoms, atom = item - slot * a.n_atoms;
+  bool on = sub < a.nsub && slot < nslots;
+  const int run = !on ? 0 : (a.list != nullptr) ? a.list[slot] : slot;
+  on = on && (a.status == nullptr || a.status[run] == a.need_status);   // the same for four waves
+  if (on) {
+    using U4 = typename vec4<R>::T;
+    const U4* ut = reinterpret_cast<const U4*>(a.bu);
+    const Pair<R>* rv = a.rin + (int64_t)run * a.N;
+    const Pair<R>* pv = a.pold + (int64_t)run * a.N;
+    const double2 bt = a.beta[run];
+    const cplx<C> ba = mkc<C>((C)bt.x, (C)bt.y), bb = cconj<C>(ba);
+    for (int sg = 0; sg < 3; ++sg) {
+      const int lo = a.bseg[4 * atom + sg], hi = a.bseg[4 * atom + sg + 1];
+      C acc[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[k] = 0;
+      // two entries a step, their gathers out together; loads past the segment are clamped into it
+      // and weighted by zero
+      const int last = max(hi - 1, lo);
+      for (int e0 = lo + tid; e0 - tid < hi; e0 += 512) {
+        Pair<R> r[2], p[2];
+        U4 u[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int e = min(e0 + 256 * q, last), n = a.bidx[e];
+          u[q] = ut[e];
+          r[q] = rv[n];
+          p[q] = pv[n];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          Pair<C> v = pcast<C, R>(r[q]);
+          const Pair<C> po = pcast<C, R>(p[q]);
+          v.a = dir_fma<C>(v.a, ba, po.a);
+          v.b = dir_fma<C>(v.b, bb, po.b);
+          v = pcast<C, R>(pcast<R, C>(v));
+          const C w = e0 + 256 * q < hi ? (C)1 : (C)0;
+          const C us[4] = {w * (C)u[q].x, w * (C)u[q].y, w * (C)u[q].z, w * (C)u[q].w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            acc[4 * i] += us[i] * v.a.x;
+            acc[4 * i + 1] += us[i] * v.a.y;
+            acc[4 * i + 2] += us[i] * v.b.x;
+            acc[4 * i + 3] += us[i] * v.b.y;
+          }
+        }
+      }
+      C t = 0;
+      if (lo < hi) t = wave_sums<16, C>(acc, lane);   // uniform over the four waves
+      if ((lane & 3) == 0) red[wv][sg][lane >> 2] = t;
+    }
+  }
+  __syncthreads();
+  if (!on || wv != 0 || lane >= 24) return;
+  const RunCoef& cf = a.coef[run];
+  // lane: half, projector, cell shift
+  const int half = lane & 1, i = (lane >> 1) & 3, w = lane >> 3;
+  const cplx<C> zp = ccast<C, double>(cf.c[3 * half + 1]), zm = ccast<C, double>(cf.c[3 * half + 2]);
+  cplx<C> c = mkc<C>(0, 0);
+#pragma unroll
+  for (int w2 = 0; w2 < 3; ++w2) {
+    const int q = 4 * i + 2 * half;
+    const cplx<C> g = mkc<C>(red[0][w2][q] + red[1][w2][q] + red[2][w2][q] + red[3][w2][q],
+                             red[0][w2][q + 1] + red[1][w2][q + 1] + red[2][w2][q + 1] + red[3][w2][q + 1]);
+    c = cadd<C>(c, w2 == 1 ? g : cmul<C>(w2 == 0 ? zm : zp, g));
+  }
+  const C h = (C)a.bcoeff[4 * atom + i];
+  const cplx<C> k = cscale<C>(w == 1 ? c : cmul<C>(w == 0 ? zp : zm, c), h);
+  cplx<R>* dst = reinterpret_cast<cplx<R>*>(&a.kt[((int64_t)run * a.n_atoms + atom) * 12 + w * 4 + i]);
+  dst[half] = ccast<R, C>(k);
+  // sigma: sum_i h conj(c_dual) c_primal, over the lanes of the first shift
+  const C ox = __shfl_xor(c.x, 1, 64), oy = __shfl_xor(c.y, 1, 64);
+  const cplx<C> pr = cscale<C>(cmulc<C>(mkc<C>(ox, oy), c), h);   // meant on the primal lanes 0, 2, 4, 6
+  double sx = (double)pr.x, sy = (double)pr.y;
+  sx += __shfl_xor(sx, 2, 64);
+  sy += __shfl_xor(sy, 2, 64);
+  sx += __shfl_xor(sx, 4, 64);
+  sy += __shfl_xor(sy, 4, 64);
+  if (lane == 0) a.signl[(int64_t)run * a.n_atoms + atom] = make_double2(sx, sy);
+}
+
 // R: storage precision of the vectors (and of the LDS plane); C: arithmetic precision.  SEG: the
 // march is cut into z segments, whose neighbouring planes are prefetched as the staged ones are
 // (whole tiles, 48 x 48 x 32 and 256 runs in complex128: 0.77 ms without that, 0.82 ms with it).
-template <typename R, typename C, int P, bool BICG, bool SEG>
+// BRA: the launch begins with the workgroups of bicg_bra.
+template <typename R, typename C, int P, bool BICG, bool SEG, bool BRA>
 __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double2 red[8];
+  if constexpr (BRA) {
+    if ((int)blockIdx.x < a.bgrid) {
+      bicg_bra<R, C>(a, smem_raw);
+      return;
+    }
+  }
   Pair<R>* lds = reinterpret_cast<Pair<R>*>(smem_raw);
 
   const int per_run = a.ntiles * a.nzseg;
   const int nl = (a.list != nullptr) ? min(a.nlogical, *a.count * per_run) : a.nlogical;
-  const int lb = remap_active(blockIdx.x, nl);
+  const int lb = remap_active(blockIdx.x - (BRA ? a.bgrid : 0), nl);
   if (lb < 0) return;
   const int slot = lb / per_run;
   const int rem = lb - slot * per_run;
@@ -97,7 +203,7 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
   const int tx = tid % nx;
   const int ty = tid / nx;
   const int y = tile * TY + ty;
-  const bool own = (y < ny);
+  const bool own = ty < TY && y < ny;   // a workgroup with the bra may have threads to spare
   const int64_t plane = (int64_t)nx * ny;
   const int64_t base = (int64_t)run * a.N;
   const int rows = TY + 2 * P;
@@ -377,6 +483,18 @@ int32_t stencil_segments(const cbs_system* s, int32_t tile_y, int32_t nruns) {
   return best;
 }
 
+// Up to a million (ball entry, run) pairs and a thousand (atom, run) items the stencil's launch
+// does the bra too.  Microseconds per iteration, apart and together: 48x48x32, 402,000 entries, one
+// run 81 and 62, four 90 and 91; 32x32x24, 109,000 entries, four 73 and 62, sixteen 86 and 92;
+// 23x19x17, 11,000 entries, 64 runs 87 and 80, 128 runs 115 and 118; 16x16x16, eight atoms, 64 runs 65
+// and 61, 128 runs 79 and 78.  Not where the environment chooses among the separate kernels.
+bool bra_with_stencil(const cbs_system* s, int32_t nruns, int32_t zseg) {
+  for (const char* e : {"CBS_BRA_TILE", "CBS_BRA_NW", "CBS_BRA_SPREAD", "CBS_BRA_MAP", "CBS_NO_MFMA"})
+    if (getenv(e) != nullptr) return false;
+  return zseg > 1 && s->proj.n_atoms > 0 && s->proj.nnz * nruns <= 1000000 &&
+         (int64_t)s->proj.n_atoms * nruns <= 1000;
+}
+
 int32_t default_tile_y(const cbs_system* s, int32_t bytes_per_pair) {
   int best = 1;
   double best_cost = 1e30;
@@ -396,24 +514,36 @@ int32_t default_tile_y(const cbs_system* s, int32_t bytes_per_pair) {
 }
 
 template <typename R, typename C, int P, bool BICG>
-static int32_t launch_pc(const cbs_system* s, const StArgs<R>& a, hipStream_t st) {
-  const int nthr = s->nx * a.ty;
-  const size_t smem = (size_t)a.nbuf * (a.ty + 2 * P) * s->nx * sizeof(Pair<R>);
+static int32_t launch_pc(const cbs_system* s, StArgs<R>& a, hipStream_t st) {
+  int nthr = s->nx * a.ty;
+  size_t smem = (size_t)a.nbuf * (a.ty + 2 * P) * s->nx * sizeof(Pair<R>);
   if (smem > 64 * 1024) {
     set_error("stencil tile of %d rows x %d needs %zu bytes of LDS", a.ty, s->nx, smem);
     return CBS_EINVAL;
   }
-  const int grid = (a.nlogical + 7) / 8 * 8;
+  int grid = (a.nlogical + 7) / 8 * 8;
+  if constexpr (BICG) {
+    if (a.kt != nullptr) {
+      nthr = std::max((nthr + 63) / 64 * 64, 256);
+      a.nsub = nthr / 256;
+      smem = std::max(smem, (size_t)a.nsub * 4 * 3 * 16 * sizeof(C));
+      a.bgrid = ((a.nruns * a.n_atoms + a.nsub - 1) / a.nsub + 7) / 8 * 8;
+      grid += a.bgrid;
+      hipLaunchKernelGGL((k_stencil<R, C, P, true, true, true>), dim3(grid), dim3(nthr), smem, st, a);
+      CBS_HIP(hipGetLastError());
+      return CBS_OK;
+    }
+  }
   if (a.nzseg > 1)
-    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, true>), dim3(grid), dim3(nthr), smem, st, a);
+    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, true, false>), dim3(grid), dim3(nthr), smem, st, a);
   else
-    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, false>), dim3(grid), dim3(nthr), smem, st, a);
+    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, false, false>), dim3(grid), dim3(nthr), smem, st, a);
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }
 
 template <typename R, int P, bool BICG>
-static int32_t launch_p(const cbs_system* s, const StArgs<R>& a, hipStream_t st) {
+static int32_t launch_p(const cbs_system* s, StArgs<R>& a, hipStream_t st) {
   if (std::is_same<R, float>::value && lo_arith_fp32()) return launch_pc<R, float, P, BICG>(s, a, st);
   return launch_pc<R, double, P, BICG>(s, a, st);
 }
@@ -450,6 +580,14 @@ int32_t launch_stencil(const cbs_system* s, bool bicg, const StencilLaunch& l, i
   a.sig_part = l.sig_part;
   a.list = l.list;
   a.count = l.count;
+  a.nruns = l.nruns;
+  a.n_atoms = s->proj.n_atoms;
+  a.kt = bicg && l.kt != nullptr && a.n_atoms > 0 ? (Pair<R>*)l.kt : nullptr;
+  a.signl = l.signl;
+  a.bseg = s->proj.seg;
+  a.bidx = s->proj.ball_idx;
+  a.bu = std::is_same<R, double>::value ? (const R*)s->proj.ball_u64 : (const R*)s->proj.ball_u32;
+  a.bcoeff = std::is_same<R, double>::value ? (const R*)s->proj.coeff64 : (const R*)s->proj.coeff32;
   if ((a.list == nullptr) != (a.count == nullptr)) {
     set_error("launch_stencil: a run list needs its count");
     return CBS_EINVAL;

@@ -1,6 +1,6 @@
 """BiCG on cells past the one-workgroup path with too few runs to fill the chip: the stencil marches
-in z segments (down to one plane, shorter than the stencil's half-width) and the update takes short
-chunks.  Against the oracle's recurrence after a fixed number of steps, primal and dual, for staged
+in z segments (down to one plane, shorter than the stencil's half-width), the projections may share its
+launch (one or two items to a workgroup) and the update takes short chunks.  Against the oracle's recurrence after a fixed number of steps, primal and dual, for staged
 planes that fit the prefetch registers and planes that don't.
 
 Tolerance: the same recurrences with the sums added in another order, 12 steps from the start, where
@@ -20,6 +20,8 @@ CELLS = {
     "ragged_tile_unstaged_ahead": (130, 7, 11, 8, 4, 1.1, 2, 2),
     "order_2": (21, 20, 13, 2, 5, 1.6, 2, 3),
     "order_4_two_segments": (24, 24, 10, 4, 6, 1.6, 3, 30),
+    "two_items_a_workgroup": (32, 17, 12, 6, 7, 1.6, 3, 3),
+    "wide_ball": (18, 18, 13, 6, 3, 2.5, 1, 3),
 }
 
 
