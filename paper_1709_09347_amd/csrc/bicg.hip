@@ -6,7 +6,7 @@
 //
 // Per iteration, for every precision phase that has runs:
 //   A   stencil: p = r + beta p_old (dual conj(beta)), q = local part of P p,
-//       x += xcoef p_old, local part of sigma = pt^H q
+//       x += xcoef2 p_older + xcoef p_old on odd iterations, local part of sigma = pt^H q
 //   bra projector coefficients of p, nonlocal part of sigma
 // then
 //   S1  alpha = rho / sigma
@@ -103,7 +103,8 @@ __global__ void __launch_bounds__(256) k_partials(int64_t N, int32_t nchunks, in
   if (tid < 4) part[((int64_t)run * nchunks + ch) * 4 + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
 }
 
-// Residual replacement, first half: x += xcoef p (the pending update), y += x, x = 0.
+// Residual replacement, first half: the pending updates x += xcoef2 p' (p' the direction before
+// the latest, in the other buffer, where x takes two at a time) and x += xcoef p, y += x, x = 0.
 // The run's latest direction p is in the buffer of the iteration that marked it (ru_par);
 // marked on the previous iteration, it is also copied to this iteration's buffer, the one
 // the run's next stencil pass reads as p_old.  Work items: (entry of the replacement list,
@@ -112,8 +113,8 @@ __global__ void __launch_bounds__(256) k_partials(int64_t N, int32_t nchunks, in
 template <typename T>
 __global__ void __launch_bounds__(256) k_ru_pre(int64_t N, int32_t nchunks, int32_t nlogical, const int32_t* list,
                                                 const int32_t* count, const int32_t* status, int32_t need,
-                                                const double2* xcoef, const int32_t* ru_par, int32_t parity,
-                                                Pair<T>* P0, Pair<T>* P1, Pair<T>* X, Pair<double>* Y) {
+                                                const double2* xcoef, const double2* xcoef2, const int32_t* ru_par,
+                                                int32_t parity, Pair<T>* P0, Pair<T>* P1, Pair<T>* X, Pair<double>* Y) {
   const int nl = min(nlogical, *count * nchunks);
   for (int lb = blockIdx.x; lb < nl; lb += gridDim.x) {
     const int slot = lb / nchunks, ch = lb - slot * nchunks;
@@ -123,14 +124,23 @@ __global__ void __launch_bounds__(256) k_ru_pre(int64_t N, int32_t nchunks, int3
     const int64_t lo = ch * chunk, hi = std::min<int64_t>(lo + chunk, N);
     const double2 xc = xcoef[run];
     const cplx<T> xa = mkc<T>((T)xc.x, (T)xc.y), xb = cconj<T>(xa);
+    const double2 yc = xcoef2[run];
+    const cplx<T> ya = mkc<T>((T)yc.x, (T)yc.y), yb = cconj<T>(ya);
+    const bool two = yc.x != 0.0 || yc.y != 0.0;
     const int rp = ru_par[run];
     const Pair<T>* P = rp ? P1 : P0;
+    const Pair<T>* Pb = rp ? P0 : P1;
     Pair<T>* Pnow = (parity & 1) ? P1 : P0;
     const bool copy = rp != (parity & 1);
     for (int64_t n = lo + threadIdx.x; n < hi; n += 256) {
       const int64_t g = (int64_t)run * N + n;
       Pair<T> x = X[g];
       const Pair<T> p = P[g];
+      if (two) {
+        const Pair<T> z = Pb[g];
+        x.a = cfma<T>(x.a, ya, z.a);
+        x.b = cfma<T>(x.b, yb, z.b);
+      }
       if (copy) Pnow[g] = p;
       x.a = cfma<T>(x.a, xa, p.a);
       x.b = cfma<T>(x.b, xb, p.b);
@@ -360,7 +370,7 @@ __global__ void __launch_bounds__(256) k_s0(BicgScal sc, int32_t nruns, int32_t 
     sc.vn2[run] = (vref != nullptr && vref[run] > 0) ? vref[run] : s[2];
     sc.beta[run] = make_double2(0, 0);
     sc.alpha[run] = make_double2(0, 0);
-    sc.xcoef[run] = make_double2(0, 0);
+    sc.xcoef[run] = sc.xcoef2[run] = make_double2(0, 0);
     sc.iters[run] = 0;
     sc.nru[run] = 0;
     sc.brk[run] = 0;
@@ -386,7 +396,7 @@ __global__ void __launch_bounds__(256) k_s0(BicgScal sc, int32_t nruns, int32_t 
 // partials of sigma = pt^H q, lane 0 sets alpha.
 __global__ void __launch_bounds__(256) k_s1(BicgScal sc, int32_t nruns, int32_t n_atoms, const double2* sig_lo,
                                             int32_t nt_lo, const double2* sig_hi, int32_t nt_hi,
-                                            const double2* signl, int32_t parity) {
+                                            const double2* signl, int32_t parity, int32_t defer_x) {
   const int lane = threadIdx.x & 63;
   const int run = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (run >= nruns) return;
@@ -409,6 +419,8 @@ __global__ void __launch_bounds__(256) k_s1(BicgScal sc, int32_t nruns, int32_t 
   sg.x = wsum<double>(sg.x);
   sg.y = wsum<double>(sg.y);
   if (lane != 0) return;
+  // an even iteration's stencil left x without the previous direction
+  sc.xcoef2[run] = (defer_x && !(parity & 1)) ? sc.xcoef[run] : make_double2(0, 0);
   if (!(sg.x != 0.0 || sg.y != 0.0) || !finite2(sg)) {
     sc.brk[run] = 1;
     sc.status[run] = (st == ST_ACT_LO) ? ST_RU_LO : ST_RU_HI;
@@ -521,7 +533,7 @@ __global__ void __launch_bounds__(1024) k_s3(BicgScal sc, int32_t nruns, int32_t
       sc.nru[run] = nru;
       sc.ru_it[run] = sc.iters[run];
       sc.rmin[run] = fmax(rr, rrt);
-      sc.xcoef[run] = make_double2(0, 0);
+      sc.xcoef[run] = sc.xcoef2[run] = make_double2(0, 0);
       const double2 rn = make_double2(s[0], s[1]);
       if (rr < tol && rrt < tol) {
         st = ST_DONE;
@@ -764,7 +776,7 @@ __global__ void __launch_bounds__(256) k_q_s0(BicgScal sc, QueueState q, int32_t
     sc.vn2[run] = s[2];
     sc.beta[run] = make_double2(0, 0);
     sc.alpha[run] = make_double2(0, 0);
-    sc.xcoef[run] = make_double2(0, 0);
+    sc.xcoef[run] = sc.xcoef2[run] = make_double2(0, 0);
     sc.iters[run] = 0;
     sc.nru[run] = 0;
     sc.brk[run] = 0;
@@ -888,6 +900,7 @@ int32_t bicg_alloc(BicgSolve& b, const char* tag) {
     CBS_TRY(autotune_tiles(s, nullptr));
     if (b.mixed) CBS_TRY(alloc_vecs<float>(s, b.lo, R, t + ".lo."));
     CBS_TRY(alloc_vecs<double>(s, b.hi, R, t + ".hi."));
+    b.defer_x = b.hi.zseg == 1 && (!b.mixed || b.lo.zseg == 1);
     CBS_TRY(ws_get(ws, (t + ".Y").c_str(), R * s->N, &b.Y));
     b.nchunks = update_chunks(s, b.nruns);
     const int na = s->proj.n_atoms;
@@ -904,6 +917,7 @@ int32_t bicg_alloc(BicgSolve& b, const char* tag) {
   }
   CBS_TRY(ws_get(ws, (t + ".alpha").c_str(), R, &b.sc.alpha));
   CBS_TRY(ws_get(ws, (t + ".xcoef").c_str(), R, &b.sc.xcoef));
+  CBS_TRY(ws_get(ws, (t + ".xcoef2").c_str(), R, &b.sc.xcoef2));
   CBS_TRY(ws_get(ws, (t + ".beta").c_str(), R, &b.sc.beta));
   CBS_TRY(ws_get(ws, (t + ".rho").c_str(), R, &b.sc.rho));
   CBS_TRY(ws_get(ws, (t + ".rhop").c_str(), R, &b.sc.rho_prev));
@@ -962,6 +976,7 @@ static int32_t enqueue_stencil_bra(BicgSolve& b, BicgVecs<T>& v, int32_t need, i
   l.coef = b.coef;
   l.beta = b.sc.beta;
   l.xcoef = b.sc.xcoef;
+  l.xcoef2 = b.defer_x && !(parity & 1) ? nullptr : b.sc.xcoef2;
   l.status = b.sc.status;
   l.need_status = need;
   l.sig_part = v.sig;
@@ -996,10 +1011,10 @@ static int32_t enqueue_replacement(BicgSolve& b, int parity, hipStream_t st) {
   if (b.mixed)
     hipLaunchKernelGGL(k_ru_pre<float>, dim3(gru), dim3(256), 0, st, s->N, b.ru_chunks, nlr, rul, ruc,
                        (const int32_t*)b.sc.status, (int32_t)ST_RU_LO, (const double2*)b.sc.xcoef,
-                       (const int32_t*)b.sc.ru_par, parity, b.lo.Pb[0], b.lo.Pb[1], b.lo.X, b.Y);
+                       (const double2*)b.sc.xcoef2, (const int32_t*)b.sc.ru_par, parity, b.lo.Pb[0], b.lo.Pb[1], b.lo.X, b.Y);
   hipLaunchKernelGGL(k_ru_pre<double>, dim3(gru), dim3(256), 0, st, s->N, b.ru_chunks, nlr, rul, ruc,
                      (const int32_t*)b.sc.status, (int32_t)ST_RU_HI, (const double2*)b.sc.xcoef,
-                     (const int32_t*)b.sc.ru_par, parity, b.hi.Pb[0], b.hi.Pb[1], b.hi.X, b.Y);
+                     (const double2*)b.sc.xcoef2, (const int32_t*)b.sc.ru_par, parity, b.hi.Pb[0], b.hi.Pb[1], b.hi.X, b.Y);
   CBS_HIP(hipGetLastError());
   {
     StencilLaunch r{};
@@ -1040,7 +1055,7 @@ static int32_t enqueue_iter(BicgSolve& b, int parity, hipStream_t st) {
   if (b.mixed) CBS_TRY(enqueue_stencil_bra<float>(b, b.lo, ST_ACT_LO, parity, st));
   CBS_TRY(enqueue_stencil_bra<double>(b, b.hi, ST_ACT_HI, parity, st));
   hipLaunchKernelGGL(k_s1, dim3((b.nruns + 3) / 4), dim3(256), 0, st, b.sc, b.nruns, na, (const double2*)b.lo.sig,
-                     b.lo.ntiles, (const double2*)b.hi.sig, b.hi.ntiles, (const double2*)b.signl, parity);
+                     b.lo.ntiles, (const double2*)b.hi.sig, b.hi.ntiles, (const double2*)b.signl, parity, (int32_t)b.defer_x);
   CBS_HIP(hipGetLastError());
   if (b.mixed)
     CBS_TRY(launch_update<float>(s, b.nruns, b.lo.R, b.lo.Q, b.lo.KT, b.sc.alpha, b.sc.status, ST_ACT_LO,
@@ -1108,7 +1123,8 @@ static int32_t run_profiled(std::vector<BicgSolve*>& solves, hipStream_t st, int
       if (rc != CBS_OK) break;
       CBS_HIP(hipMemcpyAsync(hna, b.sc.n_active, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
       CBS_HIP(hipStreamSynchronize(st));
-      const double passes = (it == 0) ? 4.0 : 6.0;   // r, p_old (+ x) in; p_new, q (+ x) out
+      // r, p_old (+ x, and the direction before) in; p_new, q (+ x) out
+      const double passes = it == 0 ? 4.0 : !b.defer_x || it == 1 ? 6.0 : (it & 1) ? 7.0 : 4.0;
       float ms = 0;
       if (b.mixed && act[2 * i] > 0) {
         CBS_HIP(hipEventElapsedTime(&ms, b.lo.ev0, b.lo.ev1));

@@ -24,7 +24,8 @@ enum BicgState : int32_t {
 // Per-run scalars of the BiCG recurrences (device arrays, one entry per run).
 struct BicgScal {
   double2* alpha;
-  double2* xcoef;     // pending x update coefficient (applied by the next stencil pass)
+  double2* xcoef;     // pending x update coefficient of the latest direction
+  double2* xcoef2;    // and of the one before it, where x takes two at a time (defer_x)
   double2* beta;
   double2* rho;
   double2* rho_prev;
@@ -89,6 +90,7 @@ struct QueueState {
 struct BicgSolve {
   cbs_system* sys = nullptr;
   int32_t nruns = 0, L = 1, n_q = 0, nchunks = 0;
+  bool defer_x = false;    // x takes two directions on odd iterations, none on even ones
   int32_t ru_chunks = 0;   // work chunks per run of the residual replacement (ru_part)
   const double2* V = nullptr;       // [L][N]; run r uses right-hand side r % L
   const double2* Vd = nullptr;      // dual right-hand sides (same indexing), NULL: V

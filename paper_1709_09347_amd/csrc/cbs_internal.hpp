@@ -320,10 +320,11 @@ struct StencilLaunch {
   const void* pold;         // BiCG: previous search direction
   void* pnew;               // BiCG: new search direction
   void* q;                  // output: local part of P(z) p
-  void* x;                  // BiCG: x += xcoef * pold
+  void* x;                  // BiCG: x += xcoef2 * (the direction in pnew) + xcoef * pold
   const RunCoef* coef;      // [nruns]
   const double2* beta;      // BiCG [nruns]
   const double2* xcoef;     // BiCG [nruns]
+  const double2* xcoef2;    // BiCG [nruns] (not read in z segments), NULL: x waits for the next iteration
   const int32_t* status;    // [nruns] or NULL (no filter)
   int32_t need_status;      // blocks of runs whose status differs return at once
   double2* sig_part;        // BiCG [nruns * ntiles * segments]

@@ -13,8 +13,12 @@
 //    owning column only and carry the coefficients cm (= 1/z) and cp (= z); where few runs
 //    would leave CUs idle the march is cut into z segments, whose neighbouring planes inside
 //    the cell are read the same way;
-//  * BiCG mode fuses p_new = r + beta p_old (dual: conj(beta)), x += xcoef * p_old,
-//    the write of p_new and the local part of sigma = pt^H q;
+//  * BiCG mode fuses p_new = r + beta p_old (dual: conj(beta)), the write of p_new and the
+//    local part of sigma = pt^H q; on every second iteration x takes the last two directions,
+//    xcoef2 * p_older + xcoef * p_old, the older one read from the buffer that p_new is about to
+//    overwrite (seven passes over the vectors then, four on the others, where an update each time
+//    makes six: 48x48x32, 256 runs, complex128: 897 and 608 us, 781 each time before); in z segments (few runs, no
+//    registers to spare) x takes each direction on the next iteration;
 //  * blocks are renumbered so that consecutive tiles of a run land on one XCD, where
 //    they share the halo rows in that XCD's L2.
 #include <cstdlib>
@@ -42,6 +46,7 @@ struct StArgs {
   const RunCoef* coef;
   const double2* beta;
   const double2* xcoef;
+  const double2* xcoef2;  // NULL: an iteration without the x update
   const int32_t* status;
   int32_t need_status;
   double2* sig_part;
@@ -216,17 +221,41 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
   const cplx<C> c0b = ccast<C, double>(cf.c[3]), cpb = ccast<C, double>(cf.c[4]),
                 cmb = ccast<C, double>(cf.c[5]);
   const C Erun = (C)cf.E;
-  cplx<C> ba = mkc<C>(0, 0), bb = ba, xa = ba, xb = ba;
-  bool do_x = false;
+  cplx<C> ba = mkc<C>(0, 0), bb = ba, xa = ba, xb = ba, ya = ba, yb = ba;
+  bool do_x = false, do_1 = false, do_2 = false;   // x at all, with the old direction, with the older one
   if (BICG) {
     const double2 bt = a.beta[run];
     ba = mkc<C>((C)bt.x, (C)bt.y);
     bb = cconj<C>(ba);
-    const double2 xc = a.xcoef[run];
-    xa = mkc<C>((C)xc.x, (C)xc.y);
-    xb = cconj<C>(xa);
-    do_x = (xc.x != 0.0 || xc.y != 0.0);
+    if (a.xcoef2 != nullptr) {
+      const double2 xc = a.xcoef[run];
+      xa = mkc<C>((C)xc.x, (C)xc.y);
+      xb = cconj<C>(xa);
+      do_1 = (xc.x != 0.0 || xc.y != 0.0);
+      if (!SEG) {
+        const double2 yc = a.xcoef2[run];
+        ya = mkc<C>((C)yc.x, (C)yc.y);
+        yb = cconj<C>(ya);
+        do_2 = (yc.x != 0.0 || yc.y != 0.0);
+      }
+      do_x = do_1 || do_2;
+    }
   }
+  // x with the pending terms, older first, each rounded to storage as if applied by itself
+  auto x_update = [&](const Pair<R>& x0, const Pair<R>& older, const Pair<C>& old) {
+    Pair<C> xv = pcast<C, R>(x0);
+    if (!SEG && do_2) {
+      const Pair<C> z = pcast<C, R>(older);
+      xv.a = cfma<C>(xv.a, ya, z.a);
+      xv.b = cfma<C>(xv.b, yb, z.b);
+      xv = pcast<C, R>(pcast<R, C>(xv));
+    }
+    if (do_1) {
+      xv.a = cfma<C>(xv.a, xa, old.a);
+      xv.b = cfma<C>(xv.b, xb, old.b);
+    }
+    return pcast<R, C>(xv);
+  };
   const C kin = (C)a.kin;
   C cc[P + 1];
 #pragma unroll
@@ -252,7 +281,7 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
   // happen together.
   constexpr int PF = 2;
   const bool pipe = region <= PF * nthr;
-  Pair<R> pr_r[PF], pr_p[PF], pr_x[PF];
+  Pair<R> pr_r[PF], pr_p[PF], pr_x[PF], pr_z[PF];
   auto issue = [&](int mm) {
     const bool in = !SEG || (mm >= z0 && mm < z1);
     const int iz = !SEG ? mm : (mm < 0) ? mm + nz : (mm >= nz) ? mm - nz : mm;
@@ -271,7 +300,10 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
         pr_r[k] = a.rin[n];
         if (BICG) pr_p[k] = a.pold[n];
       }
-      if (BICG && in && do_x && (!SEG || e < region) && r >= P && r < P + TY && uy < ny) pr_x[k] = a.x[n];
+      if (BICG && in && do_x && (!SEG || e < region) && r >= P && r < P + TY && uy < ny) {
+        pr_x[k] = a.x[n];
+        if (!SEG && do_2) pr_z[k] = a.pnew[n];
+      }
     }
   };
   auto commit = [&](int mm, Pair<R>* buf) {
@@ -292,13 +324,8 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
         v.b = dir_fma<C>(v.b, bb, po.b);
         const Pair<R> vs = pcast<R, C>(v);
         if (r >= P && r < P + TY && uy < ny) {
+          if (do_x) a.x[n] = x_update(pr_x[k], pr_z[k], po);
           a.pnew[n] = vs;
-          if (do_x) {
-            Pair<C> xv = pcast<C, R>(pr_x[k]);
-            xv.a = cfma<C>(xv.a, xa, po.a);
-            xv.b = cfma<C>(xv.b, xb, po.b);
-            a.x[n] = pcast<R, C>(xv);
-          }
         }
         buf[e] = vs;
       } else {
@@ -336,13 +363,12 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
           v.b = dir_fma<C>(v.b, bb, po.b);
           const Pair<R> vs = pcast<R, C>(v);   // the stored direction is the one applied
           if (r >= P && r < P + TY && uy < ny) {
-            a.pnew[n] = vs;
             if (do_x) {
-              Pair<C> xv = pcast<C, R>(a.x[n]);
-              xv.a = cfma<C>(xv.a, xa, po.a);
-              xv.b = cfma<C>(xv.b, xb, po.b);
-              a.x[n] = pcast<R, C>(xv);
+              Pair<R> z;
+              if (!SEG && do_2) z = a.pnew[n];
+              a.x[n] = x_update(a.x[n], z, po);
             }
+            a.pnew[n] = vs;
           }
           buf[e] = vs;
         } else {
@@ -575,6 +601,7 @@ int32_t launch_stencil(const cbs_system* s, bool bicg, const StencilLaunch& l, i
   a.coef = l.coef;
   a.beta = l.beta;
   a.xcoef = l.xcoef;
+  a.xcoef2 = l.xcoef2;
   a.status = l.status;
   a.need_status = l.need_status;
   a.sig_part = l.sig_part;
