@@ -344,56 +344,71 @@ struct ApKet {
 // products are added through LDS in wave order and wave w updates vectors 2w and 2w + 1, lane =
 // point.  Groups outside every ball touch nothing.  The vector groups vary fastest: they share a
 // group's table slice in one XCD's L2.  48x48x32, 96 atoms, 32 vectors: 31 us in complex128 (the
-// vectors and 27 MB of table, 3.3 TB/s), 24 in complex64; one wave per group 31 and 28, one
+// vectors and 27 MB of table, 3.3 TB/s; 29 with two groups a workgroup), 24 (21) in complex64; one wave per group 31 and 28, one
 // thread per point and pair 115 and 61.
-template <typename R, typename C>
+// CB: groups of AP_VG vectors a workgroup (their columns share the table's loads).
+template <typename R, typename C, int CB>
 __global__ void __launch_bounds__(256) k_ap_ket(ApKet<R> a) {
   constexpr int KB = 2;   // keys per batch (4: one wave less per SIMD, 36 us)
   __shared__ C tile[4][KG][17];
   const int lb = remap_active(blockIdx.x, a.nlogical);
   if (lb < 0) return;
-  const int g = lb / a.nvg, vg = lb - g * a.nvg;
+  const int nwg = a.nvg / CB;   // workgroups of a point group
+  const int g = lb / nwg, vg0 = (lb - g * nwg) * CB;
   const int e0 = a.grp_off[g], e1 = a.grp_off[g + 1];
   if (e0 == e1) return;   // uniform over the workgroup
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nvec = min(AP_VG, a.nv - vg * AP_VG), ncol = 2 * nvec;
   // the vectors' values are requested first: their latency passes under the contraction
   const int64_t n = (int64_t)g * KG + lane, nc = min(n, a.N - 1);
-  cplx<R>* yp = a.y + (int64_t)vg * AP_VG * a.N + nc;
-  const cplx<R> y0 = yp[(int64_t)min(2 * wv, nvec - 1) * a.N], y1 = yp[(int64_t)min(2 * wv + 1, nvec - 1) * a.N];
   const int orow = lane & 15, ok4 = lane >> 4;
-  const R* kcol = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + (int64_t)ok4 * ncol + min(orow, ncol - 1);
-  typename apmf4<C>::T acc[4];
+  int nvec[CB], ncol[CB];
+  cplx<R>* yp[CB];
+  cplx<R> y0[CB], y1[CB];
+  const R* kcol[CB];
+  typename apmf4<C>::T acc[CB][4];
 #pragma unroll
-  for (int rb = 0; rb < 4; ++rb) acc[rb] = {0, 0, 0, 0};
+  for (int c = 0; c < CB; ++c) {
+    const int vg = vg0 + c;
+    nvec[c] = min(AP_VG, a.nv - vg * AP_VG);
+    ncol[c] = 2 * nvec[c];
+    yp[c] = a.y + (int64_t)vg * AP_VG * a.N + nc;
+    y0[c] = yp[c][(int64_t)min(2 * wv, nvec[c] - 1) * a.N];
+    y1[c] = yp[c][(int64_t)min(2 * wv + 1, nvec[c] - 1) * a.N];
+    kcol[c] = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + (int64_t)ok4 * ncol[c] + min(orow, ncol[c] - 1);
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) acc[c][rb] = {0, 0, 0, 0};
+  }
   for (int eb = e0; eb < e1; eb += 256) {
     // lane j holds this wave's key number j: entry eb + 4 j + wv of the group
     const int mine = eb + 4 * lane + wv;
     const int nk = min(64, (e1 - eb - wv + 3) >> 2);
     const int keyv = (mine < e1) ? a.grp_key[mine] : 0;
     const int maskv = (mine < e1) ? a.grp_mask[mine] : 0;
-    C kbA[KB], ubA[KB][4], kbB[KB], ubB[KB][4];
+    C kbA[KB][CB], ubA[KB][4], kbB[KB][CB], ubB[KB][4];
     int mA[KB], mB[KB];
-    auto load = [&](int j0, C (&kb)[KB], C (&ub)[KB][4], int (&m)[KB]) {
+    auto load = [&](int j0, C (&kb)[KB][CB], C (&ub)[KB][4], int (&m)[KB]) {
 #pragma unroll
       for (int j = 0; j < KB; ++j) {
         const bool valid = j0 + j < nk;   // wave-uniform
         const int jj = valid ? j0 + j : 0;
         const int key = __builtin_amdgcn_readlane(keyv, jj);
         m[j] = valid ? __builtin_amdgcn_readlane(maskv, jj) : 0;
-        kb[j] = (C)kcol[((key >> 2) * 3 + (key & 3)) * 4 * ncol];
+#pragma unroll
+        for (int c = 0; c < CB; ++c) kb[j][c] = (C)kcol[c][((key >> 2) * 3 + (key & 3)) * 4 * ncol[c]];
         const R* up = a.grp_u + ((int64_t)(eb + 4 * jj + wv) * KG + orow) * 4 + ok4;
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb) ub[j][rb] = ((m[j] >> rb) & 1) ? (C)up[64 * rb] : (C)0;
       }
     };
-    auto mma = [&](const C (&kb)[KB], const C (&ub)[KB][4], const int (&m)[KB]) {
+    auto mma = [&](const C (&kb)[KB][CB], const C (&ub)[KB][4], const int (&m)[KB]) {
 #pragma unroll
       for (int j = 0; j < KB; ++j)
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
-          if ((m[j] >> rb) & 1) acc[rb] = ap_mfma(ub[j][rb], kb[j], acc[rb]);
+          if ((m[j] >> rb) & 1)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) acc[c][rb] = ap_mfma(ub[j][rb], kb[j][c], acc[c][rb]);
     };
     load(0, kbA, ubA, mA);
     for (int j0 = 0; j0 < nk; j0 += 2 * KB) {
@@ -405,18 +420,23 @@ __global__ void __launch_bounds__(256) k_ap_ket(ApKet<R> a) {
     }
   }
 #pragma unroll
-  for (int rb = 0; rb < 4; ++rb)
+  for (int c = 0; c < CB; ++c) {
+    if (c > 0) __syncthreads();   // the tile of the columns before is read
 #pragma unroll
-    for (int v = 0; v < 4; ++v) tile[wv][16 * rb + mfma16_row<C>(lane, v)][orow] = acc[rb][v];
-  __syncthreads();
-  if (n >= a.N) return;
-  C t[4];
+    for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
-    t[c] = ((tile[0][lane][4 * wv + c] + tile[1][lane][4 * wv + c]) + tile[2][lane][4 * wv + c]) +
-           tile[3][lane][4 * wv + c];
-  if (2 * wv < nvec) yp[(int64_t)(2 * wv) * a.N] = mkc<R>((R)((C)y0.x + t[0]), (R)((C)y0.y + t[1]));
-  if (2 * wv + 1 < nvec) yp[(int64_t)(2 * wv + 1) * a.N] = mkc<R>((R)((C)y1.x + t[2]), (R)((C)y1.y + t[3]));
+      for (int v = 0; v < 4; ++v) tile[wv][16 * rb + mfma16_row<C>(lane, v)][orow] = acc[c][rb][v];
+    __syncthreads();
+    if (n >= a.N) continue;
+    C t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      t[q] = ((tile[0][lane][4 * wv + q] + tile[1][lane][4 * wv + q]) + tile[2][lane][4 * wv + q]) +
+             tile[3][lane][4 * wv + q];
+    if (2 * wv < nvec[c]) yp[c][(int64_t)(2 * wv) * a.N] = mkc<R>((R)((C)y0[c].x + t[0]), (R)((C)y0[c].y + t[1]));
+    if (2 * wv + 1 < nvec[c])
+      yp[c][(int64_t)(2 * wv + 1) * a.N] = mkc<R>((R)((C)y1[c].x + t[2]), (R)((C)y1[c].y + t[3]));
+  }
 }
 
 // ------------------------------------------------------------------ launches
@@ -589,14 +609,21 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
     k.nv = nv;
     k.nvg = (nv + AP_VG - 1) / AP_VG;
     k.N = s->N;
-    k.nlogical = (int32_t)((s->N + KG - 1) / KG) * k.nvg;
+    // two vector groups a workgroup where they pair up and enough workgroups remain (whole calls:
+    // 48x48x32, 32 vectors, 114 -> 112 us in complex128 and 79 -> 75 in complex64; 64x64x40, 64 vectors,
+    // 407 -> 378 and 248 -> 233; three groups 99 -> 102; 24x24x16, 24 vectors, 34.6 -> 35.9)
+    const int64_t ngroups = (s->N + KG - 1) / KG;
+    const int cb = k.nvg % 2 == 0 && ngroups * k.nvg >= 2048 ? 2 : 1;
+    k.nlogical = (int32_t)ngroups * (k.nvg / cb);
     k.grp_off = pr.grp_off;
     k.grp_key = pr.grp_key;
     k.grp_mask = pr.grp_mask;
     k.grp_u = f64 ? (const R*)pr.grp_u64 : (const R*)pr.grp_u32;
     k.kt = kt;
     k.y = y;
-    hipLaunchKernelGGL((k_ap_ket<R, C>), dim3((k.nlogical + 7) / 8 * 8), dim3(256), 0, st, k);
+    const dim3 grid((k.nlogical + 7) / 8 * 8);
+    if (cb == 2) hipLaunchKernelGGL((k_ap_ket<R, C, 2>), grid, dim3(256), 0, st, k);
+    else hipLaunchKernelGGL((k_ap_ket<R, C, 1>), grid, dim3(256), 0, st, k);
     CBS_HIP(hipGetLastError());
   }
   return CBS_OK;

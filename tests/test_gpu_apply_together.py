@@ -31,3 +31,23 @@ def test_items_shared_by_a_workgroup(cuda, atoms, nv, dtype):
     scale = np.abs(want).max(axis=1, keepdims=True) + 50 * np.abs(x).max(axis=1, keepdims=True)
     err = (np.abs(y - want) / scale).max()
     assert err <= (1e-13 if dtype == np.complex128 else 2e-6), err
+
+
+@pytest.mark.parametrize("dtype", [np.complex128, np.complex64])
+@pytest.mark.parametrize("nv", [9, 16, 31])
+def test_two_vector_groups_a_workgroup(cuda, nv, dtype):
+    # the product with the projectors takes two groups of eight vectors a workgroup from 2048
+    # (point group, vector group) pairs on: 65536 points make 1024 point groups
+    import torch
+    import paper_1709_09347_amd as cbs
+    sysw = W.make_system(41, 40, 41, 0.4, 4, 12, 811, 812, with_proj=True, r_c=2.0)
+    H = ham.build(sysw)
+    rng = np.random.default_rng(813)
+    x = (rng.standard_normal((nv, sysw.n)) + 1j * rng.standard_normal((nv, sysw.n))).astype(dtype)
+    z = np.exp(rng.uniform(-0.7, 0.7, nv) + 1j * rng.uniform(-np.pi, np.pi, nv))
+    print(nv, np.dtype(dtype).name, flush=True)
+    y = cbs.System.from_workload(sysw).apply(0.3, z, torch.from_numpy(x).to(cuda)).cpu().numpy().astype(np.complex128)
+    for v in (0, 7, 8, nv - 1):
+        want = H.apply(z[v], x[v].astype(np.complex128), 0.3)
+        err = np.abs(y[v] - want).max() / (np.abs(want).max() + 50 * np.abs(x[v]).max())
+        assert err <= (1e-13 if dtype == np.complex128 else 2e-6), err
