@@ -146,7 +146,8 @@ typedef struct {
   int64_t matvecs;          /* operator applications (vectors) in the solves */
   /* params.profile = 1 only: the BiCG stencil kernel, timed per launch with HIP events on
    * the stream it runs on; bytes are its algorithmic traffic (per active run: read r,
-   * p_old, x and write p_new, q, x once, plus V_loc once per launch).  stencil_*: the
+   * p_old and write p_new, q once, on the launches that update x also read x and the
+   * direction before p_old and write x, plus V_loc once per launch).  stencil_*: the
    * complex128 kernel, stencil_lo_*: the complex64 kernel (CBS_MIXED). */
   int64_t stencil_launches;
   double stencil_ms;
@@ -183,7 +184,8 @@ int64_t cbs_system_npoints(const cbs_system* sys);
  * solve, -1 for a NULL handle. */
 int64_t cbs_system_solve_id(const cbs_system* sys);
 /* Stencil tiling: tile_y[0] (complex128) and tile_y[1] (complex64) full-x rows per
- * workgroup, and the autotuner's timings ("" before the first solve tuned them;
+ * workgroup, and the autotuner's timings ("" before the first solve tuned them, and on
+ * cells small enough that a workgroup carries a run, which need no tuning;
  * CBS_AUTOTUNE=0 keeps the heuristic defaults).  The string lives until the next
  * solve on sys. */
 const char* cbs_system_tiling(const cbs_system* sys, int32_t* tile_y);
@@ -194,17 +196,16 @@ void cbs_params_default(cbs_params* p);
  * y_v = P(z_v) x_v for a batch of n_vec vectors (device, [n_vec][N], dtype
  * CBS_C128 or CBS_C64), z host [2*n_vec] (re, im), z_v != 0.  x and y must not
  * overlap.  complex64 runs the single-precision kernels end to end.  The
- * staging buffers come from the system's workspace (allocated on first use). */
+ * projector coefficients live in the system's workspace (allocated on first use). */
 int32_t cbs_apply(cbs_system* sys, double E, int32_t n_vec, const double* z,
                   int32_t dtype, const void* x, void* y, void* stream);
 
 /* Allocation-free variant of cbs_apply, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
- * Same arguments, kernels and result as cbs_apply; it calls no hipMalloc or hipFree: its
- * staging buffers (run coefficients, the two pair-interleaved vector buffers and the
- * projector coefficients) live in one fixed device array of CBS_APPLY_NOALLOC_BYTES per
- * device, held from the first cbs_system_create on that device until the process ends.
- * A call needs, each part rounded up to 256 bytes,
+ * Same arguments, kernels and result as cbs_apply; it calls no hipMalloc or hipFree: what
+ * it holds on the device (the projector coefficients) lives in one fixed array of
+ * CBS_APPLY_NOALLOC_BYTES per device, held from the first cbs_system_create on that device
+ * until the process ends.  A call is admitted by, each part rounded up to 256 bytes,
  *   ceil(n_vec/2) * 112  +  2 * ceil(n_vec/2) * N * b  +  ceil(n_vec/2) * n_atoms * 12 * b
  * bytes, b = 32 (CBS_C128) or 16 (CBS_C64); a larger call returns CBS_EINVAL before
  * touching the device.  Every call on one device shares the array and leaves its contents

@@ -1,8 +1,8 @@
 // Operator application without device allocation (cbs_apply_noalloc).
 //
-// cbs_apply stages its vectors in the system's grow-only workspace, which calls hipMalloc
-// the first time a size is seen.  This variant runs the same kernels with every staging
-// buffer inside one fixed device array, `scratch`, so a call allocates nothing: callers
+// cbs_apply keeps its projector coefficients in the system's grow-only workspace, which calls
+// hipMalloc the first time a size is seen.  This variant runs the same kernels with them
+// inside one fixed device array, `scratch`, so a call allocates nothing: callers
 // that cannot allocate (code under graph capture, tight serving loops) use it.
 //
 // The array is a file-scope __device__ symbol: in host code its name is only a stand-in,
