@@ -17,7 +17,7 @@
 //    local part of sigma = pt^H q; on every second iteration x takes the last two directions,
 //    xcoef2 * p_older + xcoef * p_old, the older one read from the buffer that p_new is about to
 //    overwrite (seven passes over the vectors then, four on the others, where an update each time
-//    makes six: 48x48x32, 256 runs, complex128: 897 and 608 us, 781 each time before); in z segments (few runs, no
+//    makes six: 48x48x32, 256 runs, complex128: 900 and 581 us, 781 each time before); in z segments (few runs, no
 //    registers to spare) x takes each direction on the next iteration;
 //  * blocks are renumbered so that consecutive tiles of a run land on one XCD, where
 //    they share the halo rows in that XCD's L2.
@@ -174,8 +174,9 @@ __device__ __forceinline__ void bicg_bra(const StArgs<R>& a, unsigned char* smem
 // R: storage precision of the vectors (and of the LDS plane); C: arithmetic precision.  SEG: the
 // march is cut into z segments, whose neighbouring planes are prefetched as the staged ones are
 // (whole tiles, 48 x 48 x 32 and 256 runs in complex128: 0.77 ms without that, 0.82 ms with it).
-// BRA: the launch begins with the workgroups of bicg_bra.
-template <typename R, typename C, int P, bool BICG, bool SEG, bool BRA>
+// BRA: the launch begins with the workgroups of bicg_bra.  XUP: x may be updated (without it the
+// launch of an even iteration takes 581 us, 610 with the code that it does not reach).
+template <typename R, typename C, int P, bool BICG, bool SEG, bool BRA, bool XUP>
 __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double2 red[8];
@@ -227,7 +228,7 @@ __global__ void __launch_bounds__(512) k_stencil(StArgs<R> a) {
     const double2 bt = a.beta[run];
     ba = mkc<C>((C)bt.x, (C)bt.y);
     bb = cconj<C>(ba);
-    if (a.xcoef2 != nullptr) {
+    if (XUP) {
       const double2 xc = a.xcoef[run];
       xa = mkc<C>((C)xc.x, (C)xc.y);
       xb = cconj<C>(xa);
@@ -555,15 +556,17 @@ static int32_t launch_pc(const cbs_system* s, StArgs<R>& a, hipStream_t st) {
       smem = std::max(smem, (size_t)a.nsub * 4 * 3 * 16 * sizeof(C));
       a.bgrid = ((a.nruns * a.n_atoms + a.nsub - 1) / a.nsub + 7) / 8 * 8;
       grid += a.bgrid;
-      hipLaunchKernelGGL((k_stencil<R, C, P, true, true, true>), dim3(grid), dim3(nthr), smem, st, a);
+      hipLaunchKernelGGL((k_stencil<R, C, P, true, true, true, true>), dim3(grid), dim3(nthr), smem, st, a);
       CBS_HIP(hipGetLastError());
       return CBS_OK;
     }
   }
   if (a.nzseg > 1)
-    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, true, false>), dim3(grid), dim3(nthr), smem, st, a);
+    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, true, false, BICG>), dim3(grid), dim3(nthr), smem, st, a);
+  else if (BICG && a.xcoef2 != nullptr)
+    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, false, false, BICG>), dim3(grid), dim3(nthr), smem, st, a);
   else
-    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, false, false>), dim3(grid), dim3(nthr), smem, st, a);
+    hipLaunchKernelGGL((k_stencil<R, C, P, BICG, false, false, false>), dim3(grid), dim3(nthr), smem, st, a);
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }
