@@ -9,7 +9,8 @@
 //   k_ap_local  y = finite differences, potential and cell phases of x (+ beta prev)
 //   k_ap_ket    y += sum_i u_{e,i} K[a_e][w_e][i], on the matrix cores, over the 64-point
 //               groups that lie in a ball
-// The bra is a launch of its own or the first workgroups of the local part's (bra_shape).
+// The bra is a launch of its own or the first workgroups of the local part's (bra_shape); the
+// smallest cells take all three in one (k_ap_cell).
 // The BiCG kernels (stencil.hip, nonlocal.hip) keep a run's primal and dual side by side; here
 // a vector stands alone, which halves the registers of the z queue and lets a cell be cut into
 // z segments until the chip is full.
@@ -439,7 +440,162 @@ __global__ void __launch_bounds__(256) k_ap_ket(ApKet<R> a) {
   }
 }
 
+// ------------------------------------------------------------------ small cells
+// All three parts by one workgroup a vector, a point a thread, with the vector and the projector
+// coefficients in LDS (at most 21 KB): on cells this small the time is the launches' and a chain of
+// latencies.  Whole calls in complex128: 5x5x8, 3 atoms, one vector 23.8 -> 20.2 us; 8x8x12, 6 atoms,
+// 64 vectors 31.7 -> 22.5.
+template <typename R>
+struct ApPoint {
+  const int32_t* off;
+  const int32_t* key;
+  const R* u;
+};
+
+// LDS: the coefficients [atom][w][i], the vector, the segments' sums [atom][w][i][re, im]
+static size_t ap_cell_lds(int64_t N, int32_t n_atoms, size_t elem, size_t real) {
+  return (size_t)n_atoms * 24 * real + (size_t)N * elem + (size_t)n_atoms * 24 * real;
+}
+
+template <typename R, typename C, int P, bool ADD>
+__global__ void __launch_bounds__(1024) k_ap_cell(ApLocal<R> a, ApBra<R> b, ApPoint<R> pt, ApCoef cf) {
+  extern __shared__ __align__(16) unsigned char ap_smem[];
+  const int N = (int)a.N, na = b.n_atoms, nx = a.nx, ny = a.ny, nz = a.nz;
+  cplx<C>* kc = reinterpret_cast<cplx<C>*>(ap_smem);
+  cplx<R>* xs = reinterpret_cast<cplx<R>*>(kc + 12 * na);
+  C* red = reinterpret_cast<C*>(xs + N);
+  const int v = blockIdx.x, tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool own = tid < N;
+  const int n = own ? tid : 0;
+  const int64_t base = (int64_t)v * N + n;
+  const cplx<R> x0 = a.x[base];
+  const C vl = (sizeof(C) == 8) ? (C)a.vloc64[n] : (C)a.vloc[n];
+  const int e0 = pt.off[n], e1 = own ? pt.off[n + 1] : e0;
+  cplx<R> add;
+  if constexpr (ADD) add = a.prev[base];
+  if (own) xs[n] = x0;
+  __syncthreads();
+  // bra: a wave per atom and cell shift
+  using U4 = typename vec4<R>::T;
+  const U4* ut = reinterpret_cast<const U4*>(b.u);
+  for (int it = wv; it < 3 * na; it += nthr >> 6) {
+    const int atom = it / 3, sg = it - 3 * atom;
+    const int lo = b.seg[4 * atom + sg], hi = b.seg[4 * atom + sg + 1];
+    C acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0;
+    const int last = hi - 1;
+    for (int eb = lo; eb < hi; eb += 256) {   // four entries a lane; past the segment: weight zero
+      int idx[4];
+      U4 u[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = min(eb + 64 * k + lane, last);
+        idx[k] = b.idx[e];
+        u[k] = ut[e];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const C o = eb + 64 * k + lane < hi ? (C)1 : (C)0;
+        const C w[4] = {o * (C)u[k].x, o * (C)u[k].y, o * (C)u[k].z, o * (C)u[k].w};
+        const cplx<R> t = xs[idx[k]];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[2 * i] += w[i] * (C)t.x;
+          acc[2 * i + 1] += w[i] * (C)t.y;
+        }
+      }
+    }
+    C t = 0;
+    if (lo < hi) t = wave_sums<8, C>(acc, lane);
+    if ((lane & 7) == 0) red[8 * it + (lane >> 3)] = t;
+  }
+  const cplx<C> c0 = ccast<C, double>(cf.c0[v]), cp = ccast<C, double>(cf.cp[v]), cm = ccast<C, double>(cf.cm[v]);
+  // local part at the own point
+  const int iz = n / (nx * ny), r = n - iz * nx * ny, iy = r / nx, ix = r - iy * nx;
+  const cplx<C> c = ccast<C, R>(x0);
+  cplx<C> t = cscale<C>(c, (C)2 * (C)a.c[0]), zs = cscale<C>(cmul<C>(c0, c), (C)a.zc[0]);
+  int xl = ix, xr = ix, yd = iy, yu = iy;
+#pragma unroll
+  for (int j = 1; j <= P; ++j) {
+    xl = xl == 0 ? nx - 1 : xl - 1;
+    xr = xr == nx - 1 ? 0 : xr + 1;
+    yd = yd == 0 ? ny - 1 : yd - 1;
+    yu = yu == ny - 1 ? 0 : yu + 1;
+    const cplx<C> l = ccast<C, R>(xs[n - ix + xl]), q = ccast<C, R>(xs[n - ix + xr]);
+    const cplx<C> d = ccast<C, R>(xs[n + (yd - iy) * nx]), u = ccast<C, R>(xs[n + (yu - iy) * nx]);
+    t = cfma_r<C>(t, (C)a.c[j], cadd<C>(cadd<C>(l, q), cadd<C>(d, u)));
+    const bool below = iz - j < 0, above = iz + j >= nz;
+    const cplx<C> sd = ccast<C, R>(xs[n + ((below ? nz : 0) - j) * nx * ny]);
+    const cplx<C> su = ccast<C, R>(xs[n + (j - (above ? nz : 0)) * nx * ny]);
+    const cplx<C> pd = mkc<C>(below ? cm.x : c0.x, below ? cm.y : c0.y);
+    const cplx<C> pu = mkc<C>(above ? cp.x : c0.x, above ? cp.y : c0.y);
+    zs = cfma_r<C>(zs, (C)a.zc[j], cadd<C>(cmul<C>(pd, sd), cmul<C>(pu, su)));
+  }
+  t = cfma_r<C>(cscale<C>(t, (C)a.kin), vl - (C)a.E, c);
+  cplx<C> y = cadd<C>(cmul<C>(c0, t), zs);
+  if constexpr (ADD) y = cfma_r<C>(y, (C)a.beta, ccast<C, R>(add));
+  __syncthreads();
+  for (int q = tid; q < 12 * na; q += nthr) {
+    const int atom = q / 12, w = (q - 12 * atom) >> 2, i = q & 3;
+    cplx<C> s = mkc<C>(0, 0);
+#pragma unroll
+    for (int w2 = 0; w2 < 3; ++w2) {
+      const int d = w2 - w;   // cell shift of the source relative to the entry
+      if (d > 1 || d < -1) continue;
+      const C* g = red + 8 * (3 * atom + w2) + 2 * i;
+      s = cfma<C>(s, mkc<C>(d == 0 ? c0.x : d == 1 ? cp.x : cm.x, d == 0 ? c0.y : d == 1 ? cp.y : cm.y), mkc<C>(g[0], g[1]));
+    }
+    kc[q] = cscale<C>(s, (C)b.coeff[4 * atom + i]);
+  }
+  __syncthreads();
+  // ket: four entries' loads at a time; past the point's list: weight zero
+  const U4* pu = reinterpret_cast<const U4*>(pt.u);
+  for (int eb = e0; eb < e1; eb += 4) {
+    int key[4];
+    U4 u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int e = min(eb + k, e1 - 1);
+      key[k] = pt.key[e];
+      u[k] = pu[e];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const C o = eb + k < e1 ? (C)1 : (C)0;
+      const cplx<C>* kk = kc + ((key[k] >> 2) * 3 + (key[k] & 3)) * 4;
+      const C w[4] = {o * (C)u[k].x, o * (C)u[k].y, o * (C)u[k].z, o * (C)u[k].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y = cfma_r<C>(y, w[i], kk[i]);
+    }
+  }
+  if (own) a.y[base] = ccast<R, C>(y);
+}
+
 // ------------------------------------------------------------------ launches
+// Whether k_ap_cell takes the call.  A point has a thread of its own, and one workgroup walks the
+// balls of all atoms, which costs more than the launch it saves when they are many or large (whole
+// calls in complex128, one vector, apart and in one: 5x5x8, 3 atoms 23.8 and 20.2 us; 8x8x12, 8 atoms
+// with 2100 ball entries 25.5 and 24.8; 10x10x10, 12 atoms with 3200 entries 25.6 both; 8x8x12,
+// 20 atoms with 1700 entries 25.7 and 26.4, 40 atoms with 10700 entries 27.9 and 39.5).
+static bool ap_cell_fits(const cbs_system* s) {
+  return s->N <= 1024 && s->proj.n_atoms > 0 && s->proj.n_atoms <= 12 && s->proj.nnz <= 2560;
+}
+
+template <typename R, typename C, int P>
+static void ap_cell_p(const ApLocal<R>& a, const ApBra<R>& b, const ApPoint<R>& pt, const ApCoef& cf, int32_t nv,
+                      size_t smem, hipStream_t st) {
+  const int nthr = std::max(((int)a.N + 63) / 64 * 64, 512);   // eight waves for the bra (256 or 1024: + 2 %)
+  if constexpr (sizeof(R) == 8) {
+    if (a.prev != nullptr) {
+      hipLaunchKernelGGL((k_ap_cell<R, C, P, true>), dim3(nv), dim3(nthr), smem, st, a, b, pt, cf);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_ap_cell<R, C, P, false>), dim3(nv), dim3(nthr), smem, st, a, b, pt, cf);
+}
+
 size_t apply_kt_bytes(const cbs_system* s, int32_t n_vec, size_t real_bytes) {
   const int64_t nv = std::min(n_vec, AP_VMAX);
   return (size_t)nv * s->proj.n_atoms * 24 * real_bytes;
@@ -534,18 +690,9 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
   const Projector& pr = s->proj;
   const bool f64 = std::is_same<R, double>::value;
   ApLocal<R> a;
-  int32_t ty = 1, nseg = 1;
-  ap_shape(s, nv, sizeof(cplx<R>), &ty, &nseg);
   a.nx = s->nx;
   a.ny = s->ny;
   a.nz = s->nz;
-  a.ty = ty;
-  a.ntiles = (s->ny + ty - 1) / ty;
-  a.zlen = (s->nz + nseg - 1) / nseg;
-  a.nseg = (s->nz + a.zlen - 1) / a.zlen;
-  a.nlogical = nv * a.ntiles * a.nseg;
-  const size_t one = (size_t)(ty + 2 * s->p) * s->nx * sizeof(cplx<R>);
-  a.nbuf = (2 * one <= 64 * 1024) ? 2 : 1;
   a.N = s->N;
   a.kin = -0.5 / (s->h * s->h);
   a.E = E;
@@ -559,23 +706,45 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
   a.x = x;
   a.prev = prev;
   a.y = y;
+  ApBra<R> b{};
+  b.n_atoms = pr.n_atoms;
+  b.nv = nv;
+  b.N = s->N;
+  b.seg = pr.seg;
+  b.idx = pr.ball_idx;
+  b.u = f64 ? (const R*)pr.ball_u64 : (const R*)pr.ball_u32;
+  b.coeff = f64 ? (const R*)pr.coeff64 : (const R*)pr.coeff32;
+  b.x = x;
+  b.kt = kt;
+  if (ap_cell_fits(s)) {
+    const ApPoint<R> pt{pr.pt_off, pr.pt_key, f64 ? (const R*)pr.pt_u64 : (const R*)pr.pt_u32};
+    const size_t smem = ap_cell_lds(s->N, pr.n_atoms, sizeof(cplx<R>), sizeof(C));
+    switch (s->p) {
+      case 1: ap_cell_p<R, C, 1>(a, b, pt, cf, nv, smem, st); break;
+      case 2: ap_cell_p<R, C, 2>(a, b, pt, cf, nv, smem, st); break;
+      case 3: ap_cell_p<R, C, 3>(a, b, pt, cf, nv, smem, st); break;
+      case 4: ap_cell_p<R, C, 4>(a, b, pt, cf, nv, smem, st); break;
+      default: set_error("unsupported finite-difference half-width %d", s->p); return CBS_EINVAL;
+    }
+    CBS_HIP(hipGetLastError());
+    return CBS_OK;
+  }
+  int32_t ty = 1, nseg = 1;
+  ap_shape(s, nv, sizeof(cplx<R>), &ty, &nseg);
+  a.ty = ty;
+  a.ntiles = (s->ny + ty - 1) / ty;
+  a.zlen = (s->nz + nseg - 1) / nseg;
+  a.nseg = (s->nz + a.zlen - 1) / a.zlen;
+  a.nlogical = nv * a.ntiles * a.nseg;
+  const size_t one = (size_t)(ty + 2 * s->p) * s->nx * sizeof(cplx<R>);
+  a.nbuf = (2 * one <= 64 * 1024) ? 2 : 1;
   ApGrid<R> g;
   g.nthr = (s->nx * ty + 63) / 64 * 64;
   g.smem = a.nbuf * one;
   g.vb = 0;
-  ApBra<R> b{};
   if (pr.n_atoms > 0) {
     bool together = false;
     const int vb = bra_shape(pr.n_atoms, nv, !f64, &together);
-    b.n_atoms = pr.n_atoms;
-    b.nv = nv;
-    b.N = s->N;
-    b.seg = pr.seg;
-    b.idx = pr.ball_idx;
-    b.u = f64 ? (const R*)pr.ball_u64 : (const R*)pr.ball_u32;
-    b.coeff = f64 ? (const R*)pr.coeff64 : (const R*)pr.coeff32;
-    b.x = x;
-    b.kt = kt;
     b.nvb = (nv + vb - 1) / vb;
     if (together) {
       g.vb = vb;
