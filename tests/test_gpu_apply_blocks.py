@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
 
 CELLS = {
     "ragged": lambda: W.make_system(7, 11, 13, 0.45, 8, 4, 301, 302, with_proj=True, r_c=1.6),
+    "ragged, several workgroups": lambda: W.make_system(9, 11, 13, 0.45, 8, 4, 301, 302, with_proj=True, r_c=1.6),
     "wide": lambda: W.make_system(200, 9, 6, 0.5, 8, 3, 303, 304, with_proj=True, r_c=1.2),
     "thin": lambda: W.make_system(1, 1, 4, 0.5, 8, 2, 305),
     "crowded": lambda: W.make_system(8, 8, 12, 0.4, 4, 300, 306, 307, with_proj=True, r_c=2.0),
@@ -62,6 +63,14 @@ def test_block_sizes(cuda, nv):
     _run(cuda, "ragged", nv, np.complex128, "apply")
     _run(cuda, "ragged", nv, np.complex64, "apply")
     _run(cuda, "ragged", nv, np.complex128, "parts")
+
+
+@pytest.mark.parametrize("nv", [1, 4, 9, 17, 65])
+def test_block_sizes_in_separate_launches(cuda, nv):
+    # past 1024 points the three parts are launches of their own
+    _run(cuda, "ragged, several workgroups", nv, np.complex128, "apply")
+    _run(cuda, "ragged, several workgroups", nv, np.complex64, "apply")
+    _run(cuda, "ragged, several workgroups", nv, np.complex128, "parts")
 
 
 @pytest.mark.parametrize("name", ["wide", "thin", "crowded", "local"])
