@@ -43,6 +43,7 @@
 
 #include "bicg.hpp"
 #include "cbs_internal.hpp"
+#include "chunks.hpp"
 
 namespace cbs {
 
@@ -905,7 +906,8 @@ int32_t bicg_alloc(BicgSolve& b, const char* tag) {
     b.nchunks = update_chunks(s, b.nruns);
     const int na = s->proj.n_atoms;
     CBS_TRY(ws_get(ws, (t + ".signl").c_str(), R * std::max(na, 1), &b.signl));
-    CBS_TRY(ws_get(ws, (t + ".upd").c_str(), R * b.nchunks * 4, &b.upd_part));
+    b.upd_len = update_part_len(b.nruns, b.nchunks);
+    CBS_TRY(ws_get(ws, (t + ".upd").c_str(), b.upd_len, &b.upd_part));
     b.bra_part = nullptr;
     if (s->bra_tile[0] > 0 || s->bra_tile[1] > 0) {
       unsigned char* bp = nullptr;
@@ -1059,9 +1061,9 @@ static int32_t enqueue_iter(BicgSolve& b, int parity, hipStream_t st) {
   CBS_HIP(hipGetLastError());
   if (b.mixed)
     CBS_TRY(launch_update<float>(s, b.nruns, b.lo.R, b.lo.Q, b.lo.KT, b.sc.alpha, b.sc.status, ST_ACT_LO,
-                                 b.upd_part, b.nchunks, st, b.sc.list, b.sc.n_active));
+                                 b.upd_part, b.upd_len, b.nchunks, st, b.sc.list, b.sc.n_active));
   CBS_TRY(launch_update<double>(s, b.nruns, b.hi.R, b.hi.Q, b.hi.KT, b.sc.alpha, b.sc.status, ST_ACT_HI,
-                                b.upd_part, b.nchunks, st, b.sc.list + b.nruns, b.sc.n_active + 1));
+                                b.upd_part, b.upd_len, b.nchunks, st, b.sc.list + b.nruns, b.sc.n_active + 1));
   hipLaunchKernelGGL(k_s2, dim3((b.nruns + 3) / 4), dim3(256), 0, st, b.sc, b.nruns, b.nchunks,
                      (const double*)b.upd_part, b.tol, b.max_iter, b.narrow_tol, b.ru_factor, b.lo_window,
                      b.div_factor, b.hist, b.hist_stride, b.hist_rows, parity);

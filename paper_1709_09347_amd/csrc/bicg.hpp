@@ -102,7 +102,8 @@ struct BicgSolve {
   BicgVecs<double> hi;              // complex128 phase (also the FP64 residual buffers)
   Pair<double>* Y = nullptr;        // solutions (primal, dual), complex128
   double2* signl = nullptr;
-  double* upd_part = nullptr;
+  double* upd_part = nullptr;     // partial sums of the update, upd_len doubles
+  size_t upd_len = 0;
   double* ru_part = nullptr;
   void* bra_part = nullptr;   // chunk sums of the chunked bra (NULL: the per-atom bra)
   BicgScal sc{};

@@ -354,16 +354,17 @@ int32_t launch_bra(const cbs_system* s, int32_t nruns, const void* v, const RunC
                    const int32_t* count = nullptr, bool short_list = false, void* tile_part = nullptr);
 size_t bra_tile_part_bytes(const cbs_system* s, int32_t nruns);
 
-// Fused pointwise kernels.
+// Fused pointwise kernels.  part holds part_len doubles; CBS_EINVAL if the partial sums of nruns
+// runs in nchunks chunks are more.
 template <typename R>
 int32_t launch_update(const cbs_system* s, int32_t nruns, void* r, const void* q, const void* kt,
                       const double2* alpha, const int32_t* status, int32_t need_status, double* part,
-                      int32_t nchunks, hipStream_t st, const int32_t* list = nullptr,
+                      size_t part_len, int32_t nchunks, hipStream_t st, const int32_t* list = nullptr,
                       const int32_t* count = nullptr);
 template <typename R>
 int32_t launch_ket_add(const cbs_system* s, int32_t nruns, void* q, const void* kt, hipStream_t st);
 
-int32_t update_chunks(const cbs_system* s, int32_t nruns);
+int32_t update_chunks(const cbs_system* s, int32_t nruns);   // chunks of a solve (chunks.hpp)
 
 // The operator on vector-major blocks (apply.hip): y_v = c0 (H0 - E) x_v + cp H+ x_v + cm H- x_v
 // (+ beta prev_v), coefficients on the host (passed as kernel arguments), kt: scratch of

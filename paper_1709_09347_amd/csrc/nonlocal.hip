@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "cbs_internal.hpp"
+#include "chunks.hpp"
 
 namespace cbs {
 
@@ -791,7 +792,7 @@ struct UpdArgs {
 // blocks.  One vector load brings a key's K operand for all four runs; keys go in
 // batches of four whose loads are issued while the previous batch is on the matrix cores.
 // The 64 x 16 result goes through LDS to lane = point for the update of r.
-constexpr int UR = 4;
+constexpr int UR = UPD_RUNS;
 
 template <typename R, typename C>
 __global__ void __launch_bounds__(256) k_update(UpdArgs<R> a) {
@@ -957,24 +958,23 @@ __global__ void __launch_bounds__(256) k_update(UpdArgs<R> a) {
   }
 }
 
-// The tuned chunk, halved down to a group of points per wave until there are two workgroups per CU:
-// 23 x 19 x 17 points, 30 runs: 21.6 us in chunks of 1024 points, 12.6 us in chunks of 256.
-int32_t update_chunks(const cbs_system* s, int32_t nruns) {
-  int64_t per = std::max<int64_t>(s->upd_pts, 256);
-  const int64_t rg = (nruns + UR - 1) / UR;
-  while (per > 256 && rg * ((s->N + per - 1) / per) < 512) per = std::max<int64_t>(per / 2, 256);
-  return (int32_t)((s->N + per - 1) / per);
-}
+int32_t update_chunks(const cbs_system* s, int32_t nruns) { return update_chunks_of(s->N, nruns, s->upd_pts); }
 
 template <typename R>
 int32_t launch_update(const cbs_system* s, int32_t nruns, void* r, const void* q, const void* kt,
                       const double2* alpha, const int32_t* status, int32_t need_status, double* part,
-                      int32_t nchunks, hipStream_t st, const int32_t* list, const int32_t* count) {
+                      size_t part_len, int32_t nchunks, hipStream_t st, const int32_t* list,
+                      const int32_t* count) {
   if ((list == nullptr) != (count == nullptr)) {
     set_error("launch_update: a run list needs its count");
     return CBS_EINVAL;
   }
   if (nruns <= 0) return CBS_OK;
+  if (nchunks < 1 || update_part_len(nruns, nchunks) > part_len) {
+    set_error("launch_update: %d runs in %d chunks write %zu partial sums, the buffer holds %zu", nruns, nchunks,
+              update_part_len(nruns, nchunks), part_len);
+    return CBS_EINVAL;
+  }
   UpdArgs<R> a;
   a.need_status = need_status;
   a.nchunks = nchunks;
@@ -1037,8 +1037,8 @@ int32_t launch_ket_add(const cbs_system* s, int32_t nruns, void* q, const void* 
                                  const int32_t*, int32_t, void*, double2*, hipStream_t, bool,     \
                                  const int32_t*, const int32_t*, bool, void*);                    \
   template int32_t launch_update<R>(const cbs_system*, int32_t, void*, const void*, const void*,  \
-                                    const double2*, const int32_t*, int32_t, double*, int32_t,    \
-                                    hipStream_t, const int32_t*, const int32_t*);                 \
+                                    const double2*, const int32_t*, int32_t, double*, size_t,     \
+                                    int32_t, hipStream_t, const int32_t*, const int32_t*);        \
   template int32_t launch_ket_add<R>(const cbs_system*, int32_t, void*, const void*, hipStream_t);
 INST(double)
 INST(float)

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "cbs_internal.hpp"
+#include "chunks.hpp"
 
 namespace cbs {
 
@@ -735,7 +736,8 @@ static int32_t tune_nonlocal(cbs_system* s, hipStream_t st, bool tune_update, st
   CBS_TRY(ws_get(s->ws, "tune.coef", (size_t)nr, &coef));
   CBS_TRY(ws_get(s->ws, "tune.dsc", (size_t)nr * (na + 1), &dsc));
   CBS_TRY(ws_get(s->ws, "tune.status", (size_t)nr, &status));
-  CBS_TRY(ws_get(s->ws, "tune.part", (size_t)nr * ((s->N + 1023) / 1024) * 4, &part));
+  const size_t part_len = tune_part_len(s->N, nr);
+  CBS_TRY(ws_get(s->ws, "tune.part", part_len, &part));
   CBS_HIP(hipMemsetAsync(kt, 0, (size_t)nr * na * 12 * sizeof(Pair<R>), st));
   CBS_HIP(hipMemsetAsync(dsc, 0, (size_t)nr * (na + 1) * sizeof(double2), st));
   hipEvent_t e0, e1;
@@ -813,13 +815,12 @@ static int32_t tune_nonlocal(cbs_system* s, hipStream_t st, bool tune_update, st
   if (tune_update) {
     best = 1e30f;
     int bpts = 2048;
-    for (int pts : {1024, 2048, 4096}) {
-      s->upd_pts = pts;
-      const int nch = update_chunks(s, nr);
-      CBS_TRY(launch_update<R>(s, nr, buf, buf + (size_t)nr * s->N, kt, dsc, status, 0, part, nch, st));
+    for (int pts : UPD_PTS_TUNE) {
+      const int nch = tune_chunks(s->N, pts);
+      CBS_TRY(launch_update<R>(s, nr, buf, buf + (size_t)nr * s->N, kt, dsc, status, 0, part, part_len, nch, st));
       CBS_HIP(hipEventRecord(e0, st));
       for (int k = 0; k < 3; ++k)
-        CBS_TRY(launch_update<R>(s, nr, buf, buf + (size_t)nr * s->N, kt, dsc, status, 0, part, nch, st));
+        CBS_TRY(launch_update<R>(s, nr, buf, buf + (size_t)nr * s->N, kt, dsc, status, 0, part, part_len, nch, st));
       CBS_HIP(hipEventRecord(e1, st));
       CBS_HIP(hipEventSynchronize(e1));
       float ms = 0;
