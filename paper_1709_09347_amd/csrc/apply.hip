@@ -18,6 +18,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "apply_shape.hpp"
 #include "cbs_internal.hpp"
 
 namespace cbs {
@@ -601,39 +602,6 @@ size_t apply_kt_bytes(const cbs_system* s, int32_t n_vec, size_t real_bytes) {
   return (size_t)nv * s->proj.n_atoms * 24 * real_bytes;
 }
 
-// Rows per workgroup and z segments of k_ap_local: the pair with the least modelled time.  A
-// workgroup's march costs its owned planes (staged rows with their halo, plus the points worked
-// on) and 2p halo columns, or, when few points are in flight, one latency a plane (as long as
-// 1500 points take); a CU holds 16 waves, and a launch runs in whole rounds of the chip.  Against
-// every (rows, segments) pair on thirteen cells and block sizes from 8x8x12 to 160x160x48 the
-// choice is within 6 % of the fastest call (19 % on 21x70x16), where the worst pairs take twice
-// as long: 96x96x32, 24 vectors: 76 us with 10 rows in one segment, 127 us with 8.
-static void ap_shape(const cbs_system* s, int32_t nv, size_t elem, int32_t* ty, int32_t* nseg) {
-  const int p = s->p, nx = s->nx;
-  double best = 0;
-  *ty = *nseg = 1;
-  for (int t = 1; t <= s->ny && (t == 1 || nx * t <= 1024); ++t) {
-    if (t > 1 && (size_t)(t + 2 * p) * nx * elem > 64 * 1024) break;
-    const int ntiles = (s->ny + t - 1) / t, waves = (nx * t + 63) / 64, percu = std::max(1, 16 / waves);
-    const bool pipe = (t + 2 * p) * nx <= 128 * waves;
-    for (int ns = 1; ns <= std::max(1, s->nz / p); ++ns) {
-      const int zlen = (s->nz + ns - 1) / ns;
-      const int64_t nb = (int64_t)nv * ntiles * ((s->nz + zlen - 1) / zlen);
-      const int64_t rounds = (nb + 256 * percu - 1) / (256 * percu);
-      const double conc = (double)std::min<int64_t>(percu, (nb + 255) / 256);   // workgroups sharing a CU
-      const double plane = (t + 2 * p) * nx + 2.0 * nx * t, halo = (double)nx * t;
-      const double work = conc * (zlen * plane + 0.5 * 2 * p * halo);
-      const double lat = 1500.0 * (zlen * (pipe ? 1.0 : 2.0) + 2 * p * 0.25);
-      const double cost = (double)rounds * std::max(work, lat);
-      if (best == 0 || cost < best) {
-        best = cost;
-        *ty = t;
-        *nseg = ns;
-      }
-    }
-  }
-}
-
 // Vectors per bra item, and whether the bra shares the local part's launch: neither reads what the
 // other writes, so up to 576 items of two vectors the chip has room for both at once and a launch is
 // saved (48x48x32, 96 atoms, 8 complex128 vectors, whole call: 57 us, apart 64; 45x37x29, 60 atoms,
@@ -729,11 +697,11 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
     CBS_HIP(hipGetLastError());
     return CBS_OK;
   }
-  int32_t ty = 1, nseg = 1;
-  ap_shape(s, nv, sizeof(cplx<R>), &ty, &nseg);
+  const ApplyShape shape = apply_shape(s->nx, s->ny, s->nz, s->p, nv, sizeof(cplx<R>));
+  const int32_t ty = shape.ty;
   a.ty = ty;
   a.ntiles = (s->ny + ty - 1) / ty;
-  a.zlen = (s->nz + nseg - 1) / nseg;
+  a.zlen = (s->nz + shape.nseg - 1) / shape.nseg;
   a.nseg = (s->nz + a.zlen - 1) / a.zlen;
   a.nlogical = nv * a.ntiles * a.nseg;
   const size_t one = (size_t)(ty + 2 * s->p) * s->nx * sizeof(cplx<R>);
