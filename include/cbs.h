@@ -195,7 +195,9 @@ void cbs_params_default(cbs_params* p);
 /* ---- operator (Eq. 4) --------------------------------------------------
  * y_v = P(z_v) x_v for a batch of n_vec vectors (device, [n_vec][N], dtype
  * CBS_C128 or CBS_C64), z host [2*n_vec] (re, im), z_v != 0.  x and y must not
- * overlap.  complex64 runs the single-precision kernels end to end.  The
+ * overlap.  complex64 runs the single-precision kernels end to end.  A value
+ * of x that is not finite reaches the points whose sums it enters (its stencil neighbours,
+ * the balls that hold it) and no others.  The
  * projector coefficients live in the system's workspace (allocated on first use). */
 int32_t cbs_apply(cbs_system* sys, double E, int32_t n_vec, const double* z,
                   int32_t dtype, const void* x, void* y, void* stream);

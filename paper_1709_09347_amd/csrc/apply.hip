@@ -337,14 +337,41 @@ struct ApKet {
   const R* grp_u;
   const R* kt;
   cplx<R>* y;
+  // the point's own list, for K that is not finite
+  const int32_t* pt_off;
+  const int32_t* pt_key;
+  const R* pt_u;
 };
+
+// The ket at point n of one vector (columns col and col + 1 of its group) over the balls that hold the
+// point.
+template <typename R, typename C>
+__device__ void ap_ket_point(const ApKet<R>& a, int64_t n, int vg, int ncol, int col, C& re, C& im) {
+  using U4 = typename vec4<R>::T;
+  const R* kt = a.kt + (int64_t)vg * a.n_atoms * 12 * 2 * AP_VG + col;
+  re = im = 0;
+#pragma nounroll
+  for (int e = a.pt_off[n]; e < a.pt_off[n + 1]; ++e) {
+    const int key = a.pt_key[e];
+    const U4 u = reinterpret_cast<const U4*>(a.pt_u)[e];
+    const R* k = kt + (int64_t)((key >> 2) * 3 + (key & 3)) * 4 * ncol;
+    const C us[4] = {(C)u.x, (C)u.y, (C)u.z, (C)u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      re += us[i] * (C)k[i * ncol];
+      im += us[i] * (C)k[i * ncol + 1];
+    }
+  }
+}
 
 // A workgroup adds the ket of one 64-point group to AP_VG vectors: U [64 points x 4] (grouped
 // table) times K [4 x 16 columns] summed over the group's keys with MFMA 16x16x4 in four 16-point
 // row blocks (those the key's mask names).  A group in the middle of many balls has sixty keys and
 // each batch of them is one memory latency, so the four waves take every fourth key; their
 // products are added through LDS in wave order and wave w updates vectors 2w and 2w + 1, lane =
-// point.  Groups outside every ball touch nothing.  The vector groups vary fastest: they share a
+// point.  Groups outside every ball touch nothing.  Where a sum is not finite the point's own list gives
+// it, so that a NaN in a ball reaches the points of the balls that hold it and no others of their
+// groups.  The vector groups vary fastest: they share a
 // group's table slice in one XCD's L2.  48x48x32, 96 atoms, 32 vectors: 31 us in complex128 (the
 // vectors and 27 MB of table, 3.3 TB/s; 29 with two groups a workgroup), 24 (21) in complex64; one wave per group 31 and 28, one
 // thread per point and pair 115 and 61.
@@ -435,6 +462,11 @@ __global__ void __launch_bounds__(256) k_ap_ket(ApKet<R> a) {
     for (int q = 0; q < 4; ++q)
       t[q] = ((tile[0][lane][4 * wv + q] + tile[1][lane][4 * wv + q]) + tile[2][lane][4 * wv + q]) +
              tile[3][lane][4 * wv + q];
+    // zero table entries take part in the products, and zero times an infinite or undefined K is not zero
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (!((t[2 * h] - t[2 * h]) + (t[2 * h + 1] - t[2 * h + 1]) == (C)0))
+        ap_ket_point<R, C>(a, n, vg0 + c, ncol[c], min(4 * wv + 2 * h, ncol[c] - 2), t[2 * h], t[2 * h + 1]);
     if (2 * wv < nvec[c]) yp[c][(int64_t)(2 * wv) * a.N] = mkc<R>((R)((C)y0[c].x + t[0]), (R)((C)y0[c].y + t[1]));
     if (2 * wv + 1 < nvec[c])
       yp[c][(int64_t)(2 * wv + 1) * a.N] = mkc<R>((R)((C)y1[c].x + t[2]), (R)((C)y1[c].y + t[3]));
@@ -758,6 +790,9 @@ static int32_t ap_launch(const cbs_system* s, double E, int32_t nv, const ApCoef
     k.grp_u = f64 ? (const R*)pr.grp_u64 : (const R*)pr.grp_u32;
     k.kt = kt;
     k.y = y;
+    k.pt_off = pr.pt_off;
+    k.pt_key = pr.pt_key;
+    k.pt_u = f64 ? (const R*)pr.pt_u64 : (const R*)pr.pt_u32;
     const dim3 grid((k.nlogical + 7) / 8 * 8);
     if (cb == 2) hipLaunchKernelGGL((k_ap_ket<R, C, 2>), grid, dim3(256), 0, st, k);
     else hipLaunchKernelGGL((k_ap_ket<R, C, 1>), grid, dim3(256), 0, st, k);
