@@ -571,11 +571,17 @@ __device__ __forceinline__ double rsqrt1(double x) {
   return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
+// The power of two that a matrix whose largest column has the norm nx is divided by, 0 if there is none:
+// the sweeps multiply squares of norms with each other, which overflows past 1e77 otherwise.
+__device__ __forceinline__ int sv_exponent(double nx) {
+  return nx > 0 && nx <= 1.79769313486231571e308 ? ilogb(nx) : 0;
+}
+
 constexpr int SV_T = 1024;
 constexpr size_t SV_LDS = 150 * 1024;   // columns of a block pair (or the whole matrix in the QR)
 
-// Pivoted Householder QR of A (n x n): X = R^H (lower triangular), piv[k]: the column of A taken
-// k-th.  One workgroup; a lane owns CPL columns, a wave 16 rows of them, all in registers, so that the
+// Pivoted Householder QR of A (n x n): X = R^H (lower triangular) divided by 2^piv[n], piv[k]: the
+// column of A taken k-th.  One workgroup; a lane owns CPL columns, a wave 16 rows of them, all in registers, so that the
 // inner products with the reflector are sums over a lane's own rows and then over the waves; the
 // reflector's rows are read from the pivot's lane.  A wave instruction takes four cycles whatever it
 // is for, so the parts that every wave repeats (pivot, reflector) want few waves: with a column per
@@ -584,11 +590,12 @@ template <int CPL>
 __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, int32_t lda, c64* X, int32_t* piv) {
   A += blockIdx.y * (int64_t)lda * n;
   X += blockIdx.y * (int64_t)n * n;
-  piv += blockIdx.y * n;
+  piv += blockIdx.y * (n + 1);
   constexpr int NW = 4 * CPL, RW = 16;
   __shared__ double pn[NW][64 * CPL];   // per wave: squared norms of the columns' remaining rows
   __shared__ c64 pd[NW][64 * CPL];      // per wave: products with the reflector
   __shared__ c64 rowk[64 * CPL];        // row k
+  int ex = 0;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i0 = wv * RW;
   c64 m[CPL][RW];
   int pos[CPL];   // step at which the column was taken, n: not yet
@@ -627,6 +634,7 @@ __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, i
     const double nx2 = lane_of(CPL == 1 ? nrm[0] : (pc ? nrm[CPL - 1] : nrm[0]), pl);
     const c64 xk = rowk[p];
     const double nx = sqrt(nx2), ak = sqrt(cabs2<double>(xk));
+    if (k == 0) ex = sv_exponent(nx);
     const c64 ph = ak > 0 ? make_double2(xk.x / ak, xk.y / ak) : make_double2(1, 0);
     const c64 alpha = zscale(ph, -nx);
     const double vv = nx2 + nx * ak, b = vv > 0 ? 1.0 / vv : 0.0;
@@ -673,12 +681,15 @@ __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, i
     __syncthreads();
   }
   // R[i][column] is the conjugate of X[position of the column][i]
+  if (threadIdx.x == 0) piv[n] = ex;
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     if (lane + 64 * c >= n) continue;
 #pragma unroll
     for (int r = 0; r < RW; ++r)
-      if (i0 + r < n) X[pos[c] + (int64_t)(i0 + r) * n] = pos[c] >= i0 + r ? zconj(m[c][r]) : make_double2(0, 0);
+      if (i0 + r < n)
+        X[pos[c] + (int64_t)(i0 + r) * n] = pos[c] >= i0 + r ? make_double2(ldexp(m[c][r].x, -ex), -ldexp(m[c][r].y, -ex))
+                                                            : make_double2(0, 0);
   }
 }
 
@@ -691,12 +702,13 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
   A += blockIdx.y * (int64_t)lda * n;
   M += blockIdx.y * (int64_t)n * n;
   X += blockIdx.y * (int64_t)n * n;
-  piv += blockIdx.y * n;
+  piv += blockIdx.y * (n + 1);
   __shared__ double cnb[2][64 * RP];   // squared norms of the remaining parts, -1: taken (this step's, the next's)
   __shared__ int32_t order[64 * RP];
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int CB = 4;
   const int NW = blockDim.x >> 6;
+  int ex = 0;
   for (int j = wv; j < n; j += NW) {
     double t = 0;
     for (int i = lane; i < n; i += 64) {
@@ -736,6 +748,7 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
     nx2 = wave_sum_dpp(nx2);
     const c64 xk = M[k + p * n];
     const double nx = sqrt(nx2), ak = sqrt(cabs2<double>(xk));
+    if (k == 0) ex = sv_exponent(nx);
     const c64 ph = ak > 0 ? make_double2(xk.x / ak, xk.y / ak) : make_double2(1, 0);
     const c64 alpha = zscale(ph, -nx);
     // |v|^2 = 2 (nx^2 + nx |x_k|)
@@ -784,9 +797,12 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
   }
   __syncthreads();
   // X[j][k] = conj(R[k][j]), R[k][j] = M[k][order[j]] for j >= k
+  if (tid == 0) piv[n] = ex;
   for (int t = tid; t < n * n; t += blockDim.x) {
     const int j = t % n, k = t / n;
-    X[j + k * n] = j >= k ? zconj(M[k + order[j] * n]) : make_double2(0, 0);
+    c64 v = make_double2(0, 0);
+    if (j >= k) v = zconj(M[k + order[j] * n]);
+    X[j + k * n] = make_double2(ldexp(v.x, -ex), ldexp(v.y, -ex));
   }
 }
 
@@ -909,6 +925,7 @@ __global__ void k_svd_copy(int32_t n, const c64* A, int32_t lda, c64* X, int32_t
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t < n * n) X[t] = A[t % n + (int64_t)(t / n) * lda];
   if (t < n) piv[t] = t;
+  if (t == 0) piv[n] = 0;
 }
 
 __global__ void k_svd_clear(int32_t n, unsigned long long* flags) {
@@ -916,12 +933,12 @@ __global__ void k_svd_clear(int32_t n, unsigned long long* flags) {
 }
 
 // sigma (descending, with its permutation) and W = P U: column j of W has the normalised column j
-// of X in the rows piv.
+// of X in the rows piv; sigma is multiplied by 2^piv[n].
 __global__ void __launch_bounds__(SV_T) k_svd_right(int32_t n, const c64* X, const int32_t* piv, c64* W, int32_t ldw,
                                                     double* sigma, int32_t* perm) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   X += blockIdx.y * (int64_t)n * n;
-  piv += blockIdx.y * n;
+  piv += blockIdx.y * (n + 1);
   W += blockIdx.y * (int64_t)ldw * n;
   sigma += blockIdx.y * 1024;
   perm += blockIdx.y * 512;
@@ -929,7 +946,7 @@ __global__ void __launch_bounds__(SV_T) k_svd_right(int32_t n, const c64* X, con
     double t = 0;
     for (int i = lane; i < n; i += 64) t += cabs2<double>(X[i + j * n]);
     t = sqrt(wave_sum_dpp(t));
-    if (lane == 0) sigma[512 + j] = t;
+    if (lane == 0) sigma[512 + j] = ldexp(t, piv[n]);
     const double inv = t > 0 ? 1.0 / t : 0.0;
     for (int i = lane; i < n; i += 64) W[piv[i] + (int64_t)j * ldw] = zscale(X[i + j * n], inv);
   }
@@ -1397,7 +1414,7 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
   int32_t* piv = nullptr;
   unsigned long long* flags = nullptr;
   CBS_TRY(ws_get(s->ws, "svd.X", (size_t)nbatch * n * n, &X));
-  CBS_TRY(ws_get(s->ws, "svd.piv", (size_t)nbatch * n, &piv));
+  CBS_TRY(ws_get(s->ws, "svd.piv", (size_t)nbatch * (n + 1), &piv));
   CBS_TRY(ws_get(s->ws, "svd.flag", (size_t)nbatch * MAXS, &flags));
   if (hermitian) {
     if (nbatch != 1) {
