@@ -57,9 +57,9 @@ enum {
   CBS_ERANK = -6,       /* Hankel rank reached L*M: subspace too small (results written) */
   CBS_ETOOMANY = -7,    /* more eigenvalues than max_eigs (count written) */
   CBS_ENONFINITE = -8,  /* non-finite moments (a linear solve diverged); no eigenpairs */
-  CBS_EEIG = -9         /* a small dense step of the extraction failed (QR iteration of the
-                           reduced eigenproblem, Cholesky QR of the Ritz basis or the LU of the
-                           linearised projected QEP); no eigenpairs */
+  CBS_EEIG = -9         /* a small dense step of the extraction failed (SVD of the Hankel matrix, QR
+                           iteration of the reduced eigenproblem, Cholesky QR of the Ritz basis or
+                           the LU of the linearised projected QEP); no eigenpairs */
 };
 
 enum { CBS_C128 = 0, CBS_C64 = 1 };          /* element type of cbs_apply vectors */

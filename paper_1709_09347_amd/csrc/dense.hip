@@ -933,15 +933,19 @@ __global__ void k_svd_clear(int32_t n, unsigned long long* flags) {
 }
 
 // sigma (descending, with its permutation) and W = P U: column j of W has the normalised column j
-// of X in the rows piv; sigma is multiplied by 2^piv[n].
+// of X in the rows piv; sigma is multiplied by 2^piv[n].  sigma[SV_STATE]: 0, or 1 if the sweep `last`
+// was run and still rotated (a sweep after the converged one leaves its flag at zero).
 __global__ void __launch_bounds__(SV_T) k_svd_right(int32_t n, const c64* X, const int32_t* piv, c64* W, int32_t ldw,
-                                                    double* sigma, int32_t* perm) {
+                                                    double* sigma, int32_t* perm, const unsigned long long* flags,
+                                                    int32_t last) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   X += blockIdx.y * (int64_t)n * n;
   piv += blockIdx.y * (n + 1);
   W += blockIdx.y * (int64_t)ldw * n;
   sigma += blockIdx.y * 1024;
   perm += blockIdx.y * 512;
+  if (tid == 0)
+    sigma[SV_STATE] = __longlong_as_double((long long)flags[blockIdx.y * SV_SWEEPS + last]) >= SV_TOL2 ? 1.0 : 0.0;
   for (int j = wv; j < n; j += SV_T / 64) {
     double t = 0;
     for (int i = lane; i < n; i += 64) t += cabs2<double>(X[i + j * n]);
@@ -1410,6 +1414,8 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
     return CBS_EINVAL;
   }
   constexpr int MAXS = SV_SWEEPS, BATCH = 6;
+  int limit = MAXS;   // CBS_SVD_SWEEPS=<n>: at most n sweeps (a test of what a factorisation that needs more reports)
+  if (const char* e = getenv("CBS_SVD_SWEEPS")) limit = std::max(1, std::min(atoi(e), MAXS));
   c64* X = nullptr;
   int32_t* piv = nullptr;
   unsigned long long* flags = nullptr;
@@ -1459,10 +1465,11 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
   CBS_HIP(hipGetLastError());
   int sweeps = 0;
   if (nb == 2) {
-    CBS_TRY(sweep_launch(0, 0, MAXS));
+    CBS_TRY(sweep_launch(0, 0, limit));
   } else {
-    for (int s0 = 0; s0 < MAXS; s0 += BATCH) {
-      for (int sw = s0; sw < s0 + BATCH; ++sw)
+    for (int s0 = 0; s0 < limit; s0 += BATCH) {
+      const int s1 = std::min(s0 + BATCH, limit);
+      for (int sw = s0; sw < s1; ++sw)
         for (int r = 0; r < nb - 1; ++r) CBS_TRY(sweep_launch(r, sw, 1));
       std::vector<unsigned long long> h((size_t)nbatch * MAXS);
       CBS_HIP(hipMemcpyAsync(h.data(), flags, h.size() * sizeof(h[0]), hipMemcpyDeviceToHost, st));
@@ -1470,7 +1477,7 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
       bool done = true;
       for (int b = 0; b < nbatch; ++b) {
         bool one = false;
-        for (int k = s0; k < s0 + BATCH && !one; ++k) {
+        for (int k = s0; k < s1 && !one; ++k) {
           double om = 0;
           std::memcpy(&om, &h[(size_t)b * MAXS + k], sizeof(om));
           sweeps = std::max(sweeps, k + 1);
@@ -1484,7 +1491,7 @@ int32_t svd_right(cbs_system* s, int32_t n, const c64* A, int32_t lda, c64* W, i
   if (const char* v = getenv("CBS_VERBOSE"))
     if (v[0] == '3') fprintf(stderr, "[cbs] svd: order %d, %d blocks of %d, %d sweeps\n", n, nb, bs, sweeps);
   hipLaunchKernelGGL(k_svd_right, dim3(1, nbatch), dim3(SV_T), 0, st, n, (const c64*)X, (const int32_t*)piv, W, ldw, sigma,
-                     perm);
+                     perm, (const unsigned long long*)flags, nb == 2 ? 0 : limit - 1);
   CBS_HIP(hipGetLastError());
   return CBS_OK;
 }

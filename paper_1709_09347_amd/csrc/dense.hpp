@@ -20,7 +20,8 @@ int32_t small_gemm(int32_t m, int32_t n, int32_t k, const double2* A, int32_t ld
 int32_t svd(int32_t n, double2* A, int32_t lda, double2* V, int32_t ldv, double* sigma, int32_t* perm,
             hipStream_t st);
 // sigma, perm and W alone (A kept): faster, for callers that need no U; nbatch matrices lda n apart (W:
-// ldw n, sigma: 1024, perm: 512).
+// ldw n, sigma: 1024, perm: 512).  sigma[SV_STATE] of a matrix: nonzero if its sweeps did not converge.
+constexpr int SV_STATE = 1023;
 int32_t svd_right(cbs_system* s, int32_t n, const double2* A, int32_t lda, double2* W, int32_t ldw, double* sigma,
                   int32_t* perm, bool hermitian, int32_t nbatch, hipStream_t st);
 // Eigenvalues w and unit eigenvectors V of a general complex matrix H (destroyed).

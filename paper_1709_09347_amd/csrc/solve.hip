@@ -323,6 +323,7 @@ struct HankelSvd {
   double* sig = nullptr;
   int32_t* perm = nullptr;
   std::vector<double> hsig;
+  bool right = false;   // from svd_right, which reports its convergence
   double t_mom_ms = 0, t_svd_ms = 0;   // per energy of the group
 };
 
@@ -357,10 +358,9 @@ static int32_t hankel_svds(cbs_system* s, const cbs_params* prm, const c64* V, c
   dump("T", h.T, (size_t)n * n * sizeof(c64), st);
   dump("Tl", h.Tl, (size_t)n * n * sizeof(c64), st);
   // the Rayleigh-Ritz extraction needs the right vectors only; the Hankel extraction U too
-  if (prm->extraction == CBS_HANKEL || getenv("CBS_SVD_SINGLE"))
-    CBS_TRY(svd(n, h.T, n, h.W, n, h.sig, h.perm, st));
-  else
-    CBS_TRY(svd_right(s, n, h.T, n, h.W, n, h.sig, h.perm, false, ne, st));
+  h.right = prm->extraction != CBS_HANKEL && getenv("CBS_SVD_SINGLE") == nullptr;
+  if (h.right) CBS_TRY(svd_right(s, n, h.T, n, h.W, n, h.sig, h.perm, false, ne, st));
+  else CBS_TRY(svd(n, h.T, n, h.W, n, h.sig, h.perm, st));
   dump("U", h.T, (size_t)n * n * sizeof(c64), st);
   dump("W", h.W, (size_t)n * n * sizeof(c64), st);
   dump("sigma", h.sig, (size_t)n * sizeof(double), st);
@@ -388,6 +388,10 @@ int32_t extract_S(cbs_system* s, double E, const cbs_params* prm, double noise, 
   if (!all_finite(n, hsig.data())) {
     set_error("non-finite singular values of the Hankel matrix (a linear solve diverged)");
     return CBS_ENONFINITE;
+  }
+  if (h.right && h.hsig[(size_t)at * 1024 + SV_STATE] != 0.0) {
+    set_error("the SVD of the Hankel matrix (order %d) did not converge", n);
+    return CBS_EEIG;
   }
   // rank: singular values above delta sigma_1 and above the noise floor of the moments,
   // the solves' largest residual relative to sigma_1: directions below it carry no
