@@ -361,7 +361,7 @@ static int32_t hankel_svds(cbs_system* s, const cbs_params* prm, const c64* V, c
   h.right = prm->extraction != CBS_HANKEL && getenv("CBS_SVD_SINGLE") == nullptr;
   if (h.right) CBS_TRY(svd_right(s, n, h.T, n, h.W, n, h.sig, h.perm, false, ne, st));
   else CBS_TRY(svd(n, h.T, n, h.W, n, h.sig, h.perm, st));
-  dump("U", h.T, (size_t)n * n * sizeof(c64), st);
+  if (!h.right) dump("U", h.T, (size_t)n * n * sizeof(c64), st);
   dump("W", h.W, (size_t)n * n * sizeof(c64), st);
   dump("sigma", h.sig, (size_t)n * sizeof(double), st);
   dump("perm", h.perm, (size_t)n * sizeof(int32_t), st);
