@@ -995,7 +995,7 @@ static int32_t enqueue_stencil_bra(BicgSolve& b, BicgVecs<T>& v, int32_t need, i
   CBS_TRY(launch_stencil<T>(s, true, l, v.tile_y, st));
   if (v.ev1) CBS_HIP(hipEventRecord(v.ev1, st));
   if (s->proj.n_atoms > 0 && !together)
-    CBS_TRY(launch_bra<T>(s, b.nruns, v.Pb[parity & 1], b.coef, b.sc.status, need, v.KT, b.signl, st, true,
+    CBS_TRY(launch_bra<T>(s, b.nruns, v.Pb[parity & 1], b.coef, b.sc.status, need, v.KT, b.signl, st,
                           l.list, l.count, false, b.bra_part));
   return CBS_OK;
 }
@@ -1029,7 +1029,7 @@ static int32_t enqueue_replacement(BicgSolve& b, int parity, hipStream_t st) {
     r.zseg = 4;   // the list is short: four z segments per tile shorten each workgroup's march
     CBS_TRY(launch_stencil<double>(s, false, r, b.hi.tile_y, st));
     if (na > 0)
-      CBS_TRY(launch_bra<double>(s, b.nruns, b.Y, b.coef, nullptr, 0, b.hi.KT, nullptr, st, true, rul, ruc,
+      CBS_TRY(launch_bra<double>(s, b.nruns, b.Y, b.coef, nullptr, 0, b.hi.KT, nullptr, st, rul, ruc,
                                  true));
   }
   if (b.mixed)

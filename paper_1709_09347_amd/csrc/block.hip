@@ -459,7 +459,7 @@ static int32_t blk_apply(BlockSolve& b, const Pair<double>* in, Pair<double>* ou
   const int32_t ty = s->tile_y[0] ? s->tile_y[0] : default_tile_y(s, sizeof(Pair<double>));
   CBS_TRY(launch_stencil<double>(s, false, l, ty, st));
   if (s->proj.n_atoms > 0) {
-    CBS_TRY(launch_bra<double>(s, b.nruns, in, b.coef, status, ST_ACT_HI, b.KT, nullptr, st, true));
+    CBS_TRY(launch_bra<double>(s, b.nruns, in, b.coef, status, ST_ACT_HI, b.KT, nullptr, st));
     CBS_TRY(launch_ket_add<double>(s, b.nruns, out, b.KT, st));
   }
   return CBS_OK;

@@ -350,7 +350,7 @@ int32_t autotune_tiles(cbs_system* s, hipStream_t st);
 template <typename R>
 int32_t launch_bra(const cbs_system* s, int32_t nruns, const void* v, const RunCoef* coef,
                    const int32_t* status, int32_t need_status, void* kt, double2* signl,
-                   hipStream_t st, bool phased, const int32_t* list = nullptr,
+                   hipStream_t st, const int32_t* list = nullptr,
                    const int32_t* count = nullptr, bool short_list = false, void* tile_part = nullptr);
 size_t bra_tile_part_bytes(const cbs_system* s, int32_t nruns);
 

@@ -7,10 +7,10 @@
 // coef(0) = c0, coef(1) = cp, coef(-1) = cm (P(z): 1, z, 1/z).  It is applied in two
 // passes per run:
 //   bra:  G[a][w'][i] = u_{a,i,w'}^T v            (one workgroup per atom and 16 runs,
-//                                                  MFMA; a plain kernel per atom and run)
+//                                                  MFMA; CBS_NO_MFMA=1: per atom and run)
 //         K[a][w][i]  = h_ai sum_w' coef(w'-w) G[a][w'][i]
 //   ket:  y(n) += sum_{entries e at point n} sum_i u_{e,i} K[a_e][w_e][i]
-// The ket runs inside the pointwise kernels (BiCG residual update, apply), reading
+// The ket runs inside the pointwise kernels (BiCG residual update, block BiCG), reading
 // point-ordered tables (per point, or per 64-point group and key in the update) so no two
 // threads ever add into the same point.
 // For BiCG the bra also yields the nonlocal part of sigma = pt^H P p:
@@ -696,12 +696,12 @@ static bool bra_plain() {
 template <typename R>
 int32_t launch_bra(const cbs_system* s, int32_t nruns, const void* v, const RunCoef* coef,
                    const int32_t* status, int32_t need_status, void* kt, double2* signl,
-                   hipStream_t st, bool phased, const int32_t* list, const int32_t* count,
+                   hipStream_t st, const int32_t* list, const int32_t* count,
                    bool short_list, void* tile_part) {
   const Projector& pr = s->proj;
   if (pr.n_atoms == 0 || nruns <= 0) return CBS_OK;
   const int pi = std::is_same<R, float>::value ? 1 : 0;
-  if (tile_part != nullptr && phased && !short_list && !bra_plain() && s->bra_tile[pi] > 0 &&
+  if (tile_part != nullptr && !short_list && !bra_plain() && s->bra_tile[pi] > 0 &&
       pr.bt[s->bra_tp[pi]].nslots > 0) {
     const ChunkTables& d = pr.bt[s->bra_tp[pi]];
     if ((list == nullptr) != (count == nullptr)) {
@@ -739,7 +739,7 @@ int32_t launch_bra(const cbs_system* s, int32_t nruns, const void* v, const RunC
     set_error("launch_bra: a run list needs its count");
     return CBS_EINVAL;
   }
-  if (phased && !bra_plain()) {
+  if (!bra_plain()) {
     a.nlogical = ((nruns + 15) / 16) * pr.n_atoms;
     const int grid = (a.nlogical + 7) / 8 * 8;
     const bool f32 = std::is_same<R, float>::value && lo_arith_fp32();
@@ -1034,7 +1034,7 @@ int32_t launch_ket_add(const cbs_system* s, int32_t nruns, void* q, const void* 
 
 #define INST(R)                                                                                   \
   template int32_t launch_bra<R>(const cbs_system*, int32_t, const void*, const RunCoef*,         \
-                                 const int32_t*, int32_t, void*, double2*, hipStream_t, bool,     \
+                                 const int32_t*, int32_t, void*, double2*, hipStream_t,           \
                                  const int32_t*, const int32_t*, bool, void*);                    \
   template int32_t launch_update<R>(const cbs_system*, int32_t, void*, const void*, const void*,  \
                                     const double2*, const int32_t*, int32_t, double*, size_t,     \

@@ -766,9 +766,9 @@ static int32_t tune_nonlocal(cbs_system* s, hipStream_t st, bool tune_update, st
     for (int sp : {1, 0}) {
       s->bra_nw[pi] = nw;
       s->bra_spread[pi] = sp;
-      CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st, true));
+      CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st));
       CBS_HIP(hipEventRecord(e0, st));
-      for (int k = 0; k < 3; ++k) CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st, true));
+      for (int k = 0; k < 3; ++k) CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st));
       CBS_HIP(hipEventRecord(e1, st));
       CBS_HIP(hipEventSynchronize(e1));
       float ms = 0;
@@ -797,10 +797,10 @@ static int32_t tune_nonlocal(cbs_system* s, hipStream_t st, bool tune_update, st
         for (int qx : {0, 1}) {
           s->bra_tile[pi] = rg;
           s->bra_qx[pi] = qx;
-          CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st, true, nullptr, nullptr, false, bpart));
+          CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st, nullptr, nullptr, false, bpart));
           CBS_HIP(hipEventRecord(e0, st));
           for (int k = 0; k < 3; ++k)
-            CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st, true, nullptr, nullptr, false, bpart));
+            CBS_TRY(launch_bra<R>(s, nr, buf, coef, status, 0, kt, dsc + nr, st, nullptr, nullptr, false, bpart));
           CBS_HIP(hipEventRecord(e1, st));
           CBS_HIP(hipEventSynchronize(e1));
           float ms = 0;
