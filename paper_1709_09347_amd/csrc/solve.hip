@@ -22,6 +22,7 @@
 #include "bicg.hpp"
 #include "cbs_internal.hpp"
 #include "dense.hpp"
+#include "groups.hpp"
 #include "ranking.hpp"
 
 namespace cbs {
@@ -329,9 +330,9 @@ struct HankelSvd {
 
 // Energies per group: the SVD of a small matrix is a chain on one CU, and those of other energies
 // run beside it.  One where the general SVD is asked for or the arrays are dumped.
-static int32_t svd_group(const cbs_params* prm, int32_t ne, double bytes_per_energy) {
+static int32_t svd_group(const cbs_params* prm, int32_t ne, double moment_bytes, double budget) {
   if (prm->extraction == CBS_HANKEL || getenv("CBS_SVD_SINGLE") || getenv("CBS_DUMP")) return 1;
-  return std::max(1, std::min({ne, 32, (int32_t)(64.0 * (1 << 20) / std::max(bytes_per_energy, 1.0))}));
+  return svd_group_size(ne, moment_bytes, prm->n_rhs * prm->n_mom, budget);
 }
 
 // Steps 2 (mu_k = V^H S_k) and 3 (Hankel SVD) from the moments S [ne][2M][L][N]; t0: when they were begun.
@@ -856,7 +857,7 @@ static int32_t solve_batched_queue(int32_t n_sys, cbs_system* const* systems, in
     CBS_HIP(hipMemcpyAsync(stt.data(), q.item_status, stt.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     CBS_HIP(hipMemcpyAsync(rr.data(), q.item_relres, rr.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     CBS_HIP(hipStreamSynchronize(st));
-    const int group = svd_group(prm, n_E, 0);
+    const int group = svd_group(prm, n_E, 0, budget);   // the queue holds the moments
     HankelSvd h;
     for (int e = 0; e < n_E; ++e) {
       const int ie = s * n_E + e, at = e % group;
@@ -1033,7 +1034,7 @@ extern "C" int32_t cbs_solve_batched(int32_t n_sys, cbs_system* const* systems, 
       NodeSolve ns;
       CBS_TRY(bicg_collect(solves[s], ns, st));
       const size_t s_len = (size_t)2 * prm->n_mom * L * sy->N;
-      const int group = svd_group(prm, ne, (double)s_len * sizeof(c64));
+      const int group = svd_group(prm, ne, (double)s_len * sizeof(c64), budget);
       HankelSvd h;
       c64* S = nullptr;
       for (int e = 0; e < ne; ++e) {
