@@ -638,9 +638,12 @@ size_t apply_kt_bytes(const cbs_system* s, int32_t n_vec, size_t real_bytes) {
 // other writes, so up to 576 items of two vectors the chip has room for both at once and a launch is
 // saved (48x48x32, 96 atoms, 8 complex128 vectors, whole call: 57 us, apart 64; 45x37x29, 60 atoms,
 // 8: 42, apart 51; 32x32x24, 40 atoms, 24: 46, apart 57).  Past that the table reads of four
-// vectors an item count for more: in complex64 together up to 768 items (48x48x32, 32 vectors: 78,
-// apart 83; 64x64x40, 170 atoms, 24: 118, apart 115), in complex128 in a launch of its own, where
-// the bra keeps L2 for its gathers (48x48x32, 32 vectors: 113, together 125).
+// vectors an item count for more: in complex128 in a launch of its own, where the bra keeps L2 for its
+// gathers (48x48x32, 32 vectors: 113, together 125), in complex64 together up to 768 items.  That line
+// is a middle one, as the cell counts too (together and apart, us): 32x32x24, 40 atoms, 640 items 54 and
+// 56; 48x48x32, 96 atoms, 672 items 66 and 73, 768 items 71 and 76, 864 items 86 and 90, 960 items 98 and
+// 91, 1056 items 95 and 102; 64x64x40, 170 atoms, 510 items 67 and 70, 680 items 82 and 77, 850 items 105
+// and 98, 1020 items 112 and 107.
 static int bra_shape(int32_t n_atoms, int32_t nv, bool f32, bool* together) {
   *together = true;
   if ((int64_t)n_atoms * ((nv + 1) / 2) <= 576) return 2;

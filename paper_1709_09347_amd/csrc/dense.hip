@@ -806,9 +806,6 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
   }
 }
 
-// One sweep over the columns of a block pair in LDS (nb = 2: all columns, `sweeps` times or until
-// converged).  flags[s]: the largest (|a_p^H a_q| / |a_p| |a_q|)^2 of sweep s, as bits; a launch of a
-// sweep whose predecessor was converged returns at once, so the host may queue several.
 __device__ double block_max_any(double v, double* sh) {
   v = wave_max_dpp(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
@@ -821,9 +818,12 @@ __device__ double block_max_any(double v, double* sh) {
 // LDS column stride: 128 bytes off a multiple of the 64 banks, so that the groups of a wave read
 // neighbouring columns from different banks.
 __host__ __device__ inline int sv_ldc(int n) { return (n + 7) / 16 * 16 + 8; }
-// RPL: rows of a column per lane, kept in registers from the inner products to the rotation.
 constexpr double SV_TOL2 = 1e-26;
 constexpr int SV_SWEEPS = 60;   // at most; also the flags of a matrix
+// One sweep over the columns of a block pair in LDS (nb = 2: all columns, `sweeps` times or until
+// converged).  flags[s]: the largest (|a_p^H a_q| / |a_p| |a_q|)^2 of sweep s, as bits; a launch of a
+// sweep whose predecessor was converged returns at once, so the host may queue several.
+// RPL: rows of a column per lane, kept in registers from the inner products to the rotation.
 template <int RPL>
 __global__ void __launch_bounds__(1024) k_svd_cols(int32_t n, int32_t bs, int32_t nb, int32_t round, int32_t sweep,
                                                    int32_t sweeps, int32_t gsize, c64* X, unsigned long long* flags) {
