@@ -595,7 +595,7 @@ __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, i
   __shared__ double pn[NW][64 * CPL];   // per wave: squared norms of the columns' remaining rows
   __shared__ c64 pd[NW][64 * CPL];      // per wave: products with the reflector
   __shared__ c64 rowk[64 * CPL];        // row k
-  int ex = 0;
+  double nmax = 0;   // norm of the largest column, the first pivot's
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i0 = wv * RW;
   c64 m[CPL][RW];
   int pos[CPL];   // step at which the column was taken, n: not yet
@@ -634,7 +634,7 @@ __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, i
     const double nx2 = lane_of(CPL == 1 ? nrm[0] : (pc ? nrm[CPL - 1] : nrm[0]), pl);
     const c64 xk = rowk[p];
     const double nx = sqrt(nx2), ak = sqrt(cabs2<double>(xk));
-    if (k == 0) ex = sv_exponent(nx);
+    nmax = fmax(nmax, nx);
     const c64 ph = ak > 0 ? make_double2(xk.x / ak, xk.y / ak) : make_double2(1, 0);
     const c64 alpha = zscale(ph, -nx);
     const double vv = nx2 + nx * ak, b = vv > 0 ? 1.0 / vv : 0.0;
@@ -681,6 +681,7 @@ __global__ void __launch_bounds__(256 * CPL) k_svd_qr(int32_t n, const c64* A, i
     __syncthreads();
   }
   // R[i][column] is the conjugate of X[position of the column][i]
+  const int ex = sv_exponent(nmax);
   if (threadIdx.x == 0) piv[n] = ex;
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
@@ -708,7 +709,7 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int CB = 4;
   const int NW = blockDim.x >> 6;
-  int ex = 0;
+  double nmax = 0;   // norm of the largest column, the first pivot's
   for (int j = wv; j < n; j += NW) {
     double t = 0;
     for (int i = lane; i < n; i += 64) {
@@ -748,7 +749,7 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
     nx2 = wave_sum_dpp(nx2);
     const c64 xk = M[k + p * n];
     const double nx = sqrt(nx2), ak = sqrt(cabs2<double>(xk));
-    if (k == 0) ex = sv_exponent(nx);
+    nmax = fmax(nmax, nx);
     const c64 ph = ak > 0 ? make_double2(xk.x / ak, xk.y / ak) : make_double2(1, 0);
     const c64 alpha = zscale(ph, -nx);
     // |v|^2 = 2 (nx^2 + nx |x_k|)
@@ -797,6 +798,7 @@ __global__ void __launch_bounds__(SV_T) k_svd_qr_big(int32_t n, const c64* A, in
   }
   __syncthreads();
   // X[j][k] = conj(R[k][j]), R[k][j] = M[k][order[j]] for j >= k
+  const int ex = sv_exponent(nmax);
   if (tid == 0) piv[n] = ex;
   for (int t = tid; t < n * n; t += blockDim.x) {
     const int j = t % n, k = t / n;
